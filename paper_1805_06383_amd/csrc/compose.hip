@@ -1168,10 +1168,11 @@ void Composer::run(fstc_result *out) {
       u32 *osrc = out_arcs.col(0) + arcs, *odst = out_arcs.col(1) + arcs,
           *oil = out_arcs.col(2) + arcs, *ool = out_arcs.col(3) + arcs;
       float *ow = reinterpret_cast<float *>(out_arcs.col(4)) + arcs;
-      if (nprod)  // product-merge sources interleave with the tiles' sources
+      if (R)
+        launch_compact(ma, aoff.as<u64>(), nbig ? bigoff.as<u64>() : nullptr, nbig, RB, nprod != 0, M,
+                       hvb.as<u32>(), osrc, odst, oil, ool, ow, s);
+      if (nprod)
         launch_compact_sources(ma, aoff.as<u64>(), M, hvb.as<u32>(), osrc, odst, oil, ool, ow, s);
-      else
-        launch_compact(ma, aoff.as<u64>(), nbig, M, hvb.as<u32>(), osrc, odst, oil, ool, ow, s);
     };
     // Early append: when the capacities they need, bounded since the first
     // synchronisation, are small, id assignment and the result append go to

@@ -331,15 +331,18 @@ void launch_assign_counted(const u32 *slots, const u64 *count, u32 cap, u32 base
                            hipStream_t s);
 void launch_newkeys(const u32 *newlist, u32 nnew, const u64 *hkeys, u32 vn2, int bq2, u64 *keys,
                     u32 *vals, hipStream_t s);
-// Result append of the level's merged arcs: the runs of merge tile t go to
-// output positions aoff[first source of t] + r, those of multi-block source u
-// to aoff[u] + r (aoff: exclusive scan of merged arcs per source), so the
-// output stays grouped by source id.  dst ids come from hvals.
-// M: merged arcs of the level (the output arrays' length from osrc on).
-void launch_compact(const MergeArgs &a, const u64 *aoff, u32 nbig, u64 M, const u32 *hvals,
-                    u32 *osrc, u32 *odst, u32 *oil, u32 *ool, float *ow, hipStream_t s);
-// Result append source by source (tstart[u] .. mend[u] - 1 to aoff[u] ...):
-// the form used when product-merge sources sit between tile-merged ones.
+// Result append of the level's merged arcs, so that the output stays grouped
+// by source id (aoff: exclusive scan of merged arcs per source): the runs of
+// merge tile t go to aoff[first source of t] + r, or, when product-merge
+// sources sit between the tile's (mixed), each run to aoff[its source] + its
+// number there; those of multi-block source u to aoff[u] + r (bigoff, RB: as
+// for merge_big; unused without multi-block sources).  dst ids come from
+// hvals.  M: merged arcs of the level (the output arrays' length from osrc).
+void launch_compact(const MergeArgs &a, const u64 *aoff, const u64 *bigoff, u32 nbig, u64 RB,
+                    bool mixed, u64 M, const u32 *hvals, u32 *osrc, u32 *odst, u32 *oil, u32 *ool,
+                    float *ow, hipStream_t s);
+// Result append of the product-merge sources (pk[u] != 0): tstart[u] ..
+// mend[u] - 1 to aoff[u] ....
 void launch_compact_sources(const MergeArgs &a, const u64 *aoff, u64 M, const u32 *hvals,
                             u32 *osrc, u32 *odst, u32 *oil, u32 *ool, float *ow, hipStream_t s);
 // Visited-table inserts and label lookups for every merged arc of the

@@ -2372,8 +2372,6 @@ __global__ void k_newkeys(const u32 *newlist, u32 nnew, const u64 *hkeys, u32 vn
   vals[i] = slot;
 }
 
-// Wave per segment of merged runs: merge tile i (i < ntiles) or multi-block
-// source big[i - ntiles]; lanes copy consecutive runs.
 // Target id of a merged arc's record word x: the id itself when it carries
 // kIdFlag (dense visited array only: its slots and ids are below 2^30, while
 // hash-table slots use bit 30 themselves), else the id the visited set now
@@ -2382,46 +2380,112 @@ __device__ __forceinline__ u32 target_id(const MergeArgs &a, u32 x, const u32 *h
   return (a.vn2 && (x & kIdFlag)) ? x & ~kIdFlag : hvals[x & ~kNewFlag];
 }
 
-__global__ __launch_bounds__(256) void k_compact(MergeArgs a, const u64 *aoff, u32 nbig, u64 M,
+// Result append of tile-merged and multi-block sources, kCompactB runs per
+// lane in flight.  Waves [0, ntiles wpt) share the merge tiles, wpt waves a
+// tile (each 64 kCompactB consecutive runs at a time); the others take 64
+// kCompactB positions each of the multi-block record space (position p of
+// [0, RB): run p - bigoff[i] of multi-block source i, while below its merged
+// count).  A run goes to aoff[first source of the tile] + its number in the
+// tile, or, on levels with product-merge sources between the tile's (MIXED),
+// to aoff[u] + its number in its own source u.  Bound by the temp record
+// read and the five column stores.  One wave for a whole multi-block source
+// (and one per tile) took 17.3 ms for one source of 2.7M arcs and 3.3 ms for
+// one of 0.5M, a chain of one load and one lookup per 64 arcs.
+constexpr int kCompactB = 4;
+template <bool MIXED>
+__global__ __launch_bounds__(256) void k_compact(MergeArgs a, const u64 *aoff, const u64 *bigoff,
+                                                 u32 nbig, u64 RB, u32 wpt, u64 M,
                                                  const u32 *hvals, u32 *osrc, u32 *odst,
                                                  u32 *oil, u32 *ool, float *ow) {
+  constexpr u32 kChunk = kWave * kCompactB;
   const u32 lane = lane_id();
   const u64 wv = ((u64)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
-  if (wv >= a.ntiles + nbig) return;
-  u64 tbase, obase;
-  u32 cnt;
-  if (wv < a.ntiles) {
-    cnt = a.tile_runs[wv];
-    if (cnt == 0) return;
-    const uint4 td = a.tiles[wv];
-    tbase = wv * a.window + td.z;
-    obase = aoff[td.x];
+  const u64 tw = a.ntiles * wpt;
+  u64 tp[kCompactB], op[kCompactB];  // temp and output position of this lane's runs
+  bool act[kCompactB];
+  auto write = [&]() {
+    uint4 rec[kCompactB];
+    u32 u[kCompactB];
+#pragma unroll
+    for (int j = 0; j < kCompactB; ++j) {
+      const u64 t = act[j] ? tp[j] : 0;
+      rec[j] = a.temp[t];
+      u[j] = a.runsrc[t];
+    }
+    if (MIXED) {
+#pragma unroll
+      for (int j = 0; j < kCompactB; ++j)
+        if (act[j]) op[j] = aoff[u[j]] + (tp[j] - a.tstart[u[j]]);
+    }
+    bool bad = false;
+    u32 d[kCompactB];
+#pragma unroll
+    for (int j = 0; j < kCompactB; ++j) {
+      // impossible: counts agree with aoff
+      if (act[j] && op[j] >= M) {
+        bad = true;
+        act[j] = false;
+      }
+      d[j] = act[j] ? target_id(a, rec[j].x, hvals) : 0u;
+    }
+#pragma unroll
+    for (int j = 0; j < kCompactB; ++j) {
+      if (!act[j]) continue;
+      const u64 k = op[j];
+      osrc[k] = a.lo + u[j];
+      odst[k] = d[j];
+      oil[k] = rec[j].y;
+      ool[k] = rec[j].z;
+      ow[k] = __uint_as_float(rec[j].w);
+    }
+    if (bad) set_error(&a.st->err, kErrBounds);
+  };
+  if (wv < tw) {
+    const u64 tile = wv / wpt;
+    const u32 k = (u32)(wv % wpt), cnt = a.tile_runs[tile];
+    if ((u64)k * kChunk >= cnt) return;
+    const uint4 td = a.tiles[tile];
+    const u64 tbase = tile * a.window + td.z;
+    if (tbase + cnt > a.R) {  // impossible: a tile has at most as many runs as records
+      if (lane == 0) set_error(&a.st->err, kErrBounds);
+      return;
+    }
+    const u64 obase = MIXED ? 0 : aoff[td.x];
+    for (u32 r0 = k * kChunk; r0 < cnt; r0 += wpt * kChunk) {
+#pragma unroll
+      for (int j = 0; j < kCompactB; ++j) {
+        const u32 r = r0 + j * kWave + lane;
+        act[j] = r < cnt;
+        tp[j] = tbase + r;
+        op[j] = obase + r;
+      }
+      write();
+    }
   } else {
-    const u32 u = a.big[wv - a.ntiles];
-    tbase = a.tstart[u];
-    cnt = (u32)(a.mend[u] - tbase);
-    obase = aoff[u];
-  }
-  if (tbase + cnt > a.R || obase + cnt > M) {  // impossible: counts agree with aoff
-    if (lane == 0) set_error(&a.st->err, kErrBounds);
-    return;
-  }
-  for (u32 r = lane; r < cnt; r += kWave) {
-    const uint4 rec = a.temp[tbase + r];
-    const u64 k = obase + r;
-    osrc[k] = a.lo + a.runsrc[tbase + r];
-    odst[k] = target_id(a, rec.x, hvals);
-    oil[k] = rec.y;
-    ool[k] = rec.z;
-    ow[k] = __uint_as_float(rec.w);
+    const u64 p0 = (wv - tw) * kChunk;
+    if (p0 >= RB) return;
+#pragma unroll
+    for (int j = 0; j < kCompactB; ++j) {
+      const u64 p = p0 + j * kWave + lane;
+      act[j] = p < RB;
+      tp[j] = op[j] = 0;
+      if (!act[j]) continue;
+      const u32 i = (u32)last_le<u64>(bigoff, nbig, p);
+      const u32 u = a.big[i];
+      const u64 t0 = a.tstart[u], r = p - bigoff[i];
+      act[j] = t0 + r < a.mend[u] && t0 + r < a.R;
+      tp[j] = t0 + r;
+      op[j] = aoff[u] + r;
+    }
+    write();
   }
 }
 
-// Result append, sources in consecutive groups of 64 per wave: their merged
-// arcs are consecutive in the result (aoff is the exclusive scan of the
-// per-source counts mend - tstart), so the wave walks the group's output
-// range 64 entries at a time, each lane finding its entry's source by a
-// binary search over the group's offsets held one per lane.
+// Result append of product-merge sources (the level's others have n = 0
+// here and are k_compact's), consecutive groups of 64 sources per wave: the
+// wave walks the group's merged arcs 64 at a time, each lane finding its
+// entry's source by a binary search over the group's running counts held one
+// per lane.
 __global__ __launch_bounds__(256) void k_compact_sources(MergeArgs a, const u64 *aoff, u64 M,
                                                          const u32 *hvals, u32 *osrc, u32 *odst,
                                                          u32 *oil, u32 *ool, float *ow) {
@@ -2429,15 +2493,15 @@ __global__ __launch_bounds__(256) void k_compact_sources(MergeArgs a, const u64 
   const u64 u0 = ((u64)blockIdx.x * blockDim.x + threadIdx.x) / kWave * kWave;
   if (u0 >= a.nsrc) return;
   const u64 u = u0 + lane;
-  const bool in = u < a.nsrc;
+  const bool in = u < a.nsrc && a.pk[u] != 0;
+  if (__ballot(in) == 0) return;
   const u64 tb = in ? a.tstart[u] : 0, n = in ? a.mend[u] - tb : 0;
   const u64 ob = in ? aoff[u] : 0;
   const u64 incl = wave_inclusive_sum(n);
-  const u64 rel = incl - n;  // this source's first entry, relative to the group's
+  const u64 rel = incl - n;  // this source's first entry in the walk
   const u64 total = __shfl(incl, kWave - 1, kWave);
-  const u64 ob0 = __shfl(ob, 0, kWave);
   // impossible: counts agree with aoff and the temp ranges lie in temp
-  const bool bad = (in && (ob != ob0 + rel || tb + n > a.R + a.prodpos)) || ob0 + total > M;
+  const bool bad = in && (tb + n > a.R + a.prodpos || ob + n > M);
   if (__ballot(bad)) {
     if (lane == 0) set_error(&a.st->err, kErrBounds);
     return;
@@ -2454,9 +2518,10 @@ __global__ __launch_bounds__(256) void k_compact_sources(MergeArgs a, const u64 
     }
     const u64 rs = __shfl(rel, (int)s, kWave);
     const u64 ts = __shfl(tb, (int)s, kWave);
+    const u64 os = __shfl(ob, (int)s, kWave);
     if (p < total) {
       const uint4 rec = a.temp[ts + (p - rs)];
-      const u64 k = ob0 + p;
+      const u64 k = os + (p - rs);
       osrc[k] = a.lo + (u32)(u0 + s);
       odst[k] = target_id(a, rec.x, hvals);
       oil[k] = rec.y;
@@ -2862,12 +2927,26 @@ void launch_newkeys(const u32 *newlist, u32 nnew, const u64 *hkeys, u32 vn2, int
                      nnew, hkeys, vn2, bq2, keys, vals);
 }
 
-void launch_compact(const MergeArgs &a, const u64 *aoff, u32 nbig, u64 M, const u32 *hvals,
-                    u32 *osrc, u32 *odst, u32 *oil, u32 *ool, float *ow, hipStream_t s) {
-  const u64 nw = a.ntiles + nbig;
-  if (!nw || !M) return;
-  hipLaunchKernelGGL(k_compact, dim3((unsigned)ceil_div(nw, 256 / kWave)), dim3(256), 0, s, a, aoff,
-                     nbig, M, hvals, osrc, odst, oil, ool, ow);
+void launch_compact(const MergeArgs &a, const u64 *aoff, const u64 *bigoff, u32 nbig, u64 RB,
+                    bool mixed, u64 M, const u32 *hvals, u32 *osrc, u32 *odst, u32 *oil, u32 *ool,
+                    float *ow, hipStream_t s) {
+  if (!M) return;
+  // waves per tile: enough in all to fill the chip when a level has few
+  // tiles (a tile has at most 16 chunks of 256 runs; with a wave per tile a
+  // level of 40 full tiles kept 40 of 8192 wave slots busy)
+  const u64 target = (u64)compute_units() * 32;
+  const u32 wpt = a.ntiles ? (u32)std::min<u64>(kMergeCap / (kWave * kCompactB),
+                                                std::max<u64>(1, ceil_div(target, a.ntiles)))
+                           : 1u;
+  const u64 nw = a.ntiles * wpt + ceil_div(RB, (u64)kWave * kCompactB);
+  if (!nw) return;
+  const dim3 g((unsigned)ceil_div(nw, 256 / kWave));
+  if (mixed)
+    hipLaunchKernelGGL(k_compact<true>, g, dim3(256), 0, s, a, aoff, bigoff, nbig, RB, wpt, M, hvals,
+                       osrc, odst, oil, ool, ow);
+  else
+    hipLaunchKernelGGL(k_compact<false>, g, dim3(256), 0, s, a, aoff, bigoff, nbig, RB, wpt, M,
+                       hvals, osrc, odst, oil, ool, ow);
 }
 
 u64 newlist_waves(const MergeArgs &a, u64 RB) {

@@ -68,6 +68,9 @@ constexpr u64 kJoinBoundSyms = u64(1) << 22;
 // Largest state or result arrays sized from the level's bounds (see the
 // early append in the level loop).
 constexpr u64 kEarlyBytes = u64(1) << 30;
+// Largest pair space whose ordered ids are given before the host reads a
+// level's counts (a pass over the dense visited array).
+constexpr u64 kIdScanPairs = u64(1) << 22;
 // Largest temp (entries x 20 bytes) reserved for a speculative product merge.
 constexpr u64 kSpecBytes = u64(1) << 30;
 inline size_t grown(size_t cap_bytes) { return cap_bytes * (cap_bytes < kFastGrowBytes ? 4 : 2); }
@@ -574,6 +577,13 @@ void Composer::run(fstc_result *out) {
                              4096, 2 * std::min<u64>(pairspace, m1.num_arcs + m2.num_arcs + 1))));
   if (!dense_vis && o.hash_min_log2)
     hcap = std::max<u64>(hcap, std::min<u64>(kMaxHashCap, 1ull << o.hash_min_log2));
+  // Ids can be given on the device before the host knows how many: in list
+  // order, or in (q1, q2) order by a pass over a small dense visited array
+  // (16 MB: about 8 us; a larger one costs more than the host's turnaround
+  // it saves on a short level).
+  const bool ids_by_scan = !o.deterministic_ids || (dense_vis && pairspace <= kIdScanPairs);
+  Buf claimb(&A);
+  auto claim_tmp = [&]() { return claimb.ensure(claim_temp_bytes(pairspace)); };
   if (dense_vis) {
     hvb.ensure(hcap * 4);
     fill_u32(hvb.as<u32>(), kUnvisited, hcap, s);
@@ -658,8 +668,7 @@ void Composer::run(fstc_result *out) {
       rkey(&level_tmp), rw(&level_tmp), temp(&level_tmp), newlist(&level_tmp), stmp(&level_tmp),
       dk(&level_tmp), dv(&level_tmp), dka(&level_tmp), dva(&level_tmp), dtmp(&level_tmp),
       tiles_e(&level_tmp), tiles_m(&level_tmp), tstart(&level_tmp), mend(&level_tmp),
-      sortlist(&level_tmp), tile_runs(&level_tmp), wcnt(&level_tmp), woff(&level_tmp),
-      wtmp(&level_tmp), runsrc(&level_tmp), newbits(&level_tmp);
+      sortlist(&level_tmp), tile_runs(&level_tmp), runsrc(&level_tmp);
 
   bool status_clear = true;  // level counters of *dst all zero
   // small levels (level.hpp, k_small_levels): one workgroup runs them, and
@@ -793,7 +802,7 @@ void Composer::run(fstc_result *out) {
     {
       const u64 maxk_t = std::min<u64>(maxp1 * maxp2, 64);
       if (tiny_ok && !tiny_off && product && dense_vis && last_direct && nsrc <= kTinySources &&
-          !o.deterministic_ids && !o.max_arcs && (arcs + (u64)nsrc * maxk_t) * 20 <= kEarlyBytes) {
+          ids_by_scan && !o.max_arcs && (arcs + (u64)nsrc * maxk_t) * 20 <= kEarlyBytes) {
         out_arcs.grow(arcs + (u64)nsrc * maxk_t, arcs);
         const u64 newcap_t = std::min<u64>((u64)nsrc * maxk_t, pairspace - n_states);
         sq1b.grow_keep((n_states + newcap_t) * 4, n_states * 4);
@@ -828,7 +837,7 @@ void Composer::run(fstc_result *out) {
         const u32 seqt = next_publication();
         T.at(kCount);
         launch_product_level(la, mt, poff.as<u64>(), newoff.as<u64>(), (u32)n_states,
-                             sq1b.as<u32>(), sq2b.as<u32>(), hs_dev, seqt, s);
+                             sq1b.as<u32>(), sq2b.as<u32>(), o.deterministic_ids != 0, hs_dev, seqt, s);
         T.at(kNone);
         wait_published(seqt);
         if (!hs->st.declined) {
@@ -910,9 +919,12 @@ void Composer::run(fstc_result *out) {
     // Direct product level: the speculative product kernel writes its merged
     // arcs straight into the result (grown to hold every source's largest
     // table first); when the level turns out to have records it writes
-    // nothing and the level takes the usual path.  Deterministic ids (a sort
-    // of the new pairs) and an arc cap keep the usual path.
-    const bool direct = spec && !o.deterministic_ids && !o.max_arcs &&
+    // nothing and the level takes the usual path.  An arc cap, and ordered ids
+    // over a large pair space, keep the usual path.
+    // (small pair spaces in either numbering: 2 x 3.5 us a level of 10^6 pairs
+    // against 7.5 us for the per-source form, whose lanes read every entry)
+    const bool direct_scan = o.deterministic_ids || pairspace <= kIdScanPairs;
+    const bool direct = spec && ids_by_scan && !o.max_arcs &&
                         (arcs + (u64)nsrc * maxk) * 20 <= kEarlyBytes;
     if (spec) {
       temp.ensure((u64)nsrc * maxk * sizeof(uint4));
@@ -1004,7 +1016,11 @@ void Composer::run(fstc_result *out) {
       md.out_ol = out_arcs.col(3);
       md.out_w = reinterpret_cast<float *>(out_arcs.col(4));
       md.out_base = arcs;
-      launch_assign_direct(md, newoff.as<u64>(), (u32)n_states, sq1b.as<u32>(), sq2b.as<u32>(), s);
+      if (direct_scan)
+        launch_claim_ids(hvb.as<u32>(), pairspace, vn2, (u32)n_states, sq1b.as<u32>(),
+                         sq2b.as<u32>(), claim_tmp(), md.R_dev, s);
+      else
+        launch_assign_direct(md, newoff.as<u64>(), (u32)n_states, sq1b.as<u32>(), sq2b.as<u32>(), s);
       T.at(kNone);
     }
     wait_published(seq_wait);
@@ -1177,11 +1193,11 @@ void Composer::run(fstc_result *out) {
     // Early append: when the capacities they need, bounded since the first
     // synchronisation, are small, id assignment and the result append go to
     // the stream before the host reads the level's totals, and the GPU runs
-    // them while the host waits (deterministic ids and an arc cap need the
-    // exact counts first).
+    // them while the host waits (an arc cap, and ordered ids over a large
+    // pair space, need the exact counts first).
     const bool direct_level = direct && R == 0;  // the speculative launch wrote the result
     bool assigned = false;                        // ids and arcs of the level are in place
-    const bool early = !direct_level && !o.no_reduction && !o.deterministic_ids && !o.max_arcs &&
+    const bool early = !direct_level && !o.no_reduction && ids_by_scan && !o.max_arcs &&
                        (n_states + newcap) * 8 <= kEarlyBytes &&
                        (arcs + R + prodpos) * 20 <= kEarlyBytes;
     last_direct = direct_level;
@@ -1229,7 +1245,11 @@ void Composer::run(fstc_result *out) {
       ma.out_base = arcs;
       sq1b.grow_keep((n_states + newcap) * 4, n_states * 4);
       sq2b.grow_keep((n_states + newcap) * 4, n_states * 4);
-      launch_assign_direct(ma, newoff.as<u64>(), (u32)n_states, sq1b.as<u32>(), sq2b.as<u32>(), s);
+      if (direct_scan)
+        launch_claim_ids(hvb.as<u32>(), pairspace, vn2, (u32)n_states, sq1b.as<u32>(),
+                         sq2b.as<u32>(), claim_tmp(), nullptr, s);
+      else
+        launch_assign_direct(ma, newoff.as<u64>(), (u32)n_states, sq1b.as<u32>(), sq2b.as<u32>(), s);
       T.at(kNone);
       wait_published(seq2);
       status_clear = true;  // the totals scan cleared the level counters
@@ -1286,38 +1306,27 @@ void Composer::run(fstc_result *out) {
       // merged arcs per source (mend - tstart) scanned into result offsets;
       // the per-source joined pairs (records, or the product merge's terms)
       // summed for the level's product-merge pairs
-      // (on a level of product-merge sources alone, also the new pairs
-      // each source claimed, for the new-pair list)
-      const bool prod_only = R == 0;
       {
-        ScanJob jobs[3] = {{mend.p, true, aoff.as<u64>()}, {cnt.p, true, ptot.as<u64>()},
-                           {newc.p, false, newoff.as<u64>()}};
+        ScanJob jobs[2] = {{mend.p, true, aoff.as<u64>()}, {cnt.p, true, ptot.as<u64>()}};
         jobs[0].sub = tstart.as<u64>();
         jobs[1].total_only = true;
-        exclusive_scan_lb(jobs, prod_only ? 3 : 2, nsrc, lb(nsrc), &dst->scan_ctr, &dst->err, s);
+        exclusive_scan_lb(jobs, 2, nsrc, lb(nsrc), &dst->scan_ctr, &dst->err, s);
       }
       launch_emit_tiles(ma, s);
-      const u64 *new_total = nullptr;
-      if (prod_only) {
-        launch_newlist_sources(ma, newoff.as<u64>(), s);
-        new_total = newoff.as<u64>() + nsrc;
-      } else {
-        const u64 nw = newlist_waves(ma, RB);
-        wcnt.ensure(nw * 4);
-        woff.ensure((nw + 1) * 8);
-        new_total = launch_newlist(ma, nbig ? bigoff.as<u64>() : nullptr, nbig, RB,
-                                   wcnt.as<u32>(), woff.as<u64>(), lb(nw), s);
-      }
+      if (nprod) launch_newlist_product(ma, s);
       const u32 seq2 = next_publication();
-      launch_merged_total(aoff.as<u64>() + nsrc, new_total, ptot.as<u64>() + nsrc, ma, hs_dev,
-                          seq2, s);
+      launch_merged_total(aoff.as<u64>() + nsrc, nullptr, ptot.as<u64>() + nsrc, ma, hs_dev, seq2, s);
       if (early) {
         T.at(kAssign);
         sq1b.grow_keep((n_states + newcap) * 4, n_states * 4);
         sq2b.grow_keep((n_states + newcap) * 4, n_states * 4);
-        launch_assign_counted(newlist.as<u32>(), new_total, (u32)newcap, (u32)n_states,
-                              hkb.as<u64>(), hvb.as<u32>(), vn2, sq1b.as<u32>(), sq2b.as<u32>(),
-                              s);
+        if (o.deterministic_ids)
+          launch_claim_ids(hvb.as<u32>(), pairspace, vn2, (u32)n_states, sq1b.as<u32>(),
+                           sq2b.as<u32>(), claim_tmp(), nullptr, s);
+        else
+          launch_assign_counted(newlist.as<u32>(), &dst->new_count, (u32)newcap, (u32)n_states,
+                                hkb.as<u64>(), hvb.as<u32>(), vn2, sq1b.as<u32>(),
+                                sq2b.as<u32>(), s);
         append(R + prodpos);
       }
       T.at(kNone);
@@ -1415,19 +1424,13 @@ void Composer::run(fstc_result *out) {
           *ool = out_arcs.col(3);
       float *ow = reinterpret_cast<float *>(out_arcs.col(4));
       T.at(kMerge);
-      const u64 nwords = ceil_div(hcap, 32);
-      newbits.ensure(nwords * 4);
-      fill_u32(newbits.as<u32>(), 0, nwords, s);
-      launch_unreduced(ma, wide_keys, newbits.as<u32>(), osrc + arcs, odst + arcs, oil + arcs,
-                       ool + arcs, ow + arcs, s);
-      const u64 nw = bitlist_waves(nwords);
-      wcnt.ensure(nw * 4);
-      woff.ensure((nw + 1) * 8);
-      wtmp.ensure(scan_temp_bytes(nw));
-      launch_bitlist(newbits.as<u32>(), nwords, newlist.as<u32>(), newcap, wcnt.as<u32>(),
-                     woff.as<u64>(), wtmp.p, dst, s);
+      launch_unreduced(ma, wide_keys, osrc + arcs, odst + arcs, oil + arcs, ool + arcs, ow + arcs, s);
+      const u32 seq2 = next_publication();
+      ma.ntiles = 0;  // no merge tiles to add up
+      launch_merged_total(roff.as<u64>() + nsrc, nullptr, roff.as<u64>() + nsrc, ma, hs_dev, seq2, s);
       T.at(kNone);
-      sync_status();
+      wait_published(seq2);
+      status_clear = true;  // k_merged_total cleared the level counters
       nnew = hs->st.nnew;
       merged = R;
     }
@@ -1444,7 +1447,20 @@ void Composer::run(fstc_result *out) {
       sq1b.grow_keep(ns_new * 4, n_states * 4);
       sq2b.grow_keep(ns_new * 4, n_states * 4);
       const u32 *slots = newlist.as<u32>();
-      if (o.deterministic_ids && nnew > 1) {
+      // ordered ids: ranked in one launch up to kRankMax new pairs; a larger
+      // level takes a pass over the dense visited array while that is cheaper
+      // than a radix sort (0.9 ps a pair of the array against about 60 us and
+      // 150 ps a new pair), or the sort
+      const bool ordered = o.deterministic_ids && nnew > 1;
+      const bool rank = ordered && nnew <= kRankMax;
+      const bool scan = ordered && !rank && dense_vis && pairspace <= kDensePairs + 160ull * nnew;
+      if (rank) {
+        launch_rank_assign(slots, &dst->new_count, nnew, (u32)n_states, hkb.as<u64>(),
+                           hvb.as<u32>(), vn2, sq1b.as<u32>(), sq2b.as<u32>(), s);
+      } else if (scan) {
+        launch_claim_ids(hvb.as<u32>(), pairspace, vn2, (u32)n_states, sq1b.as<u32>(),
+                         sq2b.as<u32>(), claim_tmp(), nullptr, s);
+      } else if (ordered) {
         const int bq1 = (int)bits_for(m1.num_states - 1), bq2 = (int)bits_for(m2.num_states - 1);
         dk.ensure((u64)nnew * 8); dv.ensure((u64)nnew * 4);
         dka.ensure((u64)nnew * 8); dva.ensure((u64)nnew * 4);
@@ -1454,8 +1470,9 @@ void Composer::run(fstc_result *out) {
                          bq1 + bq2, dtmp.p, s);
         slots = dv.as<u32>();
       }
-      launch_assign(slots, nnew, (u32)n_states, hkb.as<u64>(), hvb.as<u32>(), vn2, sq1b.as<u32>(),
-                    sq2b.as<u32>(), s);
+      if (!rank && !scan)
+        launch_assign(slots, nnew, (u32)n_states, hkb.as<u64>(), hvb.as<u32>(), vn2,
+                      sq1b.as<u32>(), sq2b.as<u32>(), s);
       if (o.no_reduction)
         launch_fix_dst(out_arcs.col(1) + arcs, merged, hvb.as<u32>(), s);
       else

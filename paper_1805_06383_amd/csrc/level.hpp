@@ -47,7 +47,7 @@ struct Status {
   u32 ngen;           // product-merge sources listed for the one-per-wave kernel
   u32 ngrp;           // sources listed for the 16-lane joins
   u32 declined;       // nonzero: the one-workgroup product level did not take the level
-  u32 pad1;
+  u32 new_count;      // new pairs of the last merged level (kept when the counters clear)
 };
 static_assert(offsetof(Status, nprod) % 8 == 0 &&
                   offsetof(Status, nprod_mfma) == offsetof(Status, nprod) + 4,
@@ -326,7 +326,7 @@ void launch_assign(const u32 *slots, u32 nnew, u32 base, const u64 *hkeys, u32 *
                    u32 *sq1, u32 *sq2, hipStream_t s);
 // The same for min(*count, cap) new pairs, the count read on the device
 // (the host need not know it yet); nothing when count is NULL.
-void launch_assign_counted(const u32 *slots, const u64 *count, u32 cap, u32 base,
+void launch_assign_counted(const u32 *slots, const u32 *count, u32 cap, u32 base,
                            const u64 *hkeys, u32 *hvals, u32 vn2, u32 *sq1, u32 *sq2,
                            hipStream_t s);
 void launch_newkeys(const u32 *newlist, u32 nnew, const u64 *hkeys, u32 vn2, int bq2, u64 *keys,
@@ -348,19 +348,21 @@ void launch_compact_sources(const MergeArgs &a, const u64 *aoff, u64 M, const u3
 // Visited-table inserts and label lookups for every merged arc of the
 // tile-merged sources (merge_big does its own).
 void launch_emit_tiles(const MergeArgs &a, hipStream_t s);
-// New-state list of the level from the claimed-slot flags of the tile runs,
-// the multi-block runs and the product-merge slots.  Returns the device
-// address of its length (for launch_merged_total), or NULL when there is
-// nothing to list.
-// wcnt: newlist_waves(a, RB) u32; woff: that + 1 u64.
-// scan_state: scan_lb_state_bytes(newlist_waves(a, RB)) bytes of single-pass
-// scan state (see exclusive_scan_lb).
-u64 newlist_waves(const MergeArgs &a, u64 RB);
-// The same list for a level whose sources all took the product merge (no
-// records): newoff, the exclusive scan of a.newc, gives each source's first
-// list entry; 16 lanes per source with claims write its claimed slots in
-// temp order.
-void launch_newlist_sources(const MergeArgs &a, const u64 *newoff, hipStream_t s);
+// The merge kernels append the slots they claim to a.newlist (a.st->nnew of
+// them, in any order); the product merge's kernels only flag them in their
+// temp entries, and this adds those to the list.
+void launch_newlist_product(const MergeArgs &a, hipStream_t s);
+// ids base, base + 1, ... for the *count new pairs of the list in (q1, q2)
+// order, nothing when there are more than cap (vn2: as launch_assign).
+constexpr u32 kRankMax = 16384;
+void launch_rank_assign(const u32 *list, const u32 *count, u32 cap, u32 base, const u64 *hkeys,
+                        u32 *hvals, u32 vn2, u32 *sq1, u32 *sq2, hipStream_t s);
+// The same for every entry of the dense visited array (n pairs) that the
+// level claimed; temp: claim_temp_bytes(n).  skip_if (may be NULL): nothing
+// is done when that device word is nonzero.
+size_t claim_temp_bytes(u64 n);
+void launch_claim_ids(u32 *vis, u64 n, u32 vn2, u32 base, u32 *sq1, u32 *sq2, void *temp,
+                      const u64 *skip_if, hipStream_t s);
 // Direct product level (see MergeArgs::out_src): ids base + newoff[u] + i for
 // the claimed entries of source u in entry order (visited array, state
 // arrays and the entries' target column).  The other targets the level
@@ -376,20 +378,12 @@ void launch_fix_marked(const MergeArgs &a, u64 n, hipStream_t s);
 // out_base + aoff[u] (aoff: exclusive scan of merged arcs per source), through
 // `tmp` (20 n bytes).
 void launch_close_holes(const MergeArgs &a, const u64 *aoff, u64 n, void *tmp, hipStream_t s);
-const u64 *launch_newlist(const MergeArgs &a, const u64 *bigoff, u32 nbig, u64 RB, u32 *wcnt,
-                          u64 *woff, void *scan_state, hipStream_t s);
 // Composition without reduction: every record of the level becomes an arc
 // (osrc.. at [0, R)), its target pair claimed in the visited table and each
-// new claim flagged in `newbits` (one bit per table slot, cleared by the
-// caller); odst receives table slots until launch_fix_dst maps them to ids.
-void launch_unreduced(const MergeArgs &a, bool wide_keys, u32 *newbits, u32 *osrc, u32 *odst,
-                      u32 *oil, u32 *ool, float *ow, hipStream_t s);
-// New-state list from the claim bitmap, in slot order (st->nnew = its
-// length).  wcnt: bitlist_waves(nwords) u32; woff: that + 1 u64; scan_tmp:
-// scan_temp_bytes(bitlist_waves(nwords)) bytes.
-u64 bitlist_waves(u64 nwords);
-void launch_bitlist(const u32 *bits, u64 nwords, u32 *list, u64 cap, u32 *wcnt, u64 *woff,
-                    void *scan_tmp, Status *st, hipStream_t s);
+// new claim appended to a.newlist (a.st->nnew); odst receives table slots
+// until launch_fix_dst maps them to ids.
+void launch_unreduced(const MergeArgs &a, bool wide_keys, u32 *osrc, u32 *odst, u32 *oil, u32 *ool,
+                      float *ow, hipStream_t s);
 // dst[k] = hvals[dst[k]] for k < n.
 void launch_fix_dst(u32 *dst, u64 n, const u32 *hvals, hipStream_t s);
 void launch_finals(const u32 *sq1, const u32 *sq2, u64 n, const uint8_t *f1, const uint8_t *f2,
@@ -422,9 +416,11 @@ u64 level_clear_mask();
 // nothing) and the level takes the per-level kernels.  The result columns
 // must hold out_base + nsrc * 64 rows and the state arrays base + nsrc * 64
 // entries; la's pk, phdr, tstart, mend, newc and cnt arrays and poff (also
-// ma.poff, written here) nsrc + 1.
+// ma.poff, written here) nsrc + 1.  ordered: the new pairs' ids in (q1, q2)
+// order.
 constexpr u32 kTinySources = 64;
 void launch_product_level(const LevelArgs &la, const MergeArgs &ma, u64 *poff, u64 *newoff,
-                          u32 base, u32 *sq1, u32 *sq2, Status *host, u32 seq, hipStream_t s);
+                          u32 base, u32 *sq1, u32 *sq2, bool ordered, Status *host, u32 seq,
+                          hipStream_t s);
 
 }  // namespace fstc

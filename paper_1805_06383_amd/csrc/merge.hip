@@ -20,7 +20,8 @@
 //     once per merged arc, after merging, so repeated targets cost one probe
 //     per distinct arc rather than one per joined arc pair;
 //   * pairs claimed by the CAS are appended to a new-state list, and get the
-//     next ids once the level is merged (launch_assign).
+//     next ids once the level is merged (launch_assign, or in (q1, q2) order
+//     launch_rank_assign / launch_claim_ids).
 #include "level.hpp"
 #include "product.hpp"
 #include "radix_rank.hpp"
@@ -199,15 +200,16 @@ __device__ __forceinline__ void visit_batch(const MergeArgs &a, const u64 (&key)
 
 // The part pairs of B merged arcs -> visited-table insert of the target pair
 // (r1, r2) and the run record (slot | kNewFlag if claimed, a, c, weight) at
-// temp[tpos], source u at runsrc[tpos] (the new-state list is built from
-// these flags by k_newlist, without a shared counter).  A target that
-// already has an id in the dense array is recorded as id | kIdFlag, so the
-// result append needs no visited-array lookup for it.
+// temp[tpos], source u at runsrc[tpos]; claim[i] = the slot this call
+// claimed for item i, else kNoClaim.  A target that already has an id in the
+// dense array is recorded as id | kIdFlag, so the result append needs no
+// visited-array lookup for it.
+constexpr u32 kNoClaim = 0xffffffffu;  // slots are below 2^31
 template <int B>
 __device__ __forceinline__ void emit_parts(const MergeArgs &a, const bool (&act)[B],
                                            const u32 (&u)[B], const uint2 (&P1)[B],
                                            const uint2 (&P2)[B], const u64 (&tpos)[B],
-                                           const float (&w)[B]) {
+                                           const float (&w)[B], u32 (&claim)[B]) {
   u64 hk[B];
 #pragma unroll
   for (int i = 0; i < B; ++i) hk[i] = ((u64)P1[i].x << 32) | (u64)P2[i].x;
@@ -216,6 +218,7 @@ __device__ __forceinline__ void emit_parts(const MergeArgs &a, const bool (&act)
   visit_batch<B>(a, hk, act, slot, is_new, known);
 #pragma unroll
   for (int i = 0; i < B; ++i) {
+    claim[i] = is_new[i] ? slot[i] : kNoClaim;
     if (act[i]) {
       const u32 x = known[i] != kUnvisited ? known[i] | kIdFlag
                                            : slot[i] | (is_new[i] ? kNewFlag : 0u);
@@ -228,7 +231,8 @@ __device__ __forceinline__ void emit_parts(const MergeArgs &a, const bool (&act)
 template <int B>
 __device__ __forceinline__ void emit_batch(const MergeArgs &a, const bool (&act)[B],
                                            const u32 (&u)[B], const u64 (&key)[B],
-                                           const u64 (&tpos)[B], const float (&w)[B]) {
+                                           const u64 (&tpos)[B], const float (&w)[B],
+                                           u32 (&claim)[B]) {
   u32 q1[B], q2[B];
 #pragma unroll
   for (int i = 0; i < B; ++i) {
@@ -247,7 +251,52 @@ __device__ __forceinline__ void emit_batch(const MergeArgs &a, const bool (&act)
     P1[i] = act[i] ? a.parts1[pb1[i] + (u32)(key[i] >> a.b2)] : make_uint2(0, 0);
     P2[i] = act[i] ? a.parts2[pb2[i] + (u32)(key[i] & ((1ull << a.b2) - 1))] : make_uint2(0, 0);
   }
-  emit_parts<B>(a, act, u, P1, P2, tpos, w);
+  emit_parts<B>(a, act, u, P1, P2, tpos, w, claim);
+}
+
+// New pairs of a workgroup's merged arcs, collected in LDS and appended to the
+// level's new-pair list with one device atomic (same-address atomics
+// serialise at about 13 ns each).  The list's order is arbitrary: ids are
+// given in list order or by rank (launch_assign, launch_rank_assign).
+// Counting and listing the claims in two passes over the merged arcs, with a
+// scan between, took 180 us a level of 6M arcs and three launches a level.
+template <u32 CAP>
+struct ClaimLds {
+  u32 slot[CAP];
+  u32 n, base;
+};
+
+template <u32 CAP>
+__device__ __forceinline__ void claims_begin(ClaimLds<CAP> &L) {
+  if (threadIdx.x == 0) L.n = 0;
+  __syncthreads();
+}
+
+// Whole waves; the workgroup adds at most CAP claims in all.
+template <u32 CAP>
+__device__ __forceinline__ void claims_add(ClaimLds<CAP> &L, u32 claim) {
+  const u64 m = __ballot(claim != kNoClaim);
+  if (!m) return;
+  const u32 leader = (u32)__builtin_ctzll(m);
+  u32 at = 0;
+  if (lane_id() == leader) at = atomicAdd(&L.n, (u32)__popcll(m));
+  at = __shfl(at, (int)leader, kWave) + count_below(m);
+  if (claim != kNoClaim && at < CAP) L.slot[at] = claim;
+}
+
+template <u32 CAP>
+__device__ __forceinline__ void claims_end(const MergeArgs &a, ClaimLds<CAP> &L) {
+  __syncthreads();
+  const u32 n = L.n;
+  if (n == 0) return;  // uniform
+  if (threadIdx.x == 0) L.base = atomicAdd(&a.st->nnew, n);
+  __syncthreads();
+  const u64 base = L.base;
+  if (n > CAP || base + n > a.newcap) {  // impossible: the capacities bound both
+    if (threadIdx.x == 0) set_error(&a.st->err, kErrNewList);
+    return;
+  }
+  for (u32 i = threadIdx.x; i < n; i += blockDim.x) a.newlist[base + i] = L.slot[i];
 }
 
 // LDS of the sorting tile merge.
@@ -1950,6 +1999,8 @@ __global__ void k_run_heads(const u64 *keys, u64 n, u32 *flags) {
 // and emits the merged arc (visited-table insert included, see emit_batch).
 __global__ void k_big_reduce(MergeArgs a, const u64 *bigoff, u64 RB, const u64 *skey,
                              const u32 *sval, const u32 *flags, const u32 *ridx) {
+  __shared__ ClaimLds<256> L;
+  claims_begin(L);
   const u64 g = (u64)blockIdx.x * blockDim.x + threadIdx.x;
   bool act[1] = {g < RB && flags[g] != 0};
   u32 uu[1] = {0};
@@ -1974,18 +2025,29 @@ __global__ void k_big_reduce(MergeArgs a, const u64 *bigoff, u64 RB, const u64 *
     tpos[0] = base + local;
     wt[0] = (float)acc;
   }
-  emit_batch<1>(a, act, uu, key, tpos, wt);
+  u32 claim[1];
+  emit_batch<1>(a, act, uu, key, tpos, wt, claim);
+  claims_add(L, claim[0]);
+  claims_end(a, L);
 }
 
-// Wave k of the wpt waves sharing a tile: the tile's runs at temp[rb ...] in
-// chunks of 64 B (chunks k, k + wpt, ...), B per lane at a time (lane l takes
-// runs r0 + l + 64 i, i < B).  Wave-uniform trip count.
+// Merged arcs of the tile-merged sources, bpt workgroups per merge tile (the
+// tile kernels left tile_runs[t] runs at temp[t W + off, ...)): each run
+// record (source, part-rank key, weight) becomes (slot, a, c, weight) -- part
+// ranks mapped back to (r1, a) and (r2, c), the target pair inserted in the
+// visited table, kNewFlag set on claimed slots -- and the claimed slots join
+// the new-pair list.  Separate from the merge so that these dependent lookups
+// run at full occupancy.  Workgroup k of a tile takes its runs in chunks of
+// 256 B (chunks k, k + bpt, ...), B per lane at a time.
+constexpr int kEmitNT = 256;
+
 template <int B>
-__device__ __forceinline__ void emit_tile_runs(const MergeArgs &a, u64 rb, u32 nr, u32 lane, u32 k,
-                                               u32 wpt) {
-  for (u32 r0 = k * B * kWave; r0 < nr; r0 += wpt * B * kWave) {
+__device__ __forceinline__ void emit_tile_runs(const MergeArgs &a, u64 rb, u32 nr, u32 k, u32 bpt,
+                                               ClaimLds<kMergeCap> &L) {
+  const u32 lane = lane_id(), w = threadIdx.x / kWave;
+  for (u32 r0 = (k * kEmitNT + w * kWave) * B; r0 < nr; r0 += bpt * kEmitNT * B) {  // wave-uniform
     bool act[B];
-    u32 uu[B];
+    u32 uu[B], claim[B];
     u64 key[B], tpos[B];
     float wt[B];
 #pragma unroll
@@ -2005,115 +2067,170 @@ __device__ __forceinline__ void emit_tile_runs(const MergeArgs &a, u64 rb, u32 n
         wt[i] = __uint_as_float(rec.w);
       }
     }
-    emit_batch<B>(a, act, uu, key, tpos, wt);
+    emit_batch<B>(a, act, uu, key, tpos, wt, claim);
+#pragma unroll
+    for (int i = 0; i < B; ++i) claims_add(L, claim[i]);
   }
 }
 
-// Merged arcs of the tile-merged sources, wpt waves per merge tile (the tile
-// kernels left tile_runs[t] runs at temp[t W + off, ...)): each run record
-// (source, part-rank key, weight) becomes (slot, a, c, weight) -- part ranks
-// mapped back to (r1, a) and (r2, c), the target pair inserted in the
-// visited table, kNewFlag set on claimed slots.  Separate from the merge so
-// that these dependent lookups run at full occupancy.
-__global__ __launch_bounds__(256) void k_emit_tiles(MergeArgs a, u32 wpt) {
-  const u32 lane = lane_id();
-  const u64 gw = (u64)blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
-  const u64 tile = gw / wpt;
-  const u32 k = (u32)(gw % wpt);
-  if (tile >= a.ntiles) return;
+__global__ __launch_bounds__(kEmitNT) void k_emit_tiles(MergeArgs a, u32 bpt) {
+  __shared__ ClaimLds<kMergeCap> L;
+  const u64 tile = blockIdx.x / bpt;
+  const u32 k = blockIdx.x % bpt;
   const u32 nr = a.tile_runs[tile];
-  if (k * kWave >= nr) return;
+  if (k * kEmitNT >= nr || nr > (u32)kMergeCap) return;  // uniform
+  claims_begin(L);
   const u64 rb = tile * a.window + a.tiles[tile].z;
-  if (nr <= wpt * kWave) {
-    emit_tile_runs<1>(a, rb, nr, lane, k, wpt);
-  } else {
-    emit_tile_runs<kEmitBatch>(a, rb, nr, lane, k, wpt);  // several lookups in flight per lane
+  if (nr <= bpt * kEmitNT)
+    emit_tile_runs<1>(a, rb, nr, k, bpt, L);
+  else
+    emit_tile_runs<kEmitBatch>(a, rb, nr, k, bpt, L);  // several lookups in flight per lane
+  claims_end(a, L);
+}
+
+// Claimed slots of the product-merge sources' temp entries (empty slots carry
+// no flag) to the new-pair list.
+__global__ __launch_bounds__(256) void k_newlist_product(MergeArgs a) {
+  constexpr u32 kPer = 16;
+  __shared__ ClaimLds<256 * kPer> L;
+  claims_begin(L);
+  const u64 p0 = (u64)blockIdx.x * 256 * kPer + threadIdx.x;
+  u32 x[kPer];
+#pragma unroll
+  for (u32 j = 0; j < kPer; ++j) x[j] = a.temp[a.R + min(p0 + j * 256, a.prodpos - 1)].x;
+#pragma unroll
+  for (u32 j = 0; j < kPer; ++j) {
+    const bool f = p0 + j * 256 < a.prodpos && (x[j] & kNewFlag) != 0;
+    claims_add(L, f ? x[j] & ~kNewFlag : kNoClaim);
+  }
+  claims_end(a, L);
+}
+
+// ---------------------------------------------------------------------------
+// Ids in (q1, q2) order.
+// Up to kRankMax new pairs: new pair i of the list gets id base + (number of
+// new pairs below it).  A workgroup ranks 64 pairs, one per lane; its eight
+// waves compare them with an eighth of the list each, staged in LDS (every
+// lane of a wave reads one address: a broadcast).  In the dense visited array
+// the slot is the pair's order, in the hash table its key.  Quadratic, but one
+// launch: a radix sort takes three launches per 8 bits of the pair, 12 to 15
+// launches (about 60 us) for any list up to a few thousand pairs.
+// The list's length is read from *count on the device; above `cap` nothing is
+// done (the host then takes another form).
+constexpr u32 kRankNT = 512, kRankTile = 2048;
+
+template <class KT>
+__global__ __launch_bounds__(kRankNT) void k_rank_assign(const u32 *list, const u32 *count, u32 cap,
+                                                         u32 base, const u64 *hkeys, u32 *vis,
+                                                         u32 vn2, u32 *sq1, u32 *sq2) {
+  constexpr u32 kWaves = kRankNT / kWave, kShare = kRankTile / kWaves;
+  __shared__ __align__(16) KT s_key[kRankTile];
+  __shared__ u32 s_cnt[kWaves][kWave];
+  const u32 n = *count;
+  if (n > cap || blockIdx.x * kWave >= n) return;  // uniform
+  const u32 lane = lane_id(), w = threadIdx.x / kWave;
+  auto key_of = [&](u32 slot) -> KT {
+    if constexpr (sizeof(KT) == 4) return slot;
+    else return hkeys[slot];
+  };
+  const u32 i = blockIdx.x * kWave + lane;
+  const u32 slot = i < n ? list[i] : 0u;
+  const KT key = i < n ? key_of(slot) : KT(0);
+  u32 c = 0;
+  for (u32 t0 = 0; t0 < n; t0 += kRankTile) {
+    __syncthreads();
+    for (u32 j = threadIdx.x; j < kRankTile; j += kRankNT)
+      s_key[j] = t0 + j < n ? key_of(list[t0 + j]) : (KT)~(KT)0;  // above every key
+    __syncthreads();
+    const u32 lim = min(n - t0, kRankTile);
+    if (w * kShare < lim) {
+      const KT *k = s_key + w * kShare;
+#pragma unroll 8
+      for (u32 j = 0; j < kShare; ++j) c += k[j] < key ? 1u : 0u;
+    }
+  }
+  s_cnt[w][lane] = c;
+  __syncthreads();
+  if (w == 0 && i < n) {
+    u32 r = 0;
+#pragma unroll
+    for (u32 v = 0; v < kWaves; ++v) r += s_cnt[v][lane];
+    const u32 id = base + r;
+    vis[slot] = id;
+    if constexpr (sizeof(KT) == 4) {
+      sq1[id] = slot / vn2;
+      sq2[id] = slot % vn2;
+    } else {
+      sq1[id] = (u32)(key >> 32);
+      sq2[id] = (u32)key;
+    }
   }
 }
 
-// New-state list without a shared counter: wave w either walks the runs of
-// merge tile w (w < ntiles), or 64 positions of the multi-block record space
-// (runs of multi-block source i sit at temp[roff[big[i]] + p - bigoff[i]]
-// while below mend), or 64 product-merge slots temp[R + p] (empty slots
-// carry no flag).  Pass 0 counts the flagged (claimed) slots per wave into
-// wcnt; pass 1 writes them to newlist at woff[w] (exclusive scan of wcnt) in
-// wave order.
-template <int PASS>
-__global__ __launch_bounds__(256) void k_newlist(MergeArgs a, const u64 *bigoff, u32 nbig, u64 RB,
-                                                 u64 nbigw, u32 *wcnt, const u64 *woff) {
+// Any number of new pairs in the dense visited array, whose order is the
+// pairs': pass 1 reads the array and writes a bitmap of the entries a level
+// claimed (kClaimed, which no entry holds between levels) with their count
+// per wave, pass 2 numbers the set bits after the counts before them.  Wave v
+// takes entries [v E, v E + E), E a multiple of kClaimStep.  Bound by reading
+// the array once (4 B a pair: 5 us for 10^6 pairs, 90 us for 10^8).
+// skip_if: nothing to do when that word is nonzero.
+constexpr u32 kClaimStep = 16 * kWave;
+
+__global__ __launch_bounds__(256) void k_claim_count(const u32 *vis, u64 n, u64 E, u64 *bits,
+                                                     u32 *counts, const u64 *skip_if) {
+  if (skip_if && *skip_if) return;
   const u32 lane = lane_id();
   const u64 wv = ((u64)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
-  if (wv >= a.ntiles + nbigw + (a.prodpos + kWave - 1) / kWave) return;
-  const u64 base = PASS ? woff[wv] : 0;
-  u32 cnt = 0;
-  auto take = [&](bool f, u32 slot) {
-    const u64 m = __ballot(f);
-    if (PASS && f) {
-      const u64 pos = base + cnt + count_below(m);
-      if (pos < a.newcap) a.newlist[pos] = slot;
-      else set_error(&a.st->err, kErrNewList);
+  const u64 b = wv * E, e = min(n, b + E);
+  u32 c = 0;
+  for (u64 i0 = b; i0 < e; i0 += kClaimStep) {
+    u32 x[16];
+#pragma unroll
+    for (u32 j = 0; j < 16; ++j) x[j] = vis[min(i0 + j * kWave + lane, n - 1)];
+    u64 mine = 0;
+#pragma unroll
+    for (u32 j = 0; j < 16; ++j) {
+      const u64 m = __ballot(i0 + j * kWave + lane < n && x[j] == kClaimed);
+      c += (u32)__popcll(m);
+      mine = lane == j ? m : mine;
     }
-    cnt += (u32)__popcll(m);
-  };
-  if (wv < a.ntiles) {
-    const u32 nr = a.tile_runs[wv];
-    if (nr == 0) {
-      if (!PASS && lane == 0) wcnt[wv] = 0;
-      return;
-    }
-    const u64 rb = wv * a.window + a.tiles[wv].z;
-    for (u32 r0 = 0; r0 < nr; r0 += kWave) {
-      u32 x = 0;
-      if (r0 + lane < nr) x = a.temp[rb + r0 + lane].x;
-      take((x & kNewFlag) != 0, x & ~kNewFlag);
-    }
-  } else if (wv >= a.ntiles + nbigw) {
-    const u64 p = (wv - a.ntiles - nbigw) * kWave + lane;
-    const u32 x = p < a.prodpos ? a.temp[a.R + p].x : 0u;
-    take((x & kNewFlag) != 0, x & ~kNewFlag);
-  } else {
-    const u64 p = (wv - a.ntiles) * kWave + lane;
-    u32 x = 0;
-    if (p < RB) {
-      const u32 i = (u32)last_le<u64>(bigoff, nbig, p);
-      const u32 u = a.big[i];
-      const u64 t = a.roff[u] + (p - bigoff[i]);
-      if (t < a.mend[u]) x = a.temp[t].x;
-    }
-    take((x & kNewFlag) != 0, x & ~kNewFlag);
+    if (lane < 16) bits[i0 / kWave + lane] = mine;
   }
-  if (!PASS && lane == 0) wcnt[wv] = cnt;
+  if (lane == 0) counts[wv] = c;  // also of the waves past the array's end
 }
 
-// New-pair list of a level whose sources all took the product merge: 16
-// lanes per source (a source has at most 64 entries); a source with claims
-// writes the slots of its claimed entries, in temp order, from list entry
-// newoff[u].
-__global__ __launch_bounds__(256) void k_newlist_sources(MergeArgs a, const u64 *newoff) {
-  const u64 t = (u64)blockIdx.x * blockDim.x + threadIdx.x;
-  const u64 u = t / 16;
-  const u32 j = (u32)(t % 16), lane = lane_id();
-  const u32 nc = u < a.nsrc ? a.newc[u] : 0u;
-  if (__ballot(nc != 0) == 0) return;  // whole wave
-  u64 base = 0, n = 0, o = 0;
-  if (nc) {
-    base = a.tstart[u];
-    n = a.mend[u] - base;
-    o = newoff[u];
-  }
-  const u64 gmask = 0xffffull << (lane & ~15u);  // this lane's group of 16
-  u32 done = 0;
-  for (u32 r0 = 0; r0 < (u32)kWave; r0 += 16) {
-    const u64 r = r0 + j;
-    const u32 x = (nc && r < n) ? a.temp[base + r].x : 0u;
-    const bool f = (x & kNewFlag) != 0;
-    const u64 m = __ballot(f) & gmask;
-    if (f) {
-      const u64 pos = o + done + count_below(m);
-      if (pos < a.newcap) a.newlist[pos] = x & ~kNewFlag;
-      else set_error(&a.st->err, kErrNewList);
+__global__ __launch_bounds__(256) void k_claim_assign(u32 *vis, u64 n, u64 E, const u64 *bits,
+                                                      const u32 *counts, const u64 *skip_if,
+                                                      u32 base, u32 vn2, u32 *sq1, u32 *sq2) {
+  constexpr u32 kWaves = 256 / kWave;
+  __shared__ u32 s_tmp[kWaves];
+  if (skip_if && *skip_if) return;
+  const u32 lane = lane_id(), w = threadIdx.x / kWave;
+  const u32 first = blockIdx.x * kWaves;
+  u32 before = 0;
+  for (u32 j = threadIdx.x; j < first; j += 256) before += counts[j];
+  before = block_sum<256, u32>(before, s_tmp);
+  const u64 wv = first + w;
+  u32 id = base + before;
+  for (u32 k = 0; k < w; ++k) id += counts[first + k];
+  if (counts[wv] == 0) return;
+  const u64 b = wv * E, e = min(n, b + E);
+  for (u64 i0 = b; i0 < e; i0 += kClaimStep) {
+    const u64 word = lane < 16 ? bits[i0 / kWave + lane] : 0ull;
+#pragma unroll
+    for (u32 j = 0; j < 16; ++j) {
+      const u32 lo = (u32)__builtin_amdgcn_readlane((int)(u32)word, j);
+      const u32 hi = (u32)__builtin_amdgcn_readlane((int)(u32)(word >> 32), j);
+      const u64 m = ((u64)hi << 32) | lo;
+      if (!m) continue;  // uniform
+      if ((m >> lane) & 1u) {
+        const u32 slot = (u32)(i0 + j * kWave + lane), v = id + count_below(m);
+        vis[slot] = v;
+        sq1[v] = slot / vn2;
+        sq2[v] = slot % vn2;
+      }
+      id += (u32)__popcll(m);
     }
-    done += (u32)__popcll(m);
   }
 }
 
@@ -2226,26 +2343,24 @@ __global__ __launch_bounds__(256) void k_close_holes(MergeArgs a, const u64 *aof
     for (int c = 0; c < 5; ++c) cols[c][a.out_base + to + r] = tmp[(u64)c * n + from + r];
 }
 
-// Level total of new states (end of the exclusive scan of the per-wave counts).
-__global__ void k_new_total(const u64 *total, Status *st) { st->nnew = (u32)min<u64>(*total, 0xffffffffull); }
-
 // ---------------------------------------------------------------------------
 // Composition without reduction (every joined arc pair is an arc).  Wave per
 // kUnredB * 64 consecutive records, lane-striped: a record's source by a
 // binary search within the sources of the wave's first and last record; its
 // part ranks back to (r1, a) and (r2, c); the target pair claimed in the
-// visited table (new claims set a bit of newbits, so the new-state list
-// needs no shared counter); the arc written with the table slot as target.
+// visited table, the claims appended to the new-pair list; the arc written
+// with the table slot as target.
 constexpr int kUnredB = 4;
 
 template <class KT>
-__global__ __launch_bounds__(256) void k_unreduced(MergeArgs a, u32 *newbits, u32 *osrc,
-                                                   u32 *odst, u32 *oil, u32 *ool, float *ow) {
+__global__ __launch_bounds__(256) void k_unreduced(MergeArgs a, u32 *osrc, u32 *odst, u32 *oil,
+                                                   u32 *ool, float *ow) {
+  __shared__ ClaimLds<256 * kUnredB> L;
+  claims_begin(L);
   const u32 lane = lane_id();
   const u64 wv = ((u64)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
-  const u64 wb = wv * (u64)(kWave * kUnredB);
-  if (wb >= a.R) return;
-  const u64 we = min(wb + (u64)(kWave * kUnredB), a.R);
+  const u64 wb = min(wv * (u64)(kWave * kUnredB), a.R - 1);
+  const u64 we = min(wv * (u64)(kWave * kUnredB) + (u64)(kWave * kUnredB), a.R);
   u32 ul = 0;
   if (lane < 2) ul = (u32)last_le<u64>(a.roff, a.nsrc, lane == 0 ? wb : we - 1);
   const u32 u0 = __shfl(ul, 0, kWave), u1 = __shfl(ul, 1, kWave);
@@ -2259,7 +2374,7 @@ __global__ __launch_bounds__(256) void k_unreduced(MergeArgs a, u32 *newbits, u3
   u32 known[kUnredB];  // unused: the result holds slots until the ids are known
 #pragma unroll
   for (int i = 0; i < kUnredB; ++i) {
-    r[i] = wb + (u64)i * kWave + lane;
+    r[i] = wv * (u64)(kWave * kUnredB) + (u64)i * kWave + lane;
     act[i] = r[i] < we;
     const u64 rr = act[i] ? r[i] : wb;
     uu[i] = u0 + (u32)last_le<u64>(a.roff + u0, (u64)(u1 - u0) + 1, rr);
@@ -2273,40 +2388,15 @@ __global__ __launch_bounds__(256) void k_unreduced(MergeArgs a, u32 *newbits, u3
   visit_batch<kUnredB>(a, hk, act, slot, is_new, known);
 #pragma unroll
   for (int i = 0; i < kUnredB; ++i) {
+    claims_add(L, is_new[i] ? slot[i] : kNoClaim);
     if (!act[i]) continue;
-    if (is_new[i]) atomicOr(&newbits[slot[i] >> 5], 1u << (slot[i] & 31));
     osrc[r[i]] = a.lo + uu[i];
     odst[r[i]] = slot[i];
     oil[r[i]] = P1[i].y;
     ool[r[i]] = P2[i].y;
     ow[r[i]] = wt[i];
   }
-}
-
-// Set bits of a bitmap as a list of bit indices in increasing order: wave w
-// takes words [64 w, 64 w + 64); pass 0 counts, pass 1 writes at woff[w].
-template <int PASS>
-__global__ __launch_bounds__(256) void k_bitlist(const u32 *bits, u64 nwords, u32 *wcnt,
-                                                 const u64 *woff, u32 *list, u64 cap, Status *st) {
-  const u32 lane = lane_id();
-  const u64 wv = ((u64)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
-  const u64 i = wv * kWave + lane;
-  if (wv * kWave >= nwords) return;
-  u32 word = i < nwords ? bits[i] : 0u;
-  const u32 c = __popc(word);
-  const u32 incl = wave_inclusive_sum(c);
-  if (!PASS) {
-    if (lane == kWave - 1) wcnt[wv] = incl;
-    return;
-  }
-  u64 pos = woff[wv] + incl - c;
-  while (word) {
-    const u32 b = __ffs(word) - 1;
-    word &= word - 1;
-    if (pos < cap) list[pos] = (u32)(i * 32 + b);
-    else set_error(&st->err, kErrNewList);
-    ++pos;
-  }
+  claims_end(a, L);
 }
 
 __global__ void k_fix_dst(u32 *dst, u64 n, const u32 *hvals) {
@@ -2344,9 +2434,9 @@ __global__ void k_states_to_dense(const u32 *sq1, const u32 *sq2, u64 n, u32 *vi
 
 // New pair i of the list gets id base + i: i < nnew, or i < min(*count,
 // nnew) when count is given (nnew is then the list's capacity).
-__global__ void k_assign(const u32 *slots, u32 nnew, const u64 *count, u32 base,
+__global__ void k_assign(const u32 *slots, u32 nnew, const u32 *count, u32 base,
                          const u64 *hkeys, u32 *hvals, u32 vn2, u32 *sq1, u32 *sq2) {
-  const u64 n = count ? min<u64>(*count, nnew) : nnew;
+  const u32 n = count ? min(*count, nnew) : nnew;
   for (u64 i = (u64)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (u64)gridDim.x * blockDim.x) {
     const u32 slot = slots[i];
     const u32 id = base + (u32)i;
@@ -2569,7 +2659,7 @@ __device__ __forceinline__ void clear_level(Status *st) {
 
 
 // Level totals after the merge: merged arcs (end of the scan of merged arcs
-// per source), new pairs (end of the scan of the new-pair lists), the
+// per source), new pairs (*nt, or the length of the new-pair list), the
 // product merge's joined pairs (sum of the per-source joined pairs less the
 // level's records), and, over the merge tiles, the records and runs of the
 // tiles the dense-table kernel merged and the runs of those the sort kernel
@@ -2611,7 +2701,12 @@ __global__ __launch_bounds__(1024) void k_merged_total(const u64 *at, const u64 
     *dst = t;
   }
   if (threadIdx.x == 3) st->merged = *at;
-  if (threadIdx.x == 4 && nt) st->nnew = (u32)min<u64>(*nt, 0xffffffffull);
+  if (threadIdx.x == 4) {
+    // (without nt: the length the new-pair list reached)
+    const u32 n = nt ? (u32)min<u64>(*nt, 0xffffffffull) : st->nnew;
+    st->nnew = n;
+    st->new_count = n;
+  }
   if (threadIdx.x == 5) st->prod_records = *pt - st->R;
   __syncthreads();
   __threadfence();
@@ -2627,11 +2722,13 @@ __global__ __launch_bounds__(1024) void k_merged_total(const u64 *at, const u64 
 //   2. entry offsets (a workgroup scan of the table sizes);
 //   3. each wave merges quads of sources (the four-source kernel's code);
 //   4. new pairs and joined pairs per source scanned and summed;
-//   5. ids of the claimed targets, four lanes per source;
+//   5. ids of the claimed targets, four lanes per source, or (ordered) after
+//      a sort of the claimed slots in LDS;
 //   6. the other marked targets of the level's entries;
 //   7. the level totals, their publication, the counters cleared.
 constexpr int kTinyNT = 1024;
-static_assert(kTinySources <= (u32)kTinyNT, "a thread per source");
+static_assert(kTinySources * kProdRow * kProdRow <= (u32)kTinyNT, "a thread per source and per entry");
+static_assert(kTinyNT <= kSmallNT && (u32)kTinyNT <= kSmallRecords, "small_sort takes the level's claims");
 
 // End of a stage: every thread's stores are done (the barrier's release),
 // then each thread drops its CU's L1 lines (an agent-scope acquire), so its
@@ -2644,8 +2741,11 @@ __device__ __forceinline__ void stage_barrier() {
 
 __global__ __launch_bounds__(kTinyNT) void k_product_level(LevelArgs la, MergeArgs ma, u64 *poff,
                                                            u64 *newoff, u32 base, u32 *sq1,
-                                                           u32 *sq2, Status *host, u32 seq) {
+                                                           u32 *sq2, u32 ordered, Status *host,
+                                                           u32 seq) {
   __shared__ u64 s_scr[kTinyNT / kWave];
+  __shared__ u64 s_key[kTinyNT];  // ordered ids: claimed slots
+  __shared__ u32 s_val[kTinyNT];
   const u32 t = threadIdx.x;
   const u32 nsrc = la.nsrc;
   Status *st = ma.st;
@@ -2699,7 +2799,31 @@ __global__ __launch_bounds__(kTinyNT) void k_product_level(LevelArgs la, MergeAr
   stage_barrier();
   // 5. ids of the claimed targets (whole waves: the lanes past the level
   // have no new pairs)
-  for (u32 t0 = 0; t0 < 4 * nsrc; t0 += kTinyNT) assign_direct_lanes(ma, newoff, base, sq1, sq2, t0 + t);
+  if (!ordered) {
+    for (u32 t0 = 0; t0 < 4 * nsrc; t0 += kTinyNT) assign_direct_lanes(ma, newoff, base, sq1, sq2, t0 + t);
+  } else {
+    // in slot order, which is the pairs' (their targets keep the slot mark
+    // until the composition's last pass, like those other sources claimed)
+    const u32 x = t < entries ? ma.out_dst[ma.out_base + t] : 0u;
+    const bool f = (x & kDstClaim) != 0;
+    u64 tot;
+    const u64 pos = block_exclusive_sum<kTinyNT, u64>(f ? 1u : 0u, s_scr, &tot);
+    if (f) {
+      s_key[pos] = x & kDstSlotMask;
+      s_val[pos] = 0;
+    }
+    u32 n = 1;
+    while (n < tot) n <<= 1;
+    for (u32 i = (u32)tot + t; i < n; i += kTinyNT) s_key[i] = ~0ull;
+    __syncthreads();
+    small_sort(s_key, s_val, n);
+    for (u32 i = t; i < tot; i += kTinyNT) {
+      const u32 slot = (u32)s_key[i], v = base + i;
+      ma.vis[slot] = v;
+      sq1[v] = slot / ma.vn2;
+      sq2[v] = slot % ma.vn2;
+    }
+  }
   stage_barrier();
   // 6. totals, publication, counters cleared (the targets another source
   // claimed keep their slot marks: the composition's last pass replaces them)
@@ -2796,30 +2920,16 @@ void merge_big(const MergeArgs &a, bool wide_keys, u32 nbig, const u64 *bigoff, 
                      sval.as<u32>(), flags.as<u32>(), ridx.as<u32>());
 }
 
-void launch_unreduced(const MergeArgs &a, bool wide_keys, u32 *newbits, u32 *osrc, u32 *odst,
-                      u32 *oil, u32 *ool, float *ow, hipStream_t s) {
+void launch_unreduced(const MergeArgs &a, bool wide_keys, u32 *osrc, u32 *odst, u32 *oil, u32 *ool,
+                      float *ow, hipStream_t s) {
   if (a.R == 0) return;
   const u64 nw = ceil_div(a.R, (u64)kWave * kUnredB);
   const unsigned g = (unsigned)ceil_div(nw, 256 / kWave);
   if (ceil_div(nw, 256 / kWave) >= (1ull << 31)) throw Error(FSTC_ERR_CAPACITY, "level too large for one launch");
   if (wide_keys)
-    hipLaunchKernelGGL(k_unreduced<u64>, dim3(g), dim3(256), 0, s, a, newbits, osrc, odst, oil, ool, ow);
+    hipLaunchKernelGGL(k_unreduced<u64>, dim3(g), dim3(256), 0, s, a, osrc, odst, oil, ool, ow);
   else
-    hipLaunchKernelGGL(k_unreduced<u32>, dim3(g), dim3(256), 0, s, a, newbits, osrc, odst, oil, ool, ow);
-}
-
-u64 bitlist_waves(u64 nwords) { return ceil_div(std::max<u64>(nwords, 1), kWave); }
-
-void launch_bitlist(const u32 *bits, u64 nwords, u32 *list, u64 cap, u32 *wcnt, u64 *woff,
-                    void *scan_tmp, Status *st, hipStream_t s) {
-  const u64 nw = bitlist_waves(nwords);
-  const unsigned g = (unsigned)ceil_div(nw, 256 / kWave);
-  hipLaunchKernelGGL(k_bitlist<0>, dim3(g), dim3(256), 0, s, bits, nwords, wcnt, (const u64 *)nullptr,
-                     list, cap, st);
-  exclusive_scan(wcnt, woff, nw, scan_tmp, s);
-  hipLaunchKernelGGL(k_bitlist<1>, dim3(g), dim3(256), 0, s, bits, nwords, wcnt, (const u64 *)woff,
-                     list, cap, st);
-  hipLaunchKernelGGL(k_new_total, dim3(1), dim3(1), 0, s, (const u64 *)(woff + nw), st);
+    hipLaunchKernelGGL(k_unreduced<u32>, dim3(g), dim3(256), 0, s, a, osrc, odst, oil, ool, ow);
 }
 
 void launch_prod_sources(const MergeArgs &a, bool narrow, hipStream_t s, bool lean) {
@@ -2839,10 +2949,43 @@ void launch_prod_sources(const MergeArgs &a, bool narrow, hipStream_t s, bool le
     hipLaunchKernelGGL(k_prod_sources<false>, dim3(g), dim3(kProdNT), 0, s, a);
 }
 
-void launch_newlist_sources(const MergeArgs &a, const u64 *newoff, hipStream_t s) {
-  if (!a.nsrc) return;
-  hipLaunchKernelGGL(k_newlist_sources, dim3((unsigned)ceil_div((u64)a.nsrc * 16, 256)), dim3(256),
-                     0, s, a, newoff);
+void launch_newlist_product(const MergeArgs &a, hipStream_t s) {
+  if (!a.prodpos) return;
+  hipLaunchKernelGGL(k_newlist_product, dim3((unsigned)ceil_div(a.prodpos, 4096)), dim3(256), 0, s, a);
+}
+
+void launch_rank_assign(const u32 *list, const u32 *count, u32 cap, u32 base, const u64 *hkeys,
+                        u32 *hvals, u32 vn2, u32 *sq1, u32 *sq2, hipStream_t s) {
+  if (!cap) return;
+  const dim3 g((unsigned)ceil_div(cap, kWave));
+  if (vn2)
+    hipLaunchKernelGGL(k_rank_assign<u32>, g, dim3(kRankNT), 0, s, list, count, cap, base, hkeys,
+                       hvals, vn2, sq1, sq2);
+  else
+    hipLaunchKernelGGL(k_rank_assign<u64>, g, dim3(kRankNT), 0, s, list, count, cap, base, hkeys,
+                       hvals, vn2, sq1, sq2);
+}
+
+// Entries per wave of the claim passes: at most 8,192 waves (pass 2 adds up
+// the counts of the waves before its own).
+static u64 claim_share(u64 n) {
+  return ceil_div(std::max<u64>(ceil_div(n, 8192), 1), kClaimStep) * kClaimStep;
+}
+
+size_t claim_temp_bytes(u64 n) {
+  const u64 waves = ceil_div(ceil_div(n, claim_share(n)), 4) * 4;
+  return waves * 4 + 256 + (ceil_div(n, kClaimStep) * 16 + 16) * 8;
+}
+
+void launch_claim_ids(u32 *vis, u64 n, u32 vn2, u32 base, u32 *sq1, u32 *sq2, void *temp,
+                      const u64 *skip_if, hipStream_t s) {
+  const u64 E = claim_share(n);
+  const unsigned g = (unsigned)ceil_div(ceil_div(n, E), 4);
+  u32 *counts = static_cast<u32 *>(temp);
+  u64 *bits = reinterpret_cast<u64 *>(static_cast<char *>(temp) + ((g * 16ull + 255) & ~255ull));
+  hipLaunchKernelGGL(k_claim_count, dim3(g), dim3(256), 0, s, vis, n, E, bits, counts, skip_if);
+  hipLaunchKernelGGL(k_claim_assign, dim3(g), dim3(256), 0, s, vis, n, E, bits, counts, skip_if,
+                     base, vn2, sq1, sq2);
 }
 
 void launch_assign_direct(const MergeArgs &a, const u64 *newoff, u32 base, u32 *sq1, u32 *sq2,
@@ -2908,10 +3051,10 @@ void launch_assign(const u32 *slots, u32 nnew, u32 base, const u64 *hkeys, u32 *
                    u32 *sq1, u32 *sq2, hipStream_t s) {
   if (!nnew) return;
   hipLaunchKernelGGL(k_assign, dim3((unsigned)ceil_div(nnew, 256)), dim3(256), 0, s, slots, nnew,
-                     (const u64 *)nullptr, base, hkeys, hvals, vn2, sq1, sq2);
+                     (const u32 *)nullptr, base, hkeys, hvals, vn2, sq1, sq2);
 }
 
-void launch_assign_counted(const u32 *slots, const u64 *count, u32 cap, u32 base,
+void launch_assign_counted(const u32 *slots, const u32 *count, u32 cap, u32 base,
                            const u64 *hkeys, u32 *hvals, u32 vn2, u32 *sq1, u32 *sq2,
                            hipStream_t s) {
   if (!count || !cap) return;
@@ -2949,33 +3092,14 @@ void launch_compact(const MergeArgs &a, const u64 *aoff, const u64 *bigoff, u32 
                        hvals, osrc, odst, oil, ool, ow);
 }
 
-u64 newlist_waves(const MergeArgs &a, u64 RB) {
-  return a.ntiles + ceil_div(RB, kWave) + ceil_div(a.prodpos, (u64)kWave);
-}
-
-const u64 *launch_newlist(const MergeArgs &a, const u64 *bigoff, u32 nbig, u64 RB, u32 *wcnt,
-                          u64 *woff, void *scan_state, hipStream_t s) {
-  const u64 nbigw = ceil_div(RB, kWave);
-  const u64 nw = newlist_waves(a, RB);
-  if (nw == 0) return nullptr;  // no new pairs
-  const unsigned g = (unsigned)ceil_div(nw, 256 / kWave);
-  hipLaunchKernelGGL(k_newlist<0>, dim3(g), dim3(256), 0, s, a, bigoff, nbig, RB, nbigw, wcnt,
-                     (const u64 *)nullptr);
-  const ScanJob job{wcnt, false, woff};
-  exclusive_scan_lb(&job, 1, nw, scan_state, &a.st->scan_ctr, &a.st->err, s);
-  hipLaunchKernelGGL(k_newlist<1>, dim3(g), dim3(256), 0, s, a, bigoff, nbig, RB, nbigw, wcnt,
-                     (const u64 *)woff);
-  return woff + nw;
-}
-
 void launch_emit_tiles(const MergeArgs &a, hipStream_t s) {
   if (a.R == 0) return;
-  // waves per tile: enough waves in all to fill the chip even when a level
+  // workgroups per tile: enough in all to fill the chip even when a level
   // has few tiles (each tile holds at most kMergeCap runs)
-  const u64 target = (u64)compute_units() * 128;
-  const u32 wpt = (u32)std::min<u64>(kMergeCap / kWave, std::max<u64>(1, ceil_div(target, a.ntiles)));
-  hipLaunchKernelGGL(k_emit_tiles, dim3((unsigned)ceil_div(a.ntiles * wpt, 256 / kWave)), dim3(256),
-                     0, s, a, wpt);
+  const u64 target = (u64)compute_units() * 32;
+  const u32 bpt = (u32)std::min<u64>(kMergeCap / kEmitNT, std::max<u64>(1, ceil_div(target, a.ntiles)));
+  if (a.ntiles * bpt >= (1ull << 31)) throw Error(FSTC_ERR_CAPACITY, "level too large for one launch");
+  hipLaunchKernelGGL(k_emit_tiles, dim3((unsigned)(a.ntiles * bpt)), dim3(kEmitNT), 0, s, a, bpt);
 }
 
 void launch_finals(const u32 *sq1, const u32 *sq2, u64 n, const uint8_t *f1, const uint8_t *f2,
@@ -2998,11 +3122,12 @@ void launch_reset_level(Status *st, hipStream_t s) {
 }
 
 void launch_product_level(const LevelArgs &la, const MergeArgs &ma, u64 *poff, u64 *newoff,
-                          u32 base, u32 *sq1, u32 *sq2, Status *host, u32 seq, hipStream_t s) {
+                          u32 base, u32 *sq1, u32 *sq2, bool ordered, Status *host, u32 seq,
+                          hipStream_t s) {
   if (la.nsrc == 0 || la.nsrc > kTinySources || !ma.vn2 || !ma.out_dst || ma.poff != poff)
     throw Error(FSTC_ERR_INTERNAL, "one-workgroup product level out of its range");
   hipLaunchKernelGGL(k_product_level, dim3(1), dim3(kTinyNT), 0, s, la, ma, poff, newoff, base, sq1,
-                     sq2, host, seq);
+                     sq2, ordered ? 1u : 0u, host, seq);
 }
 
 u64 level_clear_mask() {

@@ -511,8 +511,7 @@ void Composer::run(fstc_result *out) {
   // without reduction, levels whose sources are all strided four-source
   // product sources resolve each source's targets once and write its joined
   // pairs from the two weight matrices (no records, no per-record probe)
-  const bool unred_prod = o.no_reduction && !o.no_product_merge && !o.deterministic_ids &&
-                          !o.max_arcs;
+  const bool unred_prod = o.no_reduction && !o.no_product_merge && !o.max_arcs;
   T.at(kCsr);
   {
     // the two layouts are independent: when both take the per-state build
@@ -1390,7 +1389,11 @@ void Composer::run(fstc_result *out) {
       sq2b.grow_keep((n_states + newcap_u) * 4, n_states * 4);
       pa.out_dst = utab.as<u32>();
       pa.out_base = 0;
-      launch_assign_direct(pa, newoff.as<u64>(), (u32)n_states, sq1b.as<u32>(), sq2b.as<u32>(), s);
+      if (o.deterministic_ids)
+        launch_claim_ids(hvb.as<u32>(), pairspace, vn2, (u32)n_states, sq1b.as<u32>(),
+                         sq2b.as<u32>(), claim_tmp(), nullptr, s);
+      else
+        launch_assign_direct(pa, newoff.as<u64>(), (u32)n_states, sq1b.as<u32>(), sq2b.as<u32>(), s);
       launch_fix_marked(pa, prodpos, s);
       const u32 seq2 = next_publication();
       launch_merged_total(ptot.as<u64>() + nsrc, newoff.as<u64>() + nsrc, ptot.as<u64>() + nsrc,

@@ -284,8 +284,8 @@ void launch_small_levels(const SmallArgs &a, hipStream_t s);
 // Composition without reduction, a level whose sources all took the
 // four-source form and whose targets utab holds as ids: source u's joined
 // pairs as arcs at out_base + off[u] .. (off: exclusive scan of the joined
-// pairs per source), entry (p1, p2) times symbol g at
-// (p1 P2 + p2) na + g, weight the float32 product of the two arc weights.
+// pairs per source) in record order, symbol g and entry (p1, p2) at
+// g P1 P2 + p1 P2 + p2, weight the float32 product of the two arc weights.
 void launch_unreduced_product(const MergeArgs &a, const u64 *off, hipStream_t s);
 
 // Tile descriptors of the level (a.tiles), then the two tile merges: the

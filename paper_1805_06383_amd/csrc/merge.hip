@@ -1451,53 +1451,67 @@ __global__ __launch_bounds__(256) void k_prod_quad(MergeArgs a) {
 }
 
 // Composition without reduction, a level of strided product sources whose
-// targets are resolved (utab holds ids): one wave per source, lane g for
-// symbol g, writes the na joined pairs of each entry (p1, p2) -- the float32
-// product of the M1 arc of part p1 and the M2 arc of part p2 at symbol g
-// -- with the entry's target and labels.
+// targets are resolved (utab holds ids): one wave per source writes its na K
+// joined pairs (K = P1 P2) in record order -- symbol g, then part p1, then
+// part p2: pair i is entry e = i mod K of symbol i / K -- with the float32
+// product of the M1 arc of part p1 and the M2 arc of part p2 at symbol g.
+// Consecutive lanes write consecutive arcs, so every store of the wave covers
+// whole lines (a lane per symbol, the entries one after the other, covered
+// them too but in another order than the records'); kUnredU steps of 64 pairs
+// have their loads in flight before the first store.  Bound by the 20 bytes
+// an arc that it writes.
+constexpr int kUnredU = 4;
 __global__ __launch_bounds__(256) void k_unreduced_product(MergeArgs a, const u64 *off) {
   const u32 lane = lane_id();
   const u64 u = ((u64)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
   if (u >= a.nsrc) return;
-  const u32 K = a.pk[u];
+  const u32 K = uni(a.pk[u]);
   if (!K) return;
   const uint4 h0 = a.phdr[2 * u], h1 = a.phdr[2 * u + 1];
-  const u32 P1 = h0.z & 0xffffu, P2 = h0.z >> 16, na = h0.w >> 8;
-  if (!(h0.w & 4u) || P1 * P2 != K || P1 > 4 || P2 > 4 || na > (u32)kWave) {
+  const u32 P1 = uni(h0.z & 0xffffu), P2 = uni(h0.z >> 16), na = uni(h0.w >> 8);
+  if (!(h0.w & 4u) || P1 * P2 != K || P1 > kProdRow || P2 > kProdRow || na > (u32)kWave) {
     if (lane == 0) set_error(&a.st->err, kErrBounds);  // impossible: the selection checked it
     return;
   }
   const u64 base = a.out_base + off[u];
-  const u32 *tab = a.utab + a.poff[u];
-  const u32 src = a.lo + (u32)u;
-  const bool g_ok = lane < na;
-  float w1[4], w2[4];
-#pragma unroll
-  for (u32 p = 0; p < 4; ++p) {
-    w1[p] = (g_ok && p < P1) ? __uint_as_float(a.wts1[h1.y + P1 * lane + p]) : 0.f;
-    w2[p] = (g_ok && p < P2) ? __uint_as_float(a.wts2[h1.w + P2 * lane + p]) : 0.f;
+  const u32 src = a.lo + (u32)u, n = na * K;
+  // lane e < K: entry e's target and labels, handed to the lanes by shuffles
+  const u32 ec = min(lane, K - 1);
+  const u32 t0 = a.utab[a.poff[u] + ec];
+  const u32 il0 = a.parts1[h0.x + ec / P2].y, ol0 = a.parts2[h0.y + ec % P2].y;
+  if (__ballot((t0 & kDstSlot) != 0)) {  // impossible: every target was numbered before this kernel
+    if (lane == 0) set_error(&a.st->err, kErrBounds);
+    return;
   }
+  u32 g = lane / K, e = lane % K;  // pair i = lane, lane + 64, ...
+  const u32 dg = (u32)kWave / K, de = (u32)kWave % K;
+  for (u32 i0 = 0; i0 < n; i0 += kUnredU * kWave) {
+    u32 w1[kUnredU], w2[kUnredU], ee[kUnredU];
 #pragma unroll
-  for (u32 p1 = 0; p1 < 4; ++p1) {
-    if (p1 >= P1) break;
-    const u32 il = a.parts1[h0.x + p1].y;
-#pragma unroll
-    for (u32 p2 = 0; p2 < 4; ++p2) {
-      if (p2 >= P2) break;
-      const u32 e = p1 * P2 + p2;
-      const u32 t = tab[e];
-      if (t & kDstSlot) {  // impossible: every target was numbered before this kernel
-        if (lane == 0) set_error(&a.st->err, kErrBounds);
-        return;
+    for (int j = 0; j < kUnredU; ++j) {
+      const u32 gc = min(g, na - 1), p1 = e / P2;
+      ee[j] = e;
+      w1[j] = a.wts1[h1.y + P1 * gc + p1];
+      w2[j] = a.wts2[h1.w + P2 * gc + (e - p1 * P2)];
+      g += dg;
+      e += de;
+      if (e >= K) {
+        e -= K;
+        ++g;
       }
-      const u32 ol = a.parts2[h0.y + p2].y;
-      if (g_ok) {
-        const u64 k = base + (u64)e * na + lane;
+    }
+#pragma unroll
+    for (int j = 0; j < kUnredU; ++j) {
+      const u32 i = i0 + j * kWave + lane;
+      const u32 t = __shfl(t0, (int)ee[j], kWave), il = __shfl(il0, (int)ee[j], kWave),
+                ol = __shfl(ol0, (int)ee[j], kWave);
+      if (i < n) {
+        const u64 k = base + i;
         a.out_src[k] = src;
         a.out_dst[k] = t;
         a.out_il[k] = il;
         a.out_ol[k] = ol;
-        a.out_w[k] = w1[p1] * w2[p2];
+        a.out_w[k] = __uint_as_float(w1[j]) * __uint_as_float(w2[j]);
       }
     }
   }

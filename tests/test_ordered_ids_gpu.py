@@ -93,3 +93,19 @@ def test_direct_product_levels(nq, m, slots):
     x, y = a.to_host(), b.to_host()
     for f in ("q1", "q2", "final", "src", "dst", "a", "c"):
         assert np.array_equal(getattr(x, f), getattr(y, f)), f
+
+
+@pytest.mark.parametrize("slots", [1, 2, 3, 4])
+@pytest.mark.parametrize("nq,m", [(7, 8), (20, 33), (40, 64)])
+def test_unreduced_product_order(nq, m, slots):
+    """Without reduction, strided sources write their joined pairs from the
+    two weight matrices in the order of the written records: the same arrays,
+    bit for bit, as with every source on records."""
+    m1, m2 = W.config4(nq * slots, nq=nq, m=m, slots=slots)
+    a = compose(m1, m2, reduce=False)
+    b = compose(m1, m2, reduce=False, product=False)
+    assert a.stats["total_product_records"] > 0  # not all: a state may hold a slot twice
+    assert b.stats["total_product_records"] == 0
+    x, y = a.to_host(), b.to_host()
+    for f in ("q1", "q2", "final", "src", "dst", "a", "c", "w"):
+        assert np.array_equal(getattr(x, f), getattr(y, f)), f

@@ -498,9 +498,12 @@ void Composer::run(fstc_result *out) {
 
   static_assert(sizeof(Status) <= 256, "Status and the CSR counts share one allocation");
   Buf stb(&A);
-  dst = (Status *)stb.ensure(256 + 16 * sizeof(u64));
+  constexpr size_t kStatusBytes = 256 + 16 * sizeof(u64) + kHeavySplit * 4;  // zeroed
+  dst = (Status *)stb.ensure(kStatusBytes + kHeavySplit * kHeavyChunks * sizeof(HeavyChunk));
   u64 *dcounts = reinterpret_cast<u64 *>(reinterpret_cast<char *>(dst) + 256);
-  fill_u32((u32 *)dst, 0, sizeof(Status) / 4, s);
+  u32 *hdone = reinterpret_cast<u32 *>(dcounts + 16);
+  HeavyChunk *hchunk = reinterpret_cast<HeavyChunk *>(reinterpret_cast<char *>(dst) + kStatusBytes);
+  fill_u32((u32 *)dst, 0, kStatusBytes / 4, s);
 
   // (a0) device layout of both inputs
   Buf cb1(&A), cb2(&A);
@@ -794,6 +797,8 @@ void Composer::run(fstc_result *out) {
     la.quad = quad ? 1u : 0u;
     la.glist = glist.as<u32>();
     la.grp = grp.as<u32>();
+    la.hdone = hdone;
+    la.hchunk = hchunk;
     // A small level after a direct product level: one workgroup takes it
     // whole when all its sources are strided product sources (level.hpp,
     // launch_product_level), else it declines and the level takes the

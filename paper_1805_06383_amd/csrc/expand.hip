@@ -323,30 +323,79 @@ __device__ __forceinline__ void count_wide_sources(const LevelArgs &a, u32 blk, 
   }
 }
 
+// The heavy joins: the shorter list of heavy source i < kHeavySplit cut into
+// chunks (heavy_chunk, at most kHeavyChunks of them, whole steps of the
+// workgroup), a workgroup per chunk.  Each chunk's matches and joined pairs go
+// to a.hchunk[i kHeavyChunks + chunk]; the workgroup that finishes last adds
+// them up, and the emission starts every chunk at the sum before it.  One
+// workgroup for a whole source took 440 us to emit (and 70 us to count) a
+// list of 50,000 symbols, each step a chain of 17 dependent loads.  Sources
+// past kHeavySplit, of which there is one per workgroup anyway, are joined
+// whole.
+__device__ __forceinline__ u32 heavy_chunk(u32 n) {
+  const u32 per = (n + kHeavyChunks - 1) / kHeavyChunks;
+  return (per + kListNT - 1) / kListNT * kListNT;
+}
+
 __device__ __forceinline__ void count_heavy_sources(const LevelArgs &a, u32 blk, u32 nblk,
                                                     u32 &run_max, u64 *s64, u32 *s32) {
-  const u32 n = a.st->nheavy;
-  for (u32 i = blk; i < n; i += nblk) {
+  __shared__ u32 s_last;
+  const u32 n = a.st->nheavy, ns = min(n, kHeavySplit);
+  const u64 work = (u64)ns * kHeavyChunks + (n - ns);
+  for (u64 w = blk; w < work; w += nblk) {
+    const bool split = w < (u64)ns * kHeavyChunks;
+    // chunk-major: the first chunks of every source first
+    const u32 i = split ? (u32)(w % ns) : (u32)(ns + (w - (u64)ns * kHeavyChunks));
+    const u32 c = split ? (u32)(w / ns) : 0u;
     const u32 u = a.heavy[i];
     const Ranges r = source_ranges(a, u);
     const bool one_short = (r.e1 - r.b1) <= (r.e2 - r.b2);
     const u32 bs = one_short ? r.b1 : r.b2, es = one_short ? r.e1 : r.e2;
+    const u32 per = split ? heavy_chunk(es - bs) : es - bs;
+    const u32 nchunk = (es - bs + per - 1) / per;
+    if (c >= nchunk) continue;  // uniform
+    const u32 cb = bs + c * per, ce = min(es, cb + per);
     u64 cnt = 0;
     u32 mc = 0;
-    for (u32 base = bs; base < es; base += kListNT) {
+    for (u32 base = cb; base < ce; base += kListNT) {
       const Hit h = probe_one(a, r, one_short, base + threadIdx.x);
-      if (h.found) {
+      if (h.found && base + threadIdx.x < ce) {
         cnt += (u64)seg_len(a.c1.seg_off, h.s1) * seg_len(a.c2.seg_off, h.s2);
         ++mc;
       }
     }
     cnt = block_sum<kListNT, u64>(cnt, s64);
     mc = block_sum<kListNT, u32>(mc, s32);
+    if (split) {
+      HeavyChunk *hc = a.hchunk + (u64)i * kHeavyChunks;
+      if (threadIdx.x == 0) {
+        __hip_atomic_store(&hc[c].cnt, cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&hc[c].mc, (u64)mc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        // a release and acquire at the counter: the last one sees every chunk
+        s_last = __hip_atomic_fetch_add(&a.hdone[i], 1u, __ATOMIC_ACQ_REL,
+                                        __HIP_MEMORY_SCOPE_AGENT) == nchunk - 1;
+      }
+      __syncthreads();
+      if (!s_last) {
+        __syncthreads();  // s_last read by everyone before the next chunk
+        continue;
+      }
+      u64 pc = 0;
+      u32 pm = 0;
+      if (threadIdx.x < nchunk) {
+        pc = __hip_atomic_load(&hc[threadIdx.x].cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        pm = (u32)__hip_atomic_load(&hc[threadIdx.x].mc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      cnt = block_sum<kListNT, u64>(pc, s64);
+      mc = block_sum<kListNT, u32>(pm, s32);
+      if (threadIdx.x == 0) a.hdone[i] = 0;  // for the next level
+    }
     if (threadIdx.x == 0) {
       a.cnt[u] = cnt;
       a.mc[u] = mc;
       note_count(a, u, cnt, run_max);
     }
+    __syncthreads();
   }
 }
 
@@ -556,16 +605,30 @@ __global__ __launch_bounds__(256) void k_emit_wide(LevelArgs a) {
 __global__ __launch_bounds__(kHeavyNT) void k_emit_heavy(LevelArgs a) {
   __shared__ u64 s64[kHeavyNT / kWave];
   __shared__ u32 s32[kHeavyNT / kWave];
-  const u32 n = a.st->nheavy;
-  for (u32 i = blockIdx.x; i < n; i += gridDim.x) {
+  const u32 n = a.st->nheavy, ns = min(n, kHeavySplit);
+  const u64 work = (u64)ns * kHeavyChunks + (n - ns);
+  for (u64 w = blockIdx.x; w < work; w += gridDim.x) {
+    const bool split = w < (u64)ns * kHeavyChunks;
+    const u32 i = split ? (u32)(w % ns) : (u32)(ns + (w - (u64)ns * kHeavyChunks));
+    const u32 c = split ? (u32)(w / ns) : 0u;
     const u32 u = a.heavy[i];
     if (a.pk[u]) continue;  // product merge
     const Ranges r = source_ranges(a, u);
     const bool one_short = (r.e1 - r.b1) <= (r.e2 - r.b2);
     const u32 bs = one_short ? r.b1 : r.b2, es = one_short ? r.e1 : r.e2;
+    const u32 per = split ? heavy_chunk(es - bs) : es - bs;
+    const u32 cb = bs + c * per;
+    if (cb >= es) continue;  // uniform
+    const u32 ce = min(es, cb + per);
     u64 k = a.moff[u], rb = a.roff[u];
-    for (u32 base = bs; base < es; base += kHeavyNT) {
-      const Hit h = probe_one(a, r, one_short, base + threadIdx.x);
+    if (c) {  // the chunks before this one
+      const HeavyChunk *hc = a.hchunk + (u64)i * kHeavyChunks;
+      rb += block_sum<kHeavyNT, u64>(threadIdx.x < c ? hc[threadIdx.x].cnt : 0, s64);
+      k += block_sum<kHeavyNT, u32>(threadIdx.x < c ? (u32)hc[threadIdx.x].mc : 0u, s32);
+    }
+    for (u32 base = cb; base < ce; base += kHeavyNT) {
+      Hit h = probe_one(a, r, one_short, base + threadIdx.x);
+      h.found = h.found && base + threadIdx.x < ce;
       const u64 prod = h.found ? (u64)seg_len(a.c1.seg_off, h.s1) * seg_len(a.c2.seg_off, h.s2) : 0;
       u32 ftot;
       u64 ptot;
@@ -575,6 +638,7 @@ __global__ __launch_bounds__(kHeavyNT) void k_emit_heavy(LevelArgs a) {
       k += ftot;
       rb += ptot;
     }
+    __syncthreads();
   }
 }
 
@@ -785,7 +849,9 @@ __global__ __launch_bounds__(kExpandNT) void k_expand(const uint4 *match, const 
 // listed source, whose number is bounded by the frontier before the count
 // and known exactly after it.
 static unsigned wide_grid(u64 n) { return (unsigned)std::min<u64>(2048, ceil_div(n, 256 / kWave)); }
-static unsigned heavy_grid(u64 n) { return (unsigned)std::min<u64>(512, n); }
+static unsigned heavy_grid(u64 n) {
+  return (unsigned)std::min<u64>(512, std::min<u64>(n, kHeavySplit) * kHeavyChunks);
+}
 
 // Workgroups of each list kernel when the lists are expected empty.
 constexpr unsigned kLeanGrid = 64;
@@ -795,13 +861,13 @@ void launch_count(const LevelArgs &a, hipStream_t s, bool lean) {
   hipLaunchKernelGGL(k_count_small, dim3(g), dim3(kCountNT), 0, s, a);
   // 16-lane joins: at most one group per source, at most as many waves as
   // the chip holds (they loop over the list); wide: at most one wave per
-  // source (1024 blocks of 8 waves at most); heavy: one block per source
-  // (512 blocks at most)
+  // source (1024 blocks of 8 waves at most); heavy: one block per chunk of
+  // a source (512 blocks at most; kLeanGrid when there are few sources)
   const u64 n = a.nsrc;
   unsigned gg = (unsigned)std::min<u64>((u64)compute_units() * 4,
                                         ceil_div(n, kListNT / kGroupLanes));
   unsigned gw = (unsigned)std::min<u64>(1024, ceil_div(n, kListNT / kWave));
-  unsigned gh = (unsigned)std::min<u64>(512, n);
+  unsigned gh = (unsigned)std::min<u64>(512, std::max<u64>(n, kLeanGrid));
   if (lean) {
     gg = std::min(gg, kLeanGrid);
     gw = std::min(gw, kLeanGrid);

@@ -78,6 +78,13 @@ constexpr u32 kGroupLanes = 16;
 constexpr u32 kGroupMax = 32;
 constexpr u32 kGroupLong = 512;
 constexpr u32 kHeavyMin = 2048;
+// The first kHeavySplit heavy sources of a level are joined by up to
+// kHeavyChunks workgroups each (expand.hip, heavy_chunk).
+constexpr u32 kHeavySplit = 256;
+constexpr u32 kHeavyChunks = 64;
+struct HeavyChunk {
+  u64 cnt, mc;  // joined pairs and matched symbols of one chunk
+};
 
 // Merge tiles: 512 threads x 8 items = 4096 records of LDS capacity.  Sources
 // of more than kMergeSmall records take the multi-block path.  A tile takes
@@ -145,6 +152,8 @@ struct LevelArgs {
                          // kernel (dense visited array), the others to glist
   u32 *glist;            // [nsrc] product sources for the one-per-wave kernel (st->ngen)
   u32 *grp;              // [nsrc] sources for the 16-lane joins (st->ngrp)
+  HeavyChunk *hchunk;    // [kHeavySplit kHeavyChunks] chunk counts of the heavy joins
+  u32 *hdone;            // [kHeavySplit] finished chunks, all 0 between levels
   u32 unred;             // composition without reduction: only strided sources with
                          // the four-source kernel take the product form
 };

@@ -110,7 +110,10 @@ __global__ void k_copy_count(const u32 *src, u64 *dst) { *dst = *src; }
 
 // Wave per state; lane l checks segments row[q] + l, + 64, ...: a segment
 // of more arcs than kProdParts, or whose arcs' parts are not all distinct
-// (a 64-bit mask of the parts), flags the state (bit 0).  For the other
+// (a 64-bit mask of the parts), flags the state (bit 0), as do more than
+// kCellMaxSegs segments: one wave's walk over a trie root's 50,000 took
+// 570 us, and the product merge would search such a list for its at most 64
+// symbols in 64-symbol chunks, one after the other.  For the other
 // states the word also summarises the arcs' weights (kCellSpecial: a
 // non-finite or subnormal weight; the largest biased float32 exponent of a
 // nonzero weight at kCellEmaxShift, the smallest at kCellEminShift) and
@@ -136,7 +139,8 @@ __device__ __forceinline__ void cell_flags_body(const u32 *row, const u32 *seg_s
   const u32 lane = lane_id();
   const u64 nw = (u64)(nblk - gw) * blockDim.x / kWave;
   for (u64 q = ((u64)(blk - gw) * blockDim.x + threadIdx.x) / kWave; q < nq; q += nw) {
-    bool bad = part_base[q + 1] - part_base[q] > kProdParts, special = false, shuffled = false;
+    bool bad = part_base[q + 1] - part_base[q] > kProdParts || row[q + 1] - row[q] > kCellMaxSegs;
+    bool special = false, shuffled = false;
     bool gap = false;  // a symbol other than the first plus its segment index
     u32 emax = 0, emin = 255;
     if (!bad) {
@@ -941,9 +945,14 @@ namespace {
 constexpr u32 kLocMaxStates = 1u << 17;
 constexpr u64 kLocMaxAvg = 1024;
 constexpr u64 kLocAnyArcs = 1u << 16;
+// Average state up to which a small input still takes it: one tile of the
+// large class's workgroup.  (One state of 60,000 arcs, eight tiles a sort
+// pass in one workgroup, took 800 us; the global sorts take 180.)
+constexpr u64 kLocOneTile = 8192;
 
 bool use_local_build(u64 n, u32 nq) {
-  return nq <= kLocMaxStates && (n <= kLocMaxAvg * nq || n <= kLocAnyArcs);
+  return nq <= kLocMaxStates &&
+         (n <= kLocMaxAvg * nq || (n <= kLocAnyArcs && n <= kLocOneTile * nq));
 }
 
 size_t arena_bytes(std::initializer_list<size_t> sizes) {

@@ -150,9 +150,12 @@ bool build_csr_pair(const fstc_fst &m1, bool by_output1, Arena &T1, const Csr &c
 // Largest part count of a state the product merge takes (level.hpp).
 constexpr u32 kProdParts = 64;
 
-// cell_flag[q] has bit kCellBad when state q has more than kProdParts parts
-// or two arcs with the same part and inner symbol (parallel arcs with equal
-// labels and target).  Otherwise it summarises the state's arc weights: bit
+// Longest symbol list of a state the product merge takes.
+constexpr u32 kCellMaxSegs = 2048;
+
+// cell_flag[q] has bit kCellBad when state q has more than kProdParts parts,
+// more than kCellMaxSegs segments, or two arcs with the same part and inner
+// symbol (parallel arcs with equal labels and target).  Otherwise it summarises the state's arc weights: bit
 // kCellSpecial when one is infinite, NaN or subnormal, and the largest and
 // smallest biased float32 exponents of its nonzero weights (0 and 255 in
 // those fields when it has none), and bit kCellDense when every one of its

@@ -163,3 +163,38 @@ def test_csr_grouped_by_state(fstc, nq):
     check(fstc, m, f"grouped, {nq} states")
     m.src[0], m.src[-1] = m.src[-1], m.src[0]
     check(fstc, m, f"grouped, {nq} states, one arc out of place")
+
+
+@pytest.mark.parametrize("nq,n", [(1, 8192), (1, 8193), (2, 16_384), (2, 16_385), (7, 57_345),
+                                  (1, 65_536), (1, 65_537)])
+def test_csr_few_large_states(fstc, nq, n):
+    """Around the line between the per-state build and the global sorts for
+    few states of up to 8,192 arcs on average."""
+    rng = np.random.default_rng(n)
+    m = W.FST(num_states=nq, start=0, num_isyms=900, num_osyms=1200,
+              src=rng.integers(0, nq, n), dst=rng.integers(0, nq, n),
+              ilabel=rng.integers(0, 900, n), olabel=rng.integers(0, 1200, n),
+              weight=W.random_weights(rng, n), final=np.ones(nq, np.uint8))
+    check(fstc, m, f"{nq} states, {n} arcs")
+
+
+@pytest.mark.parametrize("syms", [2047, 2048, 2049])
+def test_long_lists_against_short(fstc, syms):
+    """States of few parts whose symbol list is at the longest one the product
+    merge takes, composed with states of eight and of 2,000 symbols."""
+    import oracle
+    from fstcheck import assert_same, canon_of
+    rng = np.random.default_rng(syms)
+    src = np.repeat(np.arange(3), syms)
+    m1 = W.FST(num_states=3, start=0, num_isyms=4, num_osyms=syms, src=src, dst=(src + 1) % 3,
+               ilabel=src % 4, olabel=np.tile(np.arange(syms), 3),
+               weight=W.random_weights(rng, 3 * syms), final=np.ones(3, np.uint8))
+    k = [8, 2000, 64]
+    s2 = np.repeat(np.arange(3), k)
+    b2 = np.concatenate([np.sort(rng.choice(syms, x, replace=False)) for x in k])
+    m2 = W.FST(num_states=3, start=0, num_isyms=syms, num_osyms=4, src=s2, dst=(s2 + 1) % 3,
+               ilabel=b2, olabel=s2 % 4, weight=W.random_weights(rng, len(s2)),
+               final=np.ones(3, np.uint8))
+    g = fstc.compose(m1, m2, small_levels=False)
+    assert_same(canon_of(g.to_host()), canon_of(oracle.compose(m1, m2)), rtol=1e-5, what=f"{syms}")
+    assert (g.stats["total_product_sources"] > 0) == (syms <= 2048)

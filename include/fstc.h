@@ -118,8 +118,10 @@ typedef struct fstc_opts {
                                  each, is merged by one wavefront from its
                                  two arc matrices (sum over matched symbols
                                  of float32 products, added in float64),
-                                 without records.  Same states and arcs;
-                                 weights agree to float64 rounding        */
+                                 without records, and sources of few arc
+                                 pairs are joined and merged on the chip.
+                                 Same states and arcs; weights agree to
+                                 float64 rounding                          */
   uint32_t hash_visited;      /* nonzero: the visited set is always the hash
                                  table of pair keys.  0: it is a dense array
                                  indexed by q1 |Q2| + q2 (the paper's
@@ -206,8 +208,9 @@ typedef struct fstc_stats {
   uint64_t total_dense_records; /* records merged through the dense table   */
   uint64_t total_dense_runs;  /* merged arcs the dense table produced        */
   uint64_t total_sort_runs;   /* merged arcs the sorting tiles produced      */
-  uint64_t total_product_records; /* joined arc pairs merged by the product
-                                     merge (never written as records)         */
+  uint64_t total_product_records; /* joined arc pairs merged without being
+                                     written as records (product merge, and
+                                     sources merged on the chip whole)        */
   uint64_t total_product_sources; /* sources merged by the product merge      */
   double ms_product_kernel;   /* product-merge kernel alone, all levels      */
   uint32_t product_launches;  /* launches of the product-merge kernel        */

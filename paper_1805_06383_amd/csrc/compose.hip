@@ -71,6 +71,14 @@ constexpr u64 kEarlyBytes = u64(1) << 30;
 // Largest pair space whose ordered ids are given before the host reads a
 // level's counts (a pass over the dense visited array).
 constexpr u64 kIdScanPairs = u64(1) << 22;
+// Pairs per source up to which a level finds its new pairs by a pass.
+constexpr u64 kScanPairsPerSource = 128;
+// Fewest sources of a level that the chunk merge is tried on: the one or few of
+// the first levels are the start's neighbours, often the largest states there
+// are, and the one-workgroup kernel takes small ones.
+constexpr u32 kChunkMinSources = 32;
+// Levels of the chunk merge with the most temp slots (136 MB at 17 B a slot).
+constexpr u64 kChunkFewSources = u64(1) << 17;
 // Largest temp (entries x 20 bytes) reserved for a speculative product merge.
 constexpr u64 kSpecBytes = u64(1) << 30;
 inline size_t grown(size_t cap_bytes) { return cap_bytes * (cap_bytes < kFastGrowBytes ? 4 : 2); }
@@ -287,19 +295,26 @@ struct Timer {
 
 // One wave publishes to the host's staging block (coherent pinned memory):
 // nwords words (the CSR counts, then, with `lists`, the inner-symbol list
-// lengths of the two start states as words 6 and 7), the status words but
+// lengths of the two start states as words 6 and 7 and their part counts as
+// words 9 and 10), the status words but
 // its sequence word, a system-scope fence, then the sequence word: the host
 // waits for it (wait_published) instead of a copy and a stream
 // synchronisation.
 __global__ __launch_bounds__(kWave) void k_publish_counts(const u32 *row1, u32 s1, const u32 *row2,
-                                                          u32 s2, int lists, const u64 *counts,
-                                                          u32 nwords, const Status *st,
-                                                          Status *host, u64 *host_words, u32 seq) {
+                                                          u32 s2, const u32 *part1,
+                                                          const u32 *part2, int lists,
+                                                          const u64 *counts, u32 nwords,
+                                                          const Status *st, Status *host,
+                                                          u64 *host_words, u32 seq) {
   const u32 lane = threadIdx.x;
   u64 l1 = 0, l2 = 0;
   if (lists) {  // uniform
     l1 = row1[s1 + 1] - row1[s1];
     l2 = row2[s2 + 1] - row2[s2];
+    if (lane == 0) {
+      host_words[9] = part1[s1 + 1] - part1[s1];
+      host_words[10] = part2[s2 + 1] - part2[s2];
+    }
   }
   if (lane < nwords) host_words[lane] = lists && lane == 6 ? l1 : lists && lane == 7 ? l2 : counts[lane];
   const u32 *src = reinterpret_cast<const u32 *>(st);
@@ -620,16 +635,18 @@ void Composer::run(fstc_result *out) {
   }
   {
     const u32 seq0 = next_publication();
-    static_assert(sizeof(Staging::words) >= 9 * sizeof(u64), "the CSR counts fit the staging words");
+    static_assert(sizeof(Staging::words) >= 11 * sizeof(u64), "the CSR counts fit the staging words");
     hipLaunchKernelGGL(k_publish_counts, dim3(1), dim3(kWave), 0, s, c1.row, m1.start, c2.row,
-                       m2.start, (m1.num_states && m2.num_states) ? 1 : 0, dcounts,
+                       m2.start, c1.part_base, c2.part_base, (m1.num_states && m2.num_states) ? 1 : 0, dcounts,
                        join_bound ? 9u : 8u, dst, hs_dev, hs_words_dev, seq0);
     wait_published(seq0);
     hb.release();
   }
   const u64 maxp1 = hs->words[2], maxp2 = hs->words[5];
   const u64 start_list1 = m1.num_states && m2.num_states ? hs->words[6] : 0,
-            start_list2 = m1.num_states && m2.num_states ? hs->words[7] : 0;
+            start_list2 = m1.num_states && m2.num_states ? hs->words[7] : 0,
+            start_parts1 = m1.num_states && m2.num_states ? hs->words[9] : 0,
+            start_parts2 = m1.num_states && m2.num_states ? hs->words[10] : 0;
   const int b1 = (int)bits_for(maxp1 ? maxp1 - 1 : 0);
   const int b2 = (int)bits_for(maxp2 ? maxp2 - 1 : 0);
   const int key_bits = b1 + b2;
@@ -649,7 +666,19 @@ void Composer::run(fstc_result *out) {
   u32 vis_moves = 0, direct_levels = 0;
   // the previous level was a direct product level (or none has run): the
   // next one is enqueued whole before the host reads its counts
-  bool last_direct = true;
+  // (a start pair that cannot take the product merge: it does not)
+  bool last_direct = start_parts1 + start_parts2 <= kProdRowSum &&
+                     std::min(start_list1, start_list2) >= kProdMinSymbols &&
+                     std::min(start_list1, start_list2) <= (u64)kWave;
+  // Levels whose sources are not expected to take the direct product form go
+  // through the chunk merge first (chunk.hip).  While such levels leave
+  // nothing to the general kernels (chunk_pure) the next one is enqueued
+  // whole and the host waits once.
+  const bool chunk_ok = product && !o.fused_merge && key_bits <= kChunkKeyBits;
+  bool chunk_pure = true;
+  // a level's sources had more arc pairs than the chunk merge takes: the next
+  // one's are not offered to it
+  bool chunk_heavy = false;
   // the previous per-level level had no listed sources: the list kernels
   // get lean grids (see launch_count, launch_prod_sources)
   bool lists_empty = false, listed_empty = false;
@@ -670,7 +699,72 @@ void Composer::run(fstc_result *out) {
       rkey(&level_tmp), rw(&level_tmp), temp(&level_tmp), newlist(&level_tmp), stmp(&level_tmp),
       dk(&level_tmp), dv(&level_tmp), dka(&level_tmp), dva(&level_tmp), dtmp(&level_tmp),
       tiles_e(&level_tmp), tiles_m(&level_tmp), tstart(&level_tmp), mend(&level_tmp),
-      sortlist(&level_tmp), tile_runs(&level_tmp), runsrc(&level_tmp);
+      sortlist(&level_tmp), tile_runs(&level_tmp), runsrc(&level_tmp), ctmp(&level_tmp),
+      csrc(&level_tmp), ccnt(&level_tmp), cpairs(&level_tmp);
+
+  // Visited table: keeps the load factor at most 1/2 for `states` states (at
+  // most kMaxHashCap slots: an insert into a full table reports it).
+  auto grow_visited = [&](u64 states) {
+    const u64 need = std::min<u64>(2 * states, kMaxHashCap);
+    if (dense_vis || need <= hcap) return;
+    if (!o.hash_visited && pairspace <= kDenseMaxPairs && next_pow2(need) * 12 >= pairspace * 4) {
+      // the grown table (8-byte keys, 4-byte ids) would be at least as large
+      // as the dense array over all pairs: move the visited set there (the
+      // level's inserts have not started; every state so far has its id)
+      Buf nv(&A);
+      nv.ensure(pairspace * 4);
+      fill_u32(nv.as<u32>(), kUnvisited, pairspace, s);
+      launch_states_to_dense(sq1b.as<u32>(), sq2b.as<u32>(), n_states, nv.as<u32>(),
+                             m2.num_states, s);
+      hkb.release();
+      std::swap(hvb.p, nv.p); std::swap(hvb.cap, nv.cap);
+      hcap = pairspace;
+      dense_vis = true;
+      vn2 = m2.num_states;
+      ++vis_moves;
+    } else {
+      const u64 ncap = next_pow2(need);
+      Buf nk(&A), nv(&A);
+      nk.ensure(ncap * 8);
+      nv.ensure(ncap * 4);
+      fill_u64(nk.as<u64>(), kEmptyKey, ncap, s);
+      launch_rehash(hkb.as<u64>(), hvb.as<u32>(), hcap, nk.as<u64>(), nv.as<u32>(), ncap - 1,
+                    &dst->err, s);
+      std::swap(hkb.p, nk.p); std::swap(hkb.cap, nk.cap);
+      std::swap(hvb.p, nv.p); std::swap(hvb.cap, nv.cap);
+      hcap = ncap;
+    }
+  };
+
+  // (a5) ids n_states, ... for the level's nnew listed pairs (count: the list's
+  // length on the device).  Ordered ids: ranked in one launch up to kRankMax
+  // new pairs; a larger level takes a pass over the dense visited array while
+  // that is cheaper than a radix sort (0.9 ps a pair of the array against
+  // about 60 us and 150 ps a new pair), or the sort.
+  auto assign_ids = [&](u32 nnew, u32 *slots, const u32 *count) {
+    if (!nnew) return;
+    u32 *q1 = sq1b.as<u32>(), *q2 = sq2b.as<u32>();
+    if (o.deterministic_ids && nnew > 1) {
+      if (nnew <= kRankMax) {
+        launch_rank_assign(slots, count, nnew, (u32)n_states, hkb.as<u64>(), hvb.as<u32>(), vn2, q1,
+                           q2, s);
+        return;
+      }
+      if (dense_vis && pairspace <= kDensePairs + 160ull * nnew) {
+        launch_claim_ids(hvb.as<u32>(), pairspace, vn2, (u32)n_states, q1, q2, claim_tmp(), nullptr, s);
+        return;
+      }
+      const int bq1 = (int)bits_for(m1.num_states - 1), bq2 = (int)bits_for(m2.num_states - 1);
+      dk.ensure((u64)nnew * 8); dv.ensure((u64)nnew * 4);
+      dka.ensure((u64)nnew * 8); dva.ensure((u64)nnew * 4);
+      dtmp.ensure(radix_temp_bytes(nnew));
+      launch_newkeys(slots, nnew, hkb.as<u64>(), vn2, bq2, dk.as<u64>(), dv.as<u32>(), s);
+      radix_sort_pairs(dk.as<u64>(), dv.as<u32>(), dka.as<u64>(), dva.as<u32>(), nnew, 0, bq1 + bq2,
+                       dtmp.p, s);
+      slots = dv.as<u32>();
+    }
+    launch_assign(slots, nnew, (u32)n_states, hkb.as<u64>(), hvb.as<u32>(), vn2, q1, q2, s);
+  };
 
   bool status_clear = true;  // level counters of *dst all zero
   // small levels (level.hpp, k_small_levels): one workgroup runs them, and
@@ -756,6 +850,7 @@ void Composer::run(fstc_result *out) {
       expanded_levels += out_st.levels;
       new_levels += out_st.new_levels;
       small_levels += out_st.levels;
+      if (out_st.levels) last_direct = false;
       max_frontier = std::max<u64>(max_frontier, out_st.max_frontier);
       max_level_pre = std::max<u64>(max_level_pre, out_st.max_level_pre);
       if (out_st.reason == kSmallDone) break;
@@ -873,9 +968,36 @@ void Composer::run(fstc_result *out) {
     // source; the product sources' flags summed; the scan's last tile stores
     // the level totals (R, M, product entries, product sources) and
     // publishes the counters as publication `seq`
+    // Chunk merge: a level's sources joined and merged on the chip, S to a
+    // wavefront.  What it leaves is counted by launch_count_lists.
+    const bool chunk = chunk_ok && !last_direct && !chunk_heavy && nsrc >= kChunkMinSources;
+    ChunkArgs ca{};
+    const u64 left_pairs = pairspace - n_states;  // pairs that are no states yet
+    u64 chunk_cap = 0;                            // most arcs the chunk merge produces
+    if (chunk) {
+      ca.S = chunk_sources(nsrc);
+      ca.nblk = (u32)ceil_div(nsrc, ca.S);
+      // slots per wavefront: all that its sources can need or the most while
+      // the level is small, else four times what the sources before had (a
+      // wavefront that needs more leaves its sources to the general kernels)
+      ca.cap = nsrc <= kChunkFewSources
+                   ? std::min(kChunkMaxCap, kChunkPer * ca.S)
+                   : (u32)std::min<u64>(kChunkMaxCap, std::max<u64>(kChunkMinCap,
+                                        next_pow2(4 * kChunkS * ceil_div(arcs, std::max<u64>(lo, 1)))));
+      chunk_cap = (u64)ca.nblk * ca.cap;
+      ctmp.ensure(chunk_cap * sizeof(uint4));
+      csrc.ensure(chunk_cap);
+      ccnt.ensure((u64)ca.nblk * 4);
+      cpairs.ensure(np1 * 4);
+      ca.tmp = ctmp.as<uint4>();
+      ca.src = csrc.as<uint8_t>();
+      ca.cnt = ccnt.as<u32>();
+      ca.pairs = cpairs.as<u32>();
+    }
     auto count_and_scan = [&](u32 seq) {
       T.at(kCount);
-      launch_count(la, s, lists_empty);
+      if (chunk) launch_count_lists(la, s, lists_empty);
+      else launch_count(la, s, lists_empty);
       ScanJob jobs[4] = {{cnt.p, true, roff.as<u64>()}, {mc.p, false, moff.as<u64>()},
                          {pk.p, false, poff.as<u64>()}, {pflag.p, true, ftot.as<u64>()}};
       jobs[3].total_only = true;
@@ -908,6 +1030,151 @@ void Composer::run(fstc_result *out) {
       pub = ScanPublish{dst, hs_dev, (u32)(sizeof(Status) / 4), (u32)(offsetof(Status, seq) / 4), seq};
       pub.clear_mask = level_clear_mask();
     };
+    // the visited set's arguments of the merge kernels
+    auto visit_args = [&](MergeArgs &m) {
+      m.nsrc = nsrc;
+      m.lo = lo;
+      m.st = dst;
+      m.parts1 = c1.parts;
+      m.parts2 = c2.parts;
+      m.hkeys = hkb.as<u64>();
+      m.hmask = hcap - 1;
+      m.vis = hvb.as<u32>();
+      m.vn2 = vn2;
+      m.tstart = tstart.as<u64>();
+      m.mend = mend.as<u64>();
+    };
+    // A level of many sources over a dense visited array of at most
+    // kScanPairsPerSource pairs a source finds its new pairs by a pass over the
+    // array (0.9 ps a pair) instead of listing claims made one by one.
+    const bool scan_new = chunk && dense_vis && pairspace <= kScanPairsPerSource * nsrc;
+    bool chunk_emitted = false;
+    u64 list_cap = 0;  // entries of newlist while the chunk merge's claims are in it
+    auto chunk_emit = [&](u64 cap) {
+      MergeArgs m{};
+      visit_args(m);
+      list_cap = std::max<u64>(std::min<u64>(cap, left_pairs), 1);
+      newlist.ensure(list_cap * 4);
+      m.newlist = newlist.as<u32>();
+      m.newcap = list_cap;
+      launch_chunk_emit(m, ca, scan_new, s);
+      // (all of the level's new pairs so far: the list stays empty)
+      if (scan_new) launch_claim_count(hvb.as<u32>(), pairspace, claim_tmp(), &dst->nnew, nullptr, s);
+      chunk_emitted = true;
+    };
+    // merged arcs per source scanned into result offsets, the other columns
+    // summed: published as `seq`, the counters left for the level's next steps
+    auto chunk_scan = [&](u32 seq) {
+      ScanJob jobs[4] = {{mend.p, true, aoff.as<u64>()}, {cnt.p, true, roff.as<u64>()},
+                         {pflag.p, true, ftot.as<u64>()}, {cpairs.p, false, ptot.as<u64>()}};
+      jobs[0].sub = tstart.as<u64>();
+      jobs[0].total_to = &dst->merged;
+      jobs[1].total_only = jobs[2].total_only = jobs[3].total_only = true;
+      jobs[1].total_to = &dst->R;
+      jobs[2].total_to = reinterpret_cast<u64 *>(&dst->nprod);
+      jobs[3].total_to = &dst->chunk_pairs;
+      const ScanPublish pub{dst, hs_dev, (u32)(sizeof(Status) / 4), (u32)(offsetof(Status, seq) / 4),
+                            seq};
+      exclusive_scan_lb(jobs, 4, nsrc, lb(nsrc), &dst->scan_ctr, &dst->err, s, &pub);
+    };
+    auto chunk_append = [&](u64 room, const u64 *skip_if, bool clear) {
+      out_arcs.grow(arcs + room, arcs);
+      MergeArgs m{};
+      visit_args(m);
+      launch_chunk_compact(m, ca, aoff.as<u64>(), room, hvb.as<u32>(), out_arcs.col(0) + arcs,
+                           out_arcs.col(1) + arcs, out_arcs.col(2) + arcs, out_arcs.col(3) + arcs,
+                           reinterpret_cast<float *>(out_arcs.col(4)) + arcs, skip_if, clear, s);
+    };
+    if (chunk) {
+      T.at(kCount);
+      launch_chunk_join(la, ca, b2, key_bits, s);
+      // the claims before the host knows their number, when the visited set
+      // has room for the most there can be
+      const bool room = dense_vis || 2 * (n_states + std::min<u64>(chunk_cap, left_pairs)) <= hcap;
+      T.at(kMerge);
+      if (room) chunk_emit(chunk_cap);
+      T.at(kNone);
+      if (chunk_pure || !room) {
+        const u32 seqc = next_publication();
+        T.at(kMerge);
+        chunk_scan(seqc);
+        // ids and append before the host's wait, as on other levels (they
+        // stand down when the level has other sources)
+        const u64 newcap_c = std::min<u64>(chunk_cap, left_pairs);
+        const bool ahead_c = chunk_emitted && ids_by_scan && !o.max_arcs &&
+                             (n_states + newcap_c) * 8 <= kEarlyBytes &&
+                             (arcs + chunk_cap) * 20 <= kEarlyBytes;
+        auto ids = [&](u64 cap) {
+          sq1b.grow_keep((n_states + cap) * 4, n_states * 4);
+          sq2b.grow_keep((n_states + cap) * 4, n_states * 4);
+        };
+        if (ahead_c) {
+          T.at(kAssign);
+          ids(newcap_c);
+          if (scan_new)
+            launch_claim_assign(hvb.as<u32>(), pairspace, vn2, (u32)n_states, sq1b.as<u32>(),
+                                sq2b.as<u32>(), claim_tmp(), &dst->general, s);
+          else if (o.deterministic_ids)
+            launch_claim_ids(hvb.as<u32>(), pairspace, vn2, (u32)n_states, sq1b.as<u32>(),
+                             sq2b.as<u32>(), claim_tmp(), &dst->general, s);
+          else
+            launch_assign_counted(newlist.as<u32>(), &dst->nnew, (u32)newcap_c, (u32)n_states,
+                                  hkb.as<u64>(), hvb.as<u32>(), vn2, sq1b.as<u32>(),
+                                  sq2b.as<u32>(), s, &dst->general);
+          chunk_append(chunk_cap, &dst->general, true);
+        }
+        T.at(kNone);
+        wait_published(seqc);
+        const bool pure = hs->st.general == 0;
+        chunk_pure = pure;
+        const u64 merged_c = hs->st.merged;  // of the chunk merge when not pure
+        if (pure) {
+          lists_empty = listed_empty = true;
+          if (small_shape_off && (u64)hs->st.unfit * 8 < nsrc) small_shape_off = false;
+          const u64 pairs = hs->st.chunk_pairs;
+          if (merged_c == 0) break;  // no arc leaves this level
+          u64 nnew_c = hs->st.nnew;
+          if (!chunk_emitted) {
+            grow_visited(n_states + std::min<u64>(merged_c, left_pairs));
+            T.at(kMerge);
+            chunk_emit(merged_c);
+            const u32 seqe = next_publication();
+            hipLaunchKernelGGL(k_publish_counts, dim3(1), dim3(kWave), 0, s, nullptr, 0u, nullptr, 0u,
+                               nullptr, nullptr, 0, nullptr, 0u, dst, hs_dev, hs_words_dev, seqe);
+            T.at(kNone);
+            wait_published(seqe);
+            nnew_c = hs->st.nnew;
+          }
+          if (n_states + nnew_c > state_limit)
+            throw Error(FSTC_ERR_CAPACITY, "reachable states exceed the state limit");
+          if (o.max_arcs && arcs + merged_c > o.max_arcs)
+            throw Error(FSTC_ERR_CAPACITY, "composed arcs exceed opts->max_arcs");
+          if (!ahead_c) {
+            T.at(kAssign);
+            ids(nnew_c);
+            if (scan_new)
+              launch_claim_assign(hvb.as<u32>(), pairspace, vn2, (u32)n_states, sq1b.as<u32>(),
+                                  sq2b.as<u32>(), claim_tmp(), nullptr, s);
+            else
+              assign_ids((u32)nnew_c, newlist.as<u32>(), &dst->nnew);
+            chunk_append(merged_c, nullptr, true);
+            T.at(kNone);
+          }
+          status_clear = true;  // by the append
+          premerge += pairs;
+          product_records += pairs;  // never written as records
+          max_level_pre = std::max(max_level_pre, pairs);
+          arcs += merged_c;
+          n_states += nnew_c;
+          if (nnew_c) ++new_levels;
+          lo = hi;
+          hi = (u32)n_states;
+          ++depth;
+          continue;
+        }
+        chunk_cap = merged_c;  // exact from here on
+      }
+    }
     const u32 seq1 = next_publication();
     count_and_scan(seq1);
     // Speculative product merge: with the dense visited array (no rehash
@@ -919,7 +1186,7 @@ void Composer::run(fstc_result *out) {
     // turnaround.  Otherwise it exits at once and the host launches it again
     // after the synchronisation.
     const u64 maxk = std::min<u64>(maxp1 * maxp2, 64);  // a source's table entries
-    const bool spec = product && dense_vis && (u64)nsrc * maxk * 20 <= kSpecBytes;
+    const bool spec = product && dense_vis && !chunk && (u64)nsrc * maxk * 20 <= kSpecBytes;
     // Direct product level: the speculative product kernel writes its merged
     // arcs straight into the result (grown to hold every source's largest
     // table first); when the level turns out to have records it writes
@@ -1045,7 +1312,9 @@ void Composer::run(fstc_result *out) {
     // shape (then the next, smaller levels usually have none)
     if (small_shape_off && (u64)hs->st.unfit * 8 < nsrc) small_shape_off = false;
     const u64 prodpos = nprod ? hs->st.prod_entries : 0;  // product-merge temp slots
-    if (R == 0 && nprod == 0) break;  // no arc leaves this level: no new states either
+    if (R == 0 && nprod == 0 && !chunk) break;  // no arc leaves this level: no new states either
+    chunk_heavy = nsrc >= kChunkMinSources && R > (u64)kChunkPer * nsrc;
+    if (chunk && hs->st.general == 0) chunk_pure = true;  // the next level is enqueued whole
     premerge += R;
     max_level_pre = std::max(max_level_pre, R);
     product_sources += nprod;
@@ -1070,40 +1339,22 @@ void Composer::run(fstc_result *out) {
     tiles_m.ensure(ntiles * sizeof(uint4));
     sortlist.ensure(ntiles * 4);
     tile_runs.ensure(ntiles * 4);
-    const u64 newcap = std::min<u64>(R + prodpos, pairspace - n_states);
-    newlist.ensure(std::max<u64>(newcap, 1) * 4);
+    // (the claims of a chunk merge that ran are in the list already)
+    const u64 listed = chunk_emitted ? hs->st.nnew : 0;  // (scan_new: marked, not listed)
+    const u64 newcap = std::min<u64>(R + prodpos + (chunk_emitted ? listed : chunk_cap),
+                                     pairspace - n_states);
+    if (!chunk_emitted || newcap > list_cap) {
+      const void *old = newlist.p;
+      newlist.ensure(std::max<u64>(newcap, 1) * 4);
+      if (listed && !scan_new)
+        FSTC_HIP(hipMemcpyAsync(newlist.p, old, listed * 4, hipMemcpyDeviceToDevice, s));
+    }
 
-    // visited table: keep the load factor at most 1/2 for every pair this
-    // level could add
-    // (at most kMaxHashCap slots: an insert into a full table reports it)
-    const u64 need = std::min<u64>(2 * (n_states + newcap), kMaxHashCap);
-    if (!dense_vis && need > hcap && !o.hash_visited && pairspace <= kDenseMaxPairs &&
-        next_pow2(need) * 12 >= pairspace * 4) {
-      // the grown table (8-byte keys, 4-byte ids) would be at least as large
-      // as the dense array over all pairs: move the visited set there (the
-      // level's inserts have not started; every state so far has its id)
-      Buf nv(&A);
-      nv.ensure(pairspace * 4);
-      fill_u32(nv.as<u32>(), kUnvisited, pairspace, s);
-      launch_states_to_dense(sq1b.as<u32>(), sq2b.as<u32>(), n_states, nv.as<u32>(),
-                             m2.num_states, s);
-      hkb.release();
-      std::swap(hvb.p, nv.p); std::swap(hvb.cap, nv.cap);
-      hcap = pairspace;
-      dense_vis = true;
-      vn2 = m2.num_states;
-      ++vis_moves;
-    } else if (!dense_vis && need > hcap) {
-      const u64 ncap = next_pow2(need);
-      Buf nk(&A), nv(&A);
-      nk.ensure(ncap * 8);
-      nv.ensure(ncap * 4);
-      fill_u64(nk.as<u64>(), kEmptyKey, ncap, s);
-      launch_rehash(hkb.as<u64>(), hvb.as<u32>(), hcap, nk.as<u64>(), nv.as<u32>(), ncap - 1,
-                    &dst->err, s);
-      std::swap(hkb.p, nk.p); std::swap(hkb.cap, nk.cap);
-      std::swap(hvb.p, nv.p); std::swap(hvb.cap, nv.cap);
-      hcap = ncap;
+    grow_visited(n_states + newcap);
+    if (chunk && !chunk_emitted) {
+      T.at(kMerge);
+      chunk_emit(newcap);
+      T.at(kNone);
     }
 
     // (a4) match descriptors and the arc-pair write pass
@@ -1111,7 +1362,7 @@ void Composer::run(fstc_result *out) {
     la.mrbase = mrbase.as<u64>();
     la.tiles = tiles_e.as<ExpandTile>();
     T.at(kExpand);
-    if (M) launch_emit(la, hs->st.nwide, hs->st.nheavy, hs->st.ngrp, s);
+    if (M) launch_emit(la, hs->st.nwide, hs->st.nheavy, hs->st.ngrp, !chunk, s);
     // fused levels generate each tile's records inside the merge instead
     const bool fuse = o.fused_merge && !o.no_reduction && key_bits <= kDenseKeyBits && nbig == 0;
     if (!fuse && R) {
@@ -1188,8 +1439,10 @@ void Composer::run(fstc_result *out) {
       u32 *osrc = out_arcs.col(0) + arcs, *odst = out_arcs.col(1) + arcs,
           *oil = out_arcs.col(2) + arcs, *ool = out_arcs.col(3) + arcs;
       float *ow = reinterpret_cast<float *>(out_arcs.col(4)) + arcs;
+      if (chunk) chunk_append(M, nullptr, false);
       if (R)
-        launch_compact(ma, aoff.as<u64>(), nbig ? bigoff.as<u64>() : nullptr, nbig, RB, nprod != 0, M,
+        launch_compact(ma, aoff.as<u64>(), nbig ? bigoff.as<u64>() : nullptr, nbig, RB,
+                       nprod != 0 || chunk, M,
                        hvb.as<u32>(), osrc, odst, oil, ool, ow, s);
       if (nprod)
         launch_compact_sources(ma, aoff.as<u64>(), M, hvb.as<u32>(), osrc, odst, oil, ool, ow, s);
@@ -1203,8 +1456,8 @@ void Composer::run(fstc_result *out) {
     bool assigned = false;                        // ids and arcs of the level are in place
     const bool early = !direct_level && !o.no_reduction && ids_by_scan && !o.max_arcs &&
                        (n_states + newcap) * 8 <= kEarlyBytes &&
-                       (arcs + R + prodpos) * 20 <= kEarlyBytes;
-    last_direct = direct_level;
+                       (arcs + R + prodpos + chunk_cap) * 20 <= kEarlyBytes;
+    last_direct = direct_level || (chunk && nprod == nsrc);
     if (direct_level && ahead) {
       // everything ran before the wait: read the totals
       ++product_launches;
@@ -1311,27 +1564,34 @@ void Composer::run(fstc_result *out) {
       // the per-source joined pairs (records, or the product merge's terms)
       // summed for the level's product-merge pairs
       {
-        ScanJob jobs[2] = {{mend.p, true, aoff.as<u64>()}, {cnt.p, true, ptot.as<u64>()}};
+        ScanJob jobs[3] = {{mend.p, true, aoff.as<u64>()}, {cnt.p, true, ptot.as<u64>()},
+                           {cpairs.p, false, newoff.as<u64>()}};
         jobs[0].sub = tstart.as<u64>();
-        jobs[1].total_only = true;
-        exclusive_scan_lb(jobs, 2, nsrc, lb(nsrc), &dst->scan_ctr, &dst->err, s);
+        jobs[1].total_only = jobs[2].total_only = true;
+        jobs[2].total_to = &dst->chunk_pairs;
+        exclusive_scan_lb(jobs, chunk ? 3 : 2, nsrc, lb(nsrc), &dst->scan_ctr, &dst->err, s);
       }
       launch_emit_tiles(ma, s);
       if (nprod) launch_newlist_product(ma, s);
+      if (scan_new)  // the chunk merge's new pairs and the others'
+        launch_claim_count(hvb.as<u32>(), pairspace, claim_tmp(), &dst->nnew, nullptr, s);
       const u32 seq2 = next_publication();
       launch_merged_total(aoff.as<u64>() + nsrc, nullptr, ptot.as<u64>() + nsrc, ma, hs_dev, seq2, s);
       if (early) {
         T.at(kAssign);
         sq1b.grow_keep((n_states + newcap) * 4, n_states * 4);
         sq2b.grow_keep((n_states + newcap) * 4, n_states * 4);
-        if (o.deterministic_ids)
+        if (scan_new)
+          launch_claim_assign(hvb.as<u32>(), pairspace, vn2, (u32)n_states, sq1b.as<u32>(),
+                              sq2b.as<u32>(), claim_tmp(), nullptr, s);
+        else if (o.deterministic_ids)
           launch_claim_ids(hvb.as<u32>(), pairspace, vn2, (u32)n_states, sq1b.as<u32>(),
                            sq2b.as<u32>(), claim_tmp(), nullptr, s);
         else
           launch_assign_counted(newlist.as<u32>(), &dst->new_count, (u32)newcap, (u32)n_states,
                                 hkb.as<u64>(), hvb.as<u32>(), vn2, sq1b.as<u32>(),
                                 sq2b.as<u32>(), s);
-        append(R + prodpos);
+        append(R + prodpos + chunk_cap);
       }
       T.at(kNone);
       wait_published(seq2);
@@ -1339,9 +1599,10 @@ void Composer::run(fstc_result *out) {
 
       nnew = hs->st.nnew;
       merged = hs->st.merged;
-      premerge += hs->st.prod_records;
-      product_records += hs->st.prod_records;
-      max_level_pre = std::max(max_level_pre, R + hs->st.prod_records);
+      const u64 unwritten = hs->st.prod_records + hs->st.chunk_pairs;
+      premerge += unwritten;
+      product_records += unwritten;
+      max_level_pre = std::max(max_level_pre, R + unwritten);
       dense_records += hs->st.dense_records;
       dense_runs += hs->st.dense_runs;
       sort_runs += hs->st.sort_runs;
@@ -1454,33 +1715,11 @@ void Composer::run(fstc_result *out) {
       T.at(kAssign);
       sq1b.grow_keep(ns_new * 4, n_states * 4);
       sq2b.grow_keep(ns_new * 4, n_states * 4);
-      const u32 *slots = newlist.as<u32>();
-      // ordered ids: ranked in one launch up to kRankMax new pairs; a larger
-      // level takes a pass over the dense visited array while that is cheaper
-      // than a radix sort (0.9 ps a pair of the array against about 60 us and
-      // 150 ps a new pair), or the sort
-      const bool ordered = o.deterministic_ids && nnew > 1;
-      const bool rank = ordered && nnew <= kRankMax;
-      const bool scan = ordered && !rank && dense_vis && pairspace <= kDensePairs + 160ull * nnew;
-      if (rank) {
-        launch_rank_assign(slots, &dst->new_count, nnew, (u32)n_states, hkb.as<u64>(),
-                           hvb.as<u32>(), vn2, sq1b.as<u32>(), sq2b.as<u32>(), s);
-      } else if (scan) {
-        launch_claim_ids(hvb.as<u32>(), pairspace, vn2, (u32)n_states, sq1b.as<u32>(),
-                         sq2b.as<u32>(), claim_tmp(), nullptr, s);
-      } else if (ordered) {
-        const int bq1 = (int)bits_for(m1.num_states - 1), bq2 = (int)bits_for(m2.num_states - 1);
-        dk.ensure((u64)nnew * 8); dv.ensure((u64)nnew * 4);
-        dka.ensure((u64)nnew * 8); dva.ensure((u64)nnew * 4);
-        dtmp.ensure(radix_temp_bytes(nnew));
-        launch_newkeys(newlist.as<u32>(), nnew, hkb.as<u64>(), vn2, bq2, dk.as<u64>(), dv.as<u32>(), s);
-        radix_sort_pairs(dk.as<u64>(), dv.as<u32>(), dka.as<u64>(), dva.as<u32>(), nnew, 0,
-                         bq1 + bq2, dtmp.p, s);
-        slots = dv.as<u32>();
-      }
-      if (!rank && !scan)
-        launch_assign(slots, nnew, (u32)n_states, hkb.as<u64>(), hvb.as<u32>(), vn2,
-                      sq1b.as<u32>(), sq2b.as<u32>(), s);
+      if (scan_new)
+        launch_claim_assign(hvb.as<u32>(), pairspace, vn2, (u32)n_states, sq1b.as<u32>(),
+                            sq2b.as<u32>(), claim_tmp(), nullptr, s);
+      else
+        assign_ids(nnew, newlist.as<u32>(), &dst->new_count);
       if (o.no_reduction)
         launch_fix_dst(out_arcs.col(1) + arcs, merged, hvb.as<u32>(), s);
       else
@@ -1514,8 +1753,8 @@ void Composer::run(fstc_result *out) {
   launch_finals(sq1b.as<u32>(), sq2b.as<u32>(), n_states, m1.final, m2.final, finb.as<uint8_t>(), s);
   {
     const u32 seqf = next_publication();
-    hipLaunchKernelGGL(k_publish_counts, dim3(1), dim3(kWave), 0, s, nullptr, 0u, nullptr, 0u, 0,
-                       nullptr, 0u, dst, hs_dev, hs_words_dev, seqf);
+    hipLaunchKernelGGL(k_publish_counts, dim3(1), dim3(kWave), 0, s, nullptr, 0u, nullptr, 0u,
+                       nullptr, nullptr, 0, nullptr, 0u, dst, hs_dev, hs_words_dev, seqf);
     wait_published(seqf);
   }
 

@@ -856,16 +856,15 @@ static unsigned heavy_grid(u64 n) {
 // Workgroups of each list kernel when the lists are expected empty.
 constexpr unsigned kLeanGrid = 64;
 
-void launch_count(const LevelArgs &a, hipStream_t s, bool lean) {
-  const unsigned g = (unsigned)ceil_div(a.nsrc, kCountNT);
-  hipLaunchKernelGGL(k_count_small, dim3(g), dim3(kCountNT), 0, s, a);
+static void launch_lists(const LevelArgs &a, hipStream_t s, bool lean, bool groups) {
   // 16-lane joins: at most one group per source, at most as many waves as
   // the chip holds (they loop over the list); wide: at most one wave per
   // source (1024 blocks of 8 waves at most); heavy: one block per chunk of
   // a source (512 blocks at most; kLeanGrid when there are few sources)
   const u64 n = a.nsrc;
-  unsigned gg = (unsigned)std::min<u64>((u64)compute_units() * 4,
-                                        ceil_div(n, kListNT / kGroupLanes));
+  unsigned gg = groups ? (unsigned)std::min<u64>((u64)compute_units() * 4,
+                                                 ceil_div(n, kListNT / kGroupLanes))
+                       : 0u;
   unsigned gw = (unsigned)std::min<u64>(1024, ceil_div(n, kListNT / kWave));
   unsigned gh = (unsigned)std::min<u64>(512, std::max<u64>(n, kLeanGrid));
   if (lean) {
@@ -876,9 +875,20 @@ void launch_count(const LevelArgs &a, hipStream_t s, bool lean) {
   hipLaunchKernelGGL(k_count_lists, dim3(gg + gw + gh), dim3(kListNT), 0, s, a, gg, gw);
 }
 
-void launch_emit(const LevelArgs &a, u32 nwide, u32 nheavy, u32 ngrp, hipStream_t s) {
+void launch_count(const LevelArgs &a, hipStream_t s, bool lean) {
+  const unsigned g = (unsigned)ceil_div(a.nsrc, kCountNT);
+  hipLaunchKernelGGL(k_count_small, dim3(g), dim3(kCountNT), 0, s, a);
+  launch_lists(a, s, lean, true);
+}
+
+void launch_count_lists(const LevelArgs &a, hipStream_t s, bool lean) {
+  launch_lists(a, s, lean, false);
+}
+
+void launch_emit(const LevelArgs &a, u32 nwide, u32 nheavy, u32 ngrp, bool thread_joins,
+                 hipStream_t s) {
   const unsigned g = (unsigned)ceil_div(a.nsrc, 256);
-  hipLaunchKernelGGL(k_emit_small, dim3(g), dim3(256), 0, s, a);
+  if (thread_joins) hipLaunchKernelGGL(k_emit_small, dim3(g), dim3(256), 0, s, a);
   if (ngrp) {
     const unsigned gg = (unsigned)std::min<u64>((u64)compute_units() * 8,
                                                 ceil_div((u64)ngrp, 256 / kGroupLanes));

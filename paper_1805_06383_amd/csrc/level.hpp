@@ -48,6 +48,9 @@ struct Status {
   u32 ngrp;           // sources listed for the 16-lane joins
   u32 declined;       // nonzero: the one-workgroup product level did not take the level
   u32 new_count;      // new pairs of the last merged level (kept when the counters clear)
+  u64 general;        // nonzero: the level has sources the chunk merge left to the
+                      // other kernels (product, long or large joins)
+  u64 chunk_pairs;    // joined arc pairs of the sources it merged
 };
 static_assert(offsetof(Status, nprod) % 8 == 0 &&
                   offsetof(Status, nprod_mfma) == offsetof(Status, nprod) + 4,
@@ -171,15 +174,58 @@ constexpr u32 kHoleSrc = 0xffffffffu;
 // list kernels loop over their lists, so a longer list is still counted,
 // by fewer workgroups.
 void launch_count(const LevelArgs &a, hipStream_t s, bool lean = false);
+// The wavefront and workgroup joins' counts alone (after launch_chunk_join).
+void launch_count_lists(const LevelArgs &a, hipStream_t s, bool lean = false);
 // nwide / nheavy / ngrp: the list lengths the count kernels produced
-// (st->nwide, nheavy, ngrp).
-void launch_emit(const LevelArgs &a, u32 nwide, u32 nheavy, u32 ngrp, hipStream_t s);
+// (st->nwide, nheavy, ngrp).  thread_joins: the sources in no list too (not
+// after launch_chunk_join, which lists all it leaves).
+void launch_emit(const LevelArgs &a, u32 nwide, u32 nheavy, u32 ngrp, bool thread_joins,
+                 hipStream_t s);
 // Writes R records: key = (part1 << b2) | part2 (u32 when key_bits <= 32,
 // else u64), weight = p1 * p2.
 // tiles: the ceil(R / kExpandTile) write-tile entries written by launch_emit.
 void launch_expand(const uint4 *match, const u64 *mrbase, u64 M, u64 R, const CsrView &c1,
                    const CsrView &c2, int b2, bool wide_keys, void *rec_key, float *rec_w,
                    ExpandTile *tiles, u32 *err, hipStream_t s);
+
+// Chunk merge (chunk.hip): a wavefront joins, sorts and sums the records of S
+// consecutive sources (at most kChunkS) on the chip, in place of count, scan, match
+// emission, write pass and merge tiles.  It takes the sources whose shorter
+// symbol list has at most kChunkShort symbols and that join at most kChunkPer
+// arc pairs (one record is compared with every other of its source), in
+// batches of at most kChunkElems short-list symbols and kChunkRecs records;
+// its merged arcs go to `cap` temp slots of its own.  The other sources
+// (longer lists, more pairs, no slots left) are listed for the general
+// kernels, product merge included, as the count kernel lists them.
+constexpr u32 kChunkS = 8;
+constexpr u32 kChunkShort = 64;
+constexpr u32 kChunkPer = 256;
+constexpr u32 kChunkElems = 256;
+constexpr u32 kChunkStage = 128;   // longest list staged in LDS,
+constexpr u32 kChunkStaged = 512;  // and staged symbols of a batch in all
+constexpr u32 kChunkRecs = 256;
+constexpr u32 kChunkMinCap = 256, kChunkMaxCap = 512;
+constexpr int kChunkKeyBits = 28;  // a source's number above them, and a key of all
+                                   // ones marks a merged record
+static_assert(kChunkS <= (1u << (31 - kChunkKeyBits)), "no key is all ones");
+struct ChunkArgs {
+  uint4 *tmp;   // [nblk cap] (., M1 part, M2 part, weight bits) from the join,
+                // then (slot or id, a, c, weight bits) after launch_chunk_emit
+  uint8_t *src; // [nblk cap] source of each, less the wavefront's first
+  u32 *cnt;     // [nblk] merged arcs of each wavefront
+  u32 *pairs;   // [nsrc] joined pairs of each source merged here, else 0
+  u32 S, nblk, cap;  // nblk = ceil(nsrc / S); kChunkMinCap .. kChunkMaxCap
+};
+// Sources per wavefront: fewer on a level that would not fill the chip's
+// 8,192 wave slots (a source's steps run one after the other in its wave).
+inline u32 chunk_sources(u64 nsrc) {
+  u32 s = 1;
+  while (s < kChunkS && nsrc > (u64)s * 4096) s <<= 1;
+  return s;
+}
+// Sets tstart / mend (into c.tmp) of the sources it merges, cnt = mc = 0.
+void launch_chunk_join(const LevelArgs &a, const ChunkArgs &c, int b2, int key_bits,
+                       hipStream_t s);
 
 struct MergeArgs {
   const void *rec_key;
@@ -337,7 +383,7 @@ void launch_assign(const u32 *slots, u32 nnew, u32 base, const u64 *hkeys, u32 *
 // (the host need not know it yet); nothing when count is NULL.
 void launch_assign_counted(const u32 *slots, const u32 *count, u32 cap, u32 base,
                            const u64 *hkeys, u32 *hvals, u32 vn2, u32 *sq1, u32 *sq2,
-                           hipStream_t s);
+                           hipStream_t s, const u64 *skip_if = nullptr);
 void launch_newkeys(const u32 *newlist, u32 nnew, const u64 *hkeys, u32 vn2, int bq2, u64 *keys,
                     u32 *vals, hipStream_t s);
 // Result append of the level's merged arcs, so that the output stays grouped
@@ -354,6 +400,17 @@ void launch_compact(const MergeArgs &a, const u64 *aoff, const u64 *bigoff, u32 
 // mend[u] - 1 to aoff[u] ....
 void launch_compact_sources(const MergeArgs &a, const u64 *aoff, u64 M, const u32 *hvals,
                             u32 *osrc, u32 *odst, u32 *oil, u32 *ool, float *ow, hipStream_t s);
+// Visited-table inserts and labels of the chunk-merged arcs (claims to
+// a.newlist; plain: the dense visited array alone is marked, with plain
+// stores, and launch_claim_count finds the new pairs: a claim by
+// compare-and-swap is performed beyond the L2, 100 ps each against 30 for the
+// store, and a level of millions of claims spends most of its time there),
+// and their result append (after the level's ids; M: room from osrc on).  skip_if (may be NULL): nothing is done when that device word is
+// nonzero; clear: the level counters of a.st are zeroed then.
+void launch_chunk_emit(const MergeArgs &a, const ChunkArgs &c, bool plain, hipStream_t s);
+void launch_chunk_compact(const MergeArgs &a, const ChunkArgs &c, const u64 *aoff, u64 M,
+                          const u32 *hvals, u32 *osrc, u32 *odst, u32 *oil, u32 *ool, float *ow,
+                          const u64 *skip_if, bool clear, hipStream_t s);
 // Visited-table inserts and label lookups for every merged arc of the
 // tile-merged sources (merge_big does its own).
 void launch_emit_tiles(const MergeArgs &a, hipStream_t s);
@@ -367,9 +424,15 @@ constexpr u32 kRankMax = 16384;
 void launch_rank_assign(const u32 *list, const u32 *count, u32 cap, u32 base, const u64 *hkeys,
                         u32 *hvals, u32 vn2, u32 *sq1, u32 *sq2, hipStream_t s);
 // The same for every entry of the dense visited array (n pairs) that the
-// level claimed; temp: claim_temp_bytes(n).  skip_if (may be NULL): nothing
-// is done when that device word is nonzero.
+// level claimed, in two passes: launch_claim_count finds and counts them
+// (their number to *nnew when given), launch_claim_assign numbers them;
+// launch_claim_ids is both.  temp: claim_temp_bytes(n).  skip_if (may be
+// NULL): nothing is done when that device word is nonzero.
 size_t claim_temp_bytes(u64 n);
+void launch_claim_count(const u32 *vis, u64 n, void *temp, u32 *nnew, const u64 *skip_if,
+                        hipStream_t s);
+void launch_claim_assign(u32 *vis, u64 n, u32 vn2, u32 base, u32 *sq1, u32 *sq2, void *temp,
+                         const u64 *skip_if, hipStream_t s);
 void launch_claim_ids(u32 *vis, u64 n, u32 vn2, u32 base, u32 *sq1, u32 *sq2, void *temp,
                       const u64 *skip_if, hipStream_t s);
 // Direct product level (see MergeArgs::out_src): ids base + newoff[u] + i for

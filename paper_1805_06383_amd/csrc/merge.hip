@@ -25,6 +25,7 @@
 #include "level.hpp"
 #include "product.hpp"
 #include "radix_rank.hpp"
+#include "visited.hpp"
 
 namespace fstc {
 namespace {
@@ -114,97 +115,12 @@ __device__ __forceinline__ u32 block_offset(u32 wave_value, u32 *s_tmp, u32 *tot
   return base;
 }
 
-// Linear-probing insert of B keys at once (lanes with act[i] unset skip
-// item i).  Each round issues the probe loads of all pending items before
-// testing any, so their latencies overlap.  Slots only ever change from
-// kEmptyKey to a key, so a stale read of kEmptyKey is settled by the CAS and
-// a plain (workgroup-scope) read is enough.  Bounded by the table size.
-template <int B>
-__device__ __forceinline__ void hash_insert_batch(u64 *keys, u64 mask, const u64 (&key)[B],
-                                                  const bool (&act)[B], u32 (&slot)[B],
-                                                  bool (&is_new)[B], u32 *err) {
-  u64 h[B];
-  bool pend[B];
-#pragma unroll
-  for (int i = 0; i < B; ++i) {
-    pend[i] = act[i];
-    is_new[i] = false;
-    slot[i] = 0;
-    h[i] = mix64(key[i]) & mask;
-  }
-  for (u64 probe = 0; probe <= mask; ++probe) {
-    u64 cur[B];
-#pragma unroll
-    for (int i = 0; i < B; ++i)
-      cur[i] = pend[i] ? __hip_atomic_load(&keys[h[i]], __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_WORKGROUP)
-                       : 0;
-    bool any = false;
-#pragma unroll
-    for (int i = 0; i < B; ++i) {
-      if (!pend[i]) continue;
-      if (cur[i] == kEmptyKey) {
-        cur[i] = atomicCAS((unsigned long long *)&keys[h[i]], (unsigned long long)kEmptyKey,
-                           (unsigned long long)key[i]);
-        if (cur[i] == kEmptyKey) {
-          is_new[i] = true;
-          slot[i] = (u32)h[i];
-          pend[i] = false;
-          continue;
-        }
-      }
-      if (cur[i] == key[i]) {
-        slot[i] = (u32)h[i];
-        pend[i] = false;
-        continue;
-      }
-      h[i] = (h[i] + 1) & mask;
-      any = true;
-    }
-    if (!any) return;
-  }
-  set_error(err, kErrHashFull);
-}
-
-// Visited-set insert of B target pairs (key = r1 << 32 | r2): the hash
-// table, or the dense array when a.vn2 != 0 (slot = r1 vn2 + r2; a claim is
-// a CAS from kUnvisited to kClaimed, tried only when a plain read of the
-// entry still sees kUnvisited -- entries never return to it).  known[i]:
-// the pair's id when an earlier level gave it one and the dense array holds
-// it, else kUnvisited.
-template <int B>
-__device__ __forceinline__ void visit_batch(const MergeArgs &a, const u64 (&key)[B],
-                                            const bool (&act)[B], u32 (&slot)[B],
-                                            bool (&is_new)[B], u32 (&known)[B]) {
-  if (!a.vn2) {
-    hash_insert_batch<B>(a.hkeys, a.hmask, key, act, slot, is_new, &a.st->err);
-#pragma unroll
-    for (int i = 0; i < B; ++i) known[i] = kUnvisited;
-    return;
-  }
-  u32 cur[B];
-#pragma unroll
-  for (int i = 0; i < B; ++i) {
-    slot[i] = act[i] ? (u32)(key[i] >> 32) * a.vn2 + (u32)key[i] : 0u;
-    is_new[i] = false;
-    cur[i] = act[i] ? __hip_atomic_load(&a.vis[slot[i]], __ATOMIC_RELAXED,
-                                        __HIP_MEMORY_SCOPE_WORKGROUP)
-                    : 0u;
-  }
-#pragma unroll
-  for (int i = 0; i < B; ++i) {
-    known[i] = cur[i] < kClaimed ? cur[i] : kUnvisited;  // ids are below both markers
-    if (act[i] && cur[i] == kUnvisited) is_new[i] = atomicCAS(&a.vis[slot[i]], kUnvisited, kClaimed) == kUnvisited;
-  }
-}
-
 // The part pairs of B merged arcs -> visited-table insert of the target pair
 // (r1, r2) and the run record (slot | kNewFlag if claimed, a, c, weight) at
 // temp[tpos], source u at runsrc[tpos]; claim[i] = the slot this call
 // claimed for item i, else kNoClaim.  A target that already has an id in the
 // dense array is recorded as id | kIdFlag, so the result append needs no
 // visited-array lookup for it.
-constexpr u32 kNoClaim = 0xffffffffu;  // slots are below 2^31
 template <int B>
 __device__ __forceinline__ void emit_parts(const MergeArgs &a, const bool (&act)[B],
                                            const u32 (&u)[B], const uint2 (&P1)[B],
@@ -252,51 +168,6 @@ __device__ __forceinline__ void emit_batch(const MergeArgs &a, const bool (&act)
     P2[i] = act[i] ? a.parts2[pb2[i] + (u32)(key[i] & ((1ull << a.b2) - 1))] : make_uint2(0, 0);
   }
   emit_parts<B>(a, act, u, P1, P2, tpos, w, claim);
-}
-
-// New pairs of a workgroup's merged arcs, collected in LDS and appended to the
-// level's new-pair list with one device atomic (same-address atomics
-// serialise at about 13 ns each).  The list's order is arbitrary: ids are
-// given in list order or by rank (launch_assign, launch_rank_assign).
-// Counting and listing the claims in two passes over the merged arcs, with a
-// scan between, took 180 us a level of 6M arcs and three launches a level.
-template <u32 CAP>
-struct ClaimLds {
-  u32 slot[CAP];
-  u32 n, base;
-};
-
-template <u32 CAP>
-__device__ __forceinline__ void claims_begin(ClaimLds<CAP> &L) {
-  if (threadIdx.x == 0) L.n = 0;
-  __syncthreads();
-}
-
-// Whole waves; the workgroup adds at most CAP claims in all.
-template <u32 CAP>
-__device__ __forceinline__ void claims_add(ClaimLds<CAP> &L, u32 claim) {
-  const u64 m = __ballot(claim != kNoClaim);
-  if (!m) return;
-  const u32 leader = (u32)__builtin_ctzll(m);
-  u32 at = 0;
-  if (lane_id() == leader) at = atomicAdd(&L.n, (u32)__popcll(m));
-  at = __shfl(at, (int)leader, kWave) + count_below(m);
-  if (claim != kNoClaim && at < CAP) L.slot[at] = claim;
-}
-
-template <u32 CAP>
-__device__ __forceinline__ void claims_end(const MergeArgs &a, ClaimLds<CAP> &L) {
-  __syncthreads();
-  const u32 n = L.n;
-  if (n == 0) return;  // uniform
-  if (threadIdx.x == 0) L.base = atomicAdd(&a.st->nnew, n);
-  __syncthreads();
-  const u64 base = L.base;
-  if (n > CAP || base + n > a.newcap) {  // impossible: the capacities bound both
-    if (threadIdx.x == 0) set_error(&a.st->err, kErrNewList);
-    return;
-  }
-  for (u32 i = threadIdx.x; i < n; i += blockDim.x) a.newlist[base + i] = L.slot[i];
 }
 
 // LDS of the sorting tile merge.
@@ -350,9 +221,39 @@ __device__ __forceinline__ void merge_sort_tile(const MergeArgs &a, u32 tile, So
   u32 *s_mark = reinterpret_cast<u32 *>(s_keys);
   for (u32 i = threadIdx.x; i < n; i += NT) s_mark[i] = 0;
   __syncthreads();
-  for (u32 u = s0 + threadIdx.x; u < s1; u += NT) {
-    const u64 c = a.roff[u + 1] - a.roff[u];
-    if (c) s_mark[a.roff[u] - rb] = u + 1;
+  if (s1 - s0 <= 4 * (u32)C) {
+    for (u32 u = s0 + threadIdx.x; u < s1; u += NT) {
+      const u64 c = a.roff[u + 1] - a.roff[u];
+      if (c) s_mark[a.roff[u] - rb] = u + 1;
+    }
+  } else {
+    // few of the tile's many sources have records (the others were merged on
+    // the chip): every record finds its source, and the first of a source
+    // marks it.  Walking 10^6 sources between a tile's records took 2.3 ms.
+    u32 lo[IT], hi[IT];
+#pragma unroll
+    for (int j = 0; j < IT; ++j) {
+      lo[j] = s0;  // invariant: roff[lo] <= rb + e, the source in [lo, hi)
+      hi[j] = s1;
+    }
+    for (u32 span = s1 - s0; span > 1; span = (span + 1) >> 1) {  // uniform
+      u64 x[IT];
+#pragma unroll
+      for (int j = 0; j < IT; ++j) x[j] = a.roff[(lo[j] + hi[j]) >> 1];
+#pragma unroll
+      for (int j = 0; j < IT; ++j) {
+        const u32 e = min((u32)(j * NT) + threadIdx.x, n - 1), m = (lo[j] + hi[j]) >> 1;
+        if (hi[j] - lo[j] > 1) {
+          if (x[j] <= rb + e) lo[j] = m;
+          else hi[j] = m;
+        }
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < IT; ++j) {
+      const u32 e = (u32)(j * NT) + threadIdx.x;
+      if (e < n && a.roff[lo[j]] == rb + e) s_mark[e] = lo[j] + 1;
+    }
   }
   __syncthreads();
   if (s_mark[0] == 0) {  // impossible: element 0 starts a source
@@ -2213,6 +2114,17 @@ __global__ __launch_bounds__(256) void k_claim_count(const u32 *vis, u64 n, u64 
   if (lane == 0) counts[wv] = c;  // also of the waves past the array's end
 }
 
+// *nnew = sum of the n counts.
+__global__ __launch_bounds__(1024) void k_claim_total(const u32 *counts, u32 n, u32 *nnew,
+                                                      const u64 *skip_if) {
+  __shared__ u32 s_tmp[1024 / kWave];
+  if (skip_if && *skip_if) return;
+  u32 c = 0;
+  for (u32 j = threadIdx.x; j < n; j += 1024) c += counts[j];
+  c = block_sum<1024, u32>(c, s_tmp);
+  if (threadIdx.x == 0) *nnew = c;
+}
+
 __global__ __launch_bounds__(256) void k_claim_assign(u32 *vis, u64 n, u64 E, const u64 *bits,
                                                       const u32 *counts, const u64 *skip_if,
                                                       u32 base, u32 vn2, u32 *sq1, u32 *sq2) {
@@ -2449,7 +2361,9 @@ __global__ void k_states_to_dense(const u32 *sq1, const u32 *sq2, u64 n, u32 *vi
 // New pair i of the list gets id base + i: i < nnew, or i < min(*count,
 // nnew) when count is given (nnew is then the list's capacity).
 __global__ void k_assign(const u32 *slots, u32 nnew, const u32 *count, u32 base,
-                         const u64 *hkeys, u32 *hvals, u32 vn2, u32 *sq1, u32 *sq2) {
+                         const u64 *hkeys, u32 *hvals, u32 vn2, u32 *sq1, u32 *sq2,
+                         const u64 *skip_if) {
+  if (skip_if && *skip_if) return;
   const u32 n = count ? min(*count, nnew) : nnew;
   for (u64 i = (u64)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (u64)gridDim.x * blockDim.x) {
     const u32 slot = slots[i];
@@ -2474,14 +2388,6 @@ __global__ void k_newkeys(const u32 *newlist, u32 nnew, const u64 *hkeys, u32 vn
   const u64 k = vn2 ? ((u64)(slot / vn2) << 32) | (slot % vn2) : hkeys[slot];
   keys[i] = ((k >> 32) << bq2) | (k & 0xffffffffull);
   vals[i] = slot;
-}
-
-// Target id of a merged arc's record word x: the id itself when it carries
-// kIdFlag (dense visited array only: its slots and ids are below 2^30, while
-// hash-table slots use bit 30 themselves), else the id the visited set now
-// holds at the slot.
-__device__ __forceinline__ u32 target_id(const MergeArgs &a, u32 x, const u32 *hvals) {
-  return (a.vn2 && (x & kIdFlag)) ? x & ~kIdFlag : hvals[x & ~kNewFlag];
 }
 
 // Result append of tile-merged and multi-block sources, kCompactB runs per
@@ -2655,22 +2561,6 @@ __device__ __forceinline__ void publish(const Status *st, Status *host, u32 seq,
   if (nt > 1) __syncthreads();
   if (t == 0) __hip_atomic_store(&host->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
-
-// (level_clear_mask names the same fields, for publications that clear them)
-__device__ __forceinline__ void clear_level(Status *st) {
-  st->R = st->M = st->merged = st->RB = 0;
-  st->nwide = st->nheavy = st->nbig = st->nnew = 0;
-  st->max_small = 0;
-  st->dense_records = st->dense_runs = st->sort_runs = 0;
-  st->nprod = st->nprod_mfma = 0;
-  st->prod_records = st->prod_entries = 0;
-  st->nsort = 0;
-  st->ngen = 0;
-  st->ngrp = 0;
-  st->unfit = 0;
-  st->declined = 0;
-}
-
 
 // Level totals after the merge: merged arcs (end of the scan of merged arcs
 // per source), new pairs (*nt, or the length of the new-pair list), the
@@ -2991,15 +2881,33 @@ size_t claim_temp_bytes(u64 n) {
   return waves * 4 + 256 + (ceil_div(n, kClaimStep) * 16 + 16) * 8;
 }
 
+// Workgroups and count array of the claim passes.
+static unsigned claim_grid(u64 n) { return (unsigned)ceil_div(ceil_div(n, claim_share(n)), 4); }
+static u64 *claim_bits(void *temp, unsigned g) {
+  return reinterpret_cast<u64 *>(static_cast<char *>(temp) + ((g * 16ull + 255) & ~255ull));
+}
+
+void launch_claim_count(const u32 *vis, u64 n, void *temp, u32 *nnew, const u64 *skip_if,
+                        hipStream_t s) {
+  const unsigned g = claim_grid(n);
+  hipLaunchKernelGGL(k_claim_count, dim3(g), dim3(256), 0, s, vis, n, claim_share(n),
+                     claim_bits(temp, g), static_cast<u32 *>(temp), skip_if);
+  if (nnew)
+    hipLaunchKernelGGL(k_claim_total, dim3(1), dim3(1024), 0, s, static_cast<const u32 *>(temp), g * 4u,
+                       nnew, skip_if);
+}
+
+void launch_claim_assign(u32 *vis, u64 n, u32 vn2, u32 base, u32 *sq1, u32 *sq2, void *temp,
+                         const u64 *skip_if, hipStream_t s) {
+  const unsigned g = claim_grid(n);
+  hipLaunchKernelGGL(k_claim_assign, dim3(g), dim3(256), 0, s, vis, n, claim_share(n),
+                     claim_bits(temp, g), static_cast<u32 *>(temp), skip_if, base, vn2, sq1, sq2);
+}
+
 void launch_claim_ids(u32 *vis, u64 n, u32 vn2, u32 base, u32 *sq1, u32 *sq2, void *temp,
                       const u64 *skip_if, hipStream_t s) {
-  const u64 E = claim_share(n);
-  const unsigned g = (unsigned)ceil_div(ceil_div(n, E), 4);
-  u32 *counts = static_cast<u32 *>(temp);
-  u64 *bits = reinterpret_cast<u64 *>(static_cast<char *>(temp) + ((g * 16ull + 255) & ~255ull));
-  hipLaunchKernelGGL(k_claim_count, dim3(g), dim3(256), 0, s, vis, n, E, bits, counts, skip_if);
-  hipLaunchKernelGGL(k_claim_assign, dim3(g), dim3(256), 0, s, vis, n, E, bits, counts, skip_if,
-                     base, vn2, sq1, sq2);
+  launch_claim_count(vis, n, temp, nullptr, skip_if, s);
+  launch_claim_assign(vis, n, vn2, base, sq1, sq2, temp, skip_if, s);
 }
 
 void launch_assign_direct(const MergeArgs &a, const u64 *newoff, u32 base, u32 *sq1, u32 *sq2,
@@ -3065,16 +2973,16 @@ void launch_assign(const u32 *slots, u32 nnew, u32 base, const u64 *hkeys, u32 *
                    u32 *sq1, u32 *sq2, hipStream_t s) {
   if (!nnew) return;
   hipLaunchKernelGGL(k_assign, dim3((unsigned)ceil_div(nnew, 256)), dim3(256), 0, s, slots, nnew,
-                     (const u32 *)nullptr, base, hkeys, hvals, vn2, sq1, sq2);
+                     (const u32 *)nullptr, base, hkeys, hvals, vn2, sq1, sq2, (const u64 *)nullptr);
 }
 
 void launch_assign_counted(const u32 *slots, const u32 *count, u32 cap, u32 base,
                            const u64 *hkeys, u32 *hvals, u32 vn2, u32 *sq1, u32 *sq2,
-                           hipStream_t s) {
+                           hipStream_t s, const u64 *skip_if) {
   if (!count || !cap) return;
   const unsigned g = (unsigned)std::min<u64>(ceil_div(cap, 256), 2048);
   hipLaunchKernelGGL(k_assign, dim3(g), dim3(256), 0, s, slots, cap, count, base, hkeys, hvals,
-                     vn2, sq1, sq2);
+                     vn2, sq1, sq2, skip_if);
 }
 
 void launch_newkeys(const u32 *newlist, u32 nnew, const u64 *hkeys, u32 vn2, int bq2, u64 *keys,
@@ -3172,6 +3080,8 @@ u64 level_clear_mask() {
   add(offsetof(Status, ngrp), 4);
   add(offsetof(Status, unfit), 4);
   add(offsetof(Status, declined), 4);
+  add(offsetof(Status, general), 8);
+  add(offsetof(Status, chunk_pairs), 8);
   return m;
 }
 

@@ -572,6 +572,12 @@ void exclusive_scan_lb(const ScanJob *jobs, int k, u64 n, void *state, u32 *ctr,
     go(std::integral_constant<int, 4>(), std::integral_constant<int, 0b1001>(), std::integral_constant<int, 0>());
   else if (k == 3 && p.wide == 0b110u && subm == 0b100u)
     go(std::integral_constant<int, 3>(), std::integral_constant<int, 0b110>(), std::integral_constant<int, 0b100>());
+  else if (k == 4 && p.wide == 0b0111u && subm == 0b0001u)
+    go(std::integral_constant<int, 4>(), std::integral_constant<int, 0b0111>(), std::integral_constant<int, 0b0001>());
+  else if (k == 3 && p.wide == 0b011u && subm == 0b001u)
+    go(std::integral_constant<int, 3>(), std::integral_constant<int, 0b011>(), std::integral_constant<int, 0b001>());
+  else if (k == 2 && p.wide == 0b11u && subm == 0b01u)
+    go(std::integral_constant<int, 2>(), std::integral_constant<int, 0b11>(), std::integral_constant<int, 0b01>());
   else if (k == 1 && p.wide == 1u && subm == 0)
     go(std::integral_constant<int, 1>(), std::integral_constant<int, 1>(), std::integral_constant<int, 0>());
   else if (k == 1) go(std::integral_constant<int, 1>(), I(), I());

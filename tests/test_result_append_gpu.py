@@ -30,9 +30,9 @@ def mixed_pair(seed, hub1, hub2):
 
         for q in [0] + list(range(40, NQ)):            # hubs: every arc on symbol 0
             add(q, 1 + np.arange(hub) % (NQ - 1), np.zeros(hub, int), np.arange(hub))
-        for q in range(1, 24):                         # dense: two slots x sixteen symbols
-            add(q, np.tile(rng.integers(0, NQ, 2), 16), np.repeat(np.arange(16), 2),
-                np.tile(rng.choice(hub, 2, replace=False), 16))
+        for q in range(1, 24):                         # dense: three slots x all symbols
+            add(q, np.tile(rng.integers(0, NQ, 3), SYMS), np.repeat(np.arange(SYMS), 3),
+                np.tile(rng.choice(hub, 3, replace=False), SYMS))
         for q in range(24, 40):                        # irregular
             n = int(rng.integers(1, 40))
             add(q, rng.integers(0, NQ, n), rng.integers(0, SYMS, n), rng.integers(0, hub, n))

@@ -186,7 +186,7 @@ typedef struct fstc_stats {
   uint32_t num_host_syncs;
   uint64_t max_frontier;      /* largest number of pairs expanded at once   */
   uint64_t max_level_premerge;/* largest per-level unmerged arc count       */
-  uint64_t big_sources;       /* sources merged by the multi-block path     */
+  uint64_t big_sources;       /* sources of more records than a merge tile takes */
   uint64_t hash_capacity;     /* final visited-table capacity (slots)       */
   double ms_total;            /* whole call, host wall clock                */
   double ms_csr;              /* both (state, inner symbol) CSR builds      */

@@ -404,7 +404,7 @@ __device__ __forceinline__ u32 chunk_batch(const LevelArgs &a, const ChunkArgs &
         a.wrange[a.nsrc - 1 - at] = rr;
         a.cnt[u] = n;
         a.mc[u] = mc;
-        if (n > kMergeSmall) a.big[atomicAdd(&a.st->nbig, 1u)] = u;
+        if (n > kMergeSmall) list_large(a, u, n);
         else atomicMax(&a.st->max_small, (u32)n);
       }
     }

@@ -1305,7 +1305,7 @@ void Composer::run(fstc_result *out) {
       wait_published(seq1b);
     }
     const u64 R = hs->st.R, M = hs->st.M;
-    const u32 nbig = hs->st.nbig, nprod = hs->st.nprod;
+    const u32 nbig = hs->st.nbig, nmid = hs->st.nmid, nprod = hs->st.nprod;
     lists_empty = hs->st.nwide == 0 && hs->st.nheavy == 0 && hs->st.ngrp == 0;
     listed_empty = hs->st.ngen == 0;
     // tried again once at most one source in eight of a level is of such a
@@ -1319,7 +1319,7 @@ void Composer::run(fstc_result *out) {
     max_level_pre = std::max(max_level_pre, R);
     product_sources += nprod;
     product_mfma_sources += hs->st.nprod_mfma;
-    big_total += nbig;
+    big_total += nbig + nmid;
 
     match.ensure(M * sizeof(uint4));
     mrbase.ensure(M * 8);
@@ -1334,8 +1334,8 @@ void Composer::run(fstc_result *out) {
     tiles_e.ensure(ceil_div(R, kExpandTile) * sizeof(ExpandTile));
     // merge window: as wide as the largest small source allows (see level.hpp)
     const u64 max_small = std::max<u32>(1, hs->st.max_small);
-    const u64 window = nbig ? kMergeSmall : (u64)kMergeCap - max_small + 1;
-    const u64 ntiles = ceil_div(R, window);
+    const u64 window = nbig || nmid ? kMergeSmall : (u64)kMergeCap - max_small + 1;
+    const u64 ntiles = ceil_div(R, window) + nmid;
     tiles_m.ensure(ntiles * sizeof(uint4));
     sortlist.ensure(ntiles * 4);
     tile_runs.ensure(ntiles * 4);
@@ -1364,7 +1364,8 @@ void Composer::run(fstc_result *out) {
     T.at(kExpand);
     if (M) launch_emit(la, hs->st.nwide, hs->st.nheavy, hs->st.ngrp, !chunk, s);
     // fused levels generate each tile's records inside the merge instead
-    const bool fuse = o.fused_merge && !o.no_reduction && key_bits <= kDenseKeyBits && nbig == 0;
+    const bool fuse = o.fused_merge && !o.no_reduction && key_bits <= kDenseKeyBits &&
+                      nbig == 0 && nmid == 0;
     if (!fuse && R) {
       T.at(kWriteKernel);
       launch_expand(match.as<uint4>(), mrbase.as<u64>(), M, R, view(c1), view(c2), b2, wide_keys,
@@ -1403,6 +1404,7 @@ void Composer::run(fstc_result *out) {
     ma.sortlist = sortlist.as<u32>();
     ma.tile_runs = tile_runs.as<u32>();
     ma.ntiles = ntiles;
+    ma.nmid = nmid;
     ma.window = window;
     ma.tstart = tstart.as<u64>();
     ma.mend = mend.as<u64>();
@@ -1539,6 +1541,7 @@ void Composer::run(fstc_result *out) {
         }
         T.at(kSortKernel);
         launch_merge_sort(ma, wide_keys, s);
+        launch_merge_mid(ma, wide_keys, s);
         ++sort_launches;
         T.at(kMerge);
       }
@@ -1547,8 +1550,7 @@ void Composer::run(fstc_result *out) {
         bigoff.ensure(((u64)nbig + 1) * 8);
         launch_big_counts(roff.as<u64>(), big.as<u32>(), nbig, bigcnt.as<u64>(), s);
         exclusive_scan(bigcnt.as<u64>(), bigoff.as<u64>(), nbig, stmp.p, s);
-        read_words(bigoff.as<u64>() + nbig, 1);
-        RB = hs->words[0];
+        RB = hs->st.RB;
         big_records += RB;
         merge_big(ma, wide_keys, nbig, bigoff.as<u64>(), RB, level_tmp, s);
       }

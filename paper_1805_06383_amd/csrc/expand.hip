@@ -75,8 +75,9 @@ __device__ __forceinline__ u32 seg_len(const u32 *seg_off, u32 s) { return seg_o
 
 // ---------------------------------------------------------------------------
 // Sources of more than kMergeSmall unmerged arcs are merged by the
-// multi-block path (a.big); the largest count among the others sizes the
-// merge window (st->max_small).  Both are gathered by the count kernels.
+// multi-block path (a.big) or a workgroup each (a.big from its end); the
+// largest count among the others sizes the merge window (st->max_small).  All
+// are gathered by the count kernels.
 constexpr int kCountNT = 256;
 
 // How source ranges r are joined (the rules beside kThreadSteps; sources
@@ -147,11 +148,13 @@ __global__ __launch_bounds__(kCountNT) void k_count_small(LevelArgs a) {
       });
       a.cnt[u] = cnt;
       a.mc[u] = mc;
-      pred[2] = cnt > kMergeSmall;
+      pred[2] = cnt > kMergeMid;
+      if (cnt > kMergeSmall && !pred[2]) list_large(a, (u32)u, cnt);
+      if (pred[2]) atomicAdd((unsigned long long *)&a.st->RB, (unsigned long long)cnt);
       unfit = unfit || cnt > kSmallPerSource;
     }
   }
-  const u32 small_max = wave_max((u32)(pred[2] ? 0 : cnt));
+  const u32 small_max = wave_max((u32)(cnt > kMergeSmall ? 0 : cnt));
   const u32 nunfit = (u32)__popcll(__ballot(unfit));
   __syncthreads();
   if (lane == 0 && nunfit) atomicAdd(&s_unfit, nunfit);
@@ -192,7 +195,7 @@ __global__ __launch_bounds__(kCountNT) void k_count_small(LevelArgs a) {
 // joining wave or thread 0 of the joining block): big sources are rare, the
 // maximum is kept in `run_max` and published once per block.
 __device__ __forceinline__ void note_count(const LevelArgs &a, u32 u, u64 cnt, u32 &run_max) {
-  if (cnt > kMergeSmall) a.big[atomicAdd(&a.st->nbig, 1u)] = u;
+  if (cnt > kMergeSmall) list_large(a, u, cnt);
   else run_max = max(run_max, (u32)cnt);
 }
 

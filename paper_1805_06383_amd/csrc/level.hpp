@@ -28,7 +28,7 @@ struct Status {
   u64 R;        // unmerged composed arcs of the level
   u64 M;        // matched (source, inner symbol) segment pairs of the level
   u64 merged;   // merged arcs of the level
-  u64 RB;       // records of sources merged by the multi-block path
+  u64 RB;       // records of the nbig sources merged by the multi-block path
   u32 nwide, nheavy, nbig, nnew;
   u32 err;      // kErr* bits, sticky for the whole call
   u32 max_small;  // largest record count of a source merged by the tiles
@@ -51,6 +51,7 @@ struct Status {
   u64 general;        // nonzero: the level has sources the chunk merge left to the
                       // other kernels (product, long or large joins)
   u64 chunk_pairs;    // joined arc pairs of the sources it merged
+  u32 nmid, pad;      // sources merged by a workgroup each
 };
 static_assert(offsetof(Status, nprod) % 8 == 0 &&
                   offsetof(Status, nprod_mfma) == offsetof(Status, nprod) + 4,
@@ -90,7 +91,9 @@ struct HeavyChunk {
 };
 
 // Merge tiles: 512 threads x 8 items = 4096 records of LDS capacity.  Sources
-// of more than kMergeSmall records take the multi-block path.  A tile takes
+// of more than kMergeSmall records take a workgroup of 1,024 threads each
+// (up to kMergeMid records, as many as its LDS sorts: k_merge_mid) or the
+// multi-block path.  A tile takes
 // the sources whose first record falls in a window of W records; with m the
 // largest small-source count, every such source ends within the tile's
 // capacity when W <= kMergeCap - m + 1 (and, when multi-block sources exist,
@@ -99,7 +102,10 @@ constexpr int kMergeNT = 512;
 constexpr int kMergeIT = 8;
 constexpr int kMergeCap = kMergeNT * kMergeIT;
 constexpr u64 kMergeSmall = kMergeCap / 2;
+constexpr int kMidNT = 1024;
+constexpr u64 kMergeMid = kMidNT * kMergeIT;
 constexpr int kIdxBits = 12;  // log2(kMergeCap)
+constexpr int kMidIdxBits = 13;  // log2(kMergeMid)
 constexpr int kMaxKeyBits = 64 - 2 * kIdxBits;  // 40: part-rank bits of both sides
 
 // A tile whose sources and keys span at most kDenseCap (source, key) pairs
@@ -141,7 +147,8 @@ struct LevelArgs {
   uint4 *match;          // [M] (M1 arc start, M2 arc start, n1, n2)
   u64 *mrbase;           // [M] first record of each match
   ExpandTile *tiles;     // [ceil(R / kExpandTile)] write-tile entries
-  u32 *big;              // [nsrc] sources for the multi-block merge (st->nbig)
+  u32 *big;              // [nsrc] sources for the multi-block merge (st->nbig), and
+                         // from its end those merged by a workgroup each (st->nmid)
   u32 *pk;               // [nsrc] table entries of a product-merge source, else 0
   uint4 *phdr;           // [2 nsrc] product-merge source header (see ProdHeader)
   u32 prod;              // nonzero: sources may take the product merge
@@ -253,10 +260,11 @@ struct MergeArgs {
   u64 *tstart;     // [nsrc] first temp slot of each source's merged arcs (0 if none)
   u64 *mend;       // [nsrc] one past its last slot (0 if none)
   u64 window;      // W: tile t takes the sources starting in [t W, (t + 1) W)
-  uint4 *tiles;    // [ntiles = ceil(R / W)] scratch: tile descriptors
+  uint4 *tiles;    // [ntiles = ceil(R / W) + nmid] scratch: tile descriptors
   u32 *sortlist;   // [ntiles] scratch: tiles left to the sort kernel
   u32 *tile_runs;  // [ntiles] merged runs each tile wrote (zero-filled before the merge)
-  u64 ntiles;
+  u64 ntiles;      // merge tiles: the last nmid hold one source of k_merge_mid each
+  u32 nmid;
   Status *st;
   // multi-block path
   u32 *big;        // [nbig] level-local source indices
@@ -363,6 +371,8 @@ void launch_fuse_merge(const MergeArgs &a, bool narrow, hipStream_t s);
 void launch_prod_sources(const MergeArgs &a, bool narrow, hipStream_t s, bool lean = false);
 // Multi-block merge of the nbig sources listed in a.big; bigoff has nbig + 1
 // entries (exclusive scan of their record counts, total RB).
+// Merge of the a.nmid sources listed from the end of a.big.
+void launch_merge_mid(const MergeArgs &a, bool wide_keys, hipStream_t s);
 void launch_big_counts(const u64 *roff, const u32 *big, u32 nbig, u64 *bigcnt, hipStream_t s);
 void merge_big(const MergeArgs &a, bool wide_keys, u32 nbig, const u64 *bigoff, u64 RB,
                Arena &T, hipStream_t s);

@@ -99,6 +99,7 @@ __device__ __forceinline__ bool dense_tile(const uint4 &td, int key_bits) {
 
 // Exclusive prefix over the waves of the block of one value per wave (taken
 // from any lane); *total receives the block total.  All threads must call it.
+template <int NW = fstc::kMergeNT / kWave>
 __device__ __forceinline__ u32 block_offset(u32 wave_value, u32 *s_tmp, u32 *total) {
   const u32 lane = lane_id(), w = threadIdx.x / kWave;
   __syncthreads();
@@ -170,32 +171,42 @@ __device__ __forceinline__ void emit_batch(const MergeArgs &a, const bool (&act)
   emit_parts<B>(a, act, u, P1, P2, tpos, w, claim);
 }
 
-// LDS of the sorting tile merge.
+// Where the runs of merge tile `tile` (descriptor td) begin in temp: at its
+// first record.
+__device__ __forceinline__ u64 tile_base(const MergeArgs &a, u64 tile, const uint4 &td) {
+  return tile < a.ntiles - a.nmid ? tile * a.window + td.z : a.roff[td.x];
+}
+
+// LDS of the sorting tile merge by NT threads (ONE: of a single source).
+template <int NT, bool ONE>
 struct SortLds {
-  u64 keys[C];
-  float w[C];
-  u32 segsrc[C];
-  u32 cnt[NW * 256];
+  u64 keys[NT * IT];
+  float w[NT * IT];
+  u32 segsrc[ONE ? 1 : NT * IT];
+  u32 cnt[NT / kWave * 256];
   u32 base[256];
-  u32 tmp[NW];
-  double wsum[NW];
-  u32 wflag[NW];
+  u32 tmp[NT / kWave];
+  double wsum[NT / kWave];
+  u32 wflag[NT / kWave];
 };
 
 // Sorting merge of tile `tile` by the whole block.
-template <class KT>
-__device__ __forceinline__ void merge_sort_tile(const MergeArgs &a, u32 tile, SortLds &L) {
+template <class KT, int NT, bool ONE>
+__device__ __forceinline__ void merge_sort_tile(const MergeArgs &a, u32 tile,
+                                                SortLds<NT, ONE> &L) {
+  constexpr int C = NT * IT, NW = NT / kWave, kIdxBits = ONE ? kMidIdxBits : fstc::kIdxBits;
+  static_assert(C == 1 << kIdxBits, "element indices");
   u64 *s_keys = L.keys;
   float *s_w = L.w;
   u32 *s_segsrc = L.segsrc, *s_cnt = L.cnt, *s_base = L.base, *s_tmp = L.tmp;
   double *s_wsum = L.wsum;
   u32 *s_wflag = L.wflag;
   const u32 lane = lane_id(), w = threadIdx.x / kWave;
-  const u64 tstart = (u64)tile * a.window;
   const uint4 td = a.tiles[tile];
+  const u64 tstart = ONE ? a.roff[td.x] : (u64)tile * a.window;
   const u32 s0 = td.x, s1 = td.y;
   if (s0 >= s1) return;
-  if (dense_tile(td, a.key_bits) && !(td.w & kRerouted)) return;  // merged by k_merge_dense
+  if (!ONE && dense_tile(td, a.key_bits) && !(td.w & kRerouted)) return;  // merged by k_merge_dense
   const u32 n = td.w & ~kRerouted;
   const u64 rb = tstart + td.z;
   if (n > (u32)C || (u64)td.z + n > (u64)C) {
@@ -219,46 +230,50 @@ __device__ __forceinline__ void merge_sort_tile(const MergeArgs &a, u32 tile, So
 
   // 1. mark the first record of every non-empty source with its index + 1
   u32 *s_mark = reinterpret_cast<u32 *>(s_keys);
-  for (u32 i = threadIdx.x; i < n; i += NT) s_mark[i] = 0;
-  __syncthreads();
-  if (s1 - s0 <= 4 * (u32)C) {
-    for (u32 u = s0 + threadIdx.x; u < s1; u += NT) {
-      const u64 c = a.roff[u + 1] - a.roff[u];
-      if (c) s_mark[a.roff[u] - rb] = u + 1;
-    }
+  if (ONE) {
+    if (threadIdx.x == 0) s_segsrc[0] = s0;
   } else {
-    // few of the tile's many sources have records (the others were merged on
-    // the chip): every record finds its source, and the first of a source
-    // marks it.  Walking 10^6 sources between a tile's records took 2.3 ms.
-    u32 lo[IT], hi[IT];
-#pragma unroll
-    for (int j = 0; j < IT; ++j) {
-      lo[j] = s0;  // invariant: roff[lo] <= rb + e, the source in [lo, hi)
-      hi[j] = s1;
-    }
-    for (u32 span = s1 - s0; span > 1; span = (span + 1) >> 1) {  // uniform
-      u64 x[IT];
-#pragma unroll
-      for (int j = 0; j < IT; ++j) x[j] = a.roff[(lo[j] + hi[j]) >> 1];
+    for (u32 i = threadIdx.x; i < n; i += NT) s_mark[i] = 0;
+    __syncthreads();
+    if (s1 - s0 <= 4 * (u32)C) {
+      for (u32 u = s0 + threadIdx.x; u < s1; u += NT) {
+        const u64 c = a.roff[u + 1] - a.roff[u];
+        if (c) s_mark[a.roff[u] - rb] = u + 1;
+      }
+    } else {
+      // few of the tile's many sources have records (the others were merged on
+      // the chip): every record finds its source, and the first of a source
+      // marks it.  Walking 10^6 sources between a tile's records took 2.3 ms.
+      u32 lo[IT], hi[IT];
 #pragma unroll
       for (int j = 0; j < IT; ++j) {
-        const u32 e = min((u32)(j * NT) + threadIdx.x, n - 1), m = (lo[j] + hi[j]) >> 1;
-        if (hi[j] - lo[j] > 1) {
-          if (x[j] <= rb + e) lo[j] = m;
-          else hi[j] = m;
+        lo[j] = s0;  // invariant: roff[lo] <= rb + e, the source in [lo, hi)
+        hi[j] = s1;
+      }
+      for (u32 span = s1 - s0; span > 1; span = (span + 1) >> 1) {  // uniform
+        u64 x[IT];
+#pragma unroll
+        for (int j = 0; j < IT; ++j) x[j] = a.roff[(lo[j] + hi[j]) >> 1];
+#pragma unroll
+        for (int j = 0; j < IT; ++j) {
+          const u32 e = min((u32)(j * NT) + threadIdx.x, n - 1), m = (lo[j] + hi[j]) >> 1;
+          if (hi[j] - lo[j] > 1) {
+            if (x[j] <= rb + e) lo[j] = m;
+            else hi[j] = m;
+          }
         }
       }
-    }
 #pragma unroll
-    for (int j = 0; j < IT; ++j) {
-      const u32 e = (u32)(j * NT) + threadIdx.x;
-      if (e < n && a.roff[lo[j]] == rb + e) s_mark[e] = lo[j] + 1;
+      for (int j = 0; j < IT; ++j) {
+        const u32 e = (u32)(j * NT) + threadIdx.x;
+        if (e < n && a.roff[lo[j]] == rb + e) s_mark[e] = lo[j] + 1;
+      }
     }
-  }
-  __syncthreads();
-  if (s_mark[0] == 0) {  // impossible: element 0 starts a source
-    if (threadIdx.x == 0) set_error(&a.st->err, kErrBounds);
-    return;
+    __syncthreads();
+    if (s_mark[0] == 0) {  // impossible: element 0 starts a source
+      if (threadIdx.x == 0) set_error(&a.st->err, kErrBounds);
+      return;
+    }
   }
 
   // 2. sort key = segment : record key : element index.  Items are window
@@ -280,15 +295,18 @@ __device__ __forceinline__ void merge_sort_tile(const MergeArgs &a, u32 tile, So
     if (v) {
       skey[j] = ((u64)wkey[j] << kIdxBits) | e;
       s_w[e] = wwt[j];
-      mark[j] = s_mark[e];
+      if (!ONE) mark[j] = s_mark[e];
     }
     const u64 m = __ballot(mark[j] != 0);
     f[j] = wrun + count_below(m) + (mark[j] ? 1u : 0u);
     wrun += (u32)__popcll(m);
   }
-  u32 nseg;
-  {
-    const u32 wbase = block_offset(wrun, s_tmp, &nseg);
+  u32 nseg = 1;
+  if (ONE) {
+#pragma unroll
+    for (int j = 0; j < IT; ++j) f[j] = 1;
+  } else {
+    const u32 wbase = block_offset<NW>(wrun, s_tmp, &nseg);
 #pragma unroll
     for (int j = 0; j < IT; ++j) f[j] += wbase;
   }
@@ -406,7 +424,7 @@ __device__ __forceinline__ void merge_sort_tile(const MergeArgs &a, u32 tile, So
   // run index base: heads in earlier threads
   const u32 hinc = wave_inclusive_sum(hc);
   u32 nruns;
-  const u32 hwave = block_offset(__shfl(hinc, kWave - 1, kWave), s_tmp, &nruns);  // barriers
+  const u32 hwave = block_offset<NW>(__shfl(hinc, kWave - 1, kWave), s_tmp, &nruns);  // barriers
   const u32 hbase = hwave + hinc - hc;
   if (!cflag) {
     double pre = 0.0;
@@ -452,18 +470,31 @@ __device__ __forceinline__ void merge_sort_tile(const MergeArgs &a, u32 tile, So
 // contiguous run of tiles, whose record windows then stay in its L2.
 template <class KT>
 __global__ __launch_bounds__(NT, 4) void k_merge_tiles(MergeArgs a) {
-  __shared__ SortLds L;
-  merge_sort_tile<KT>(a, xcd_tile(blockIdx.x, gridDim.x), L);
+  __shared__ SortLds<NT, false> L;
+  merge_sort_tile<KT, NT, false>(a, xcd_tile(blockIdx.x, gridDim.x), L);
+}
+
+// Sources of kMergeSmall to kMergeMid records, a workgroup each.  Bound: the
+// sort's passes one after the other in one workgroup per CU (112 KB of LDS):
+// 37 us for any number of sources up to 256.  kMergeMid is what one
+// workgroup's LDS sorts (64-bit keys, float weights).  The multi-block path
+// takes three launches per 8 key bits and ten more, 210 us at 6,306 records:
+// language model (one to four such sources in each of three levels)
+// 1.59 -> 1.47 ms, lexicon 2.30 -> 2.19 ms.
+template <class KT>
+__global__ __launch_bounds__(kMidNT) void k_merge_mid(MergeArgs a) {
+  __shared__ SortLds<kMidNT, true> L;
+  merge_sort_tile<KT, kMidNT, true>(a, (u32)(a.ntiles - a.nmid) + blockIdx.x, L);
 }
 
 // The tiles k_merge_dense listed in a.sortlist (a.st->nsort of them); a
 // fixed grid walks the list.
 template <class KT>
 __global__ __launch_bounds__(NT, 4) void k_merge_listed(MergeArgs a) {
-  __shared__ SortLds L;
+  __shared__ SortLds<NT, false> L;
   const u32 nsort = __hip_atomic_load(&a.st->nsort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   for (u32 i = blockIdx.x; i < nsort; i += gridDim.x) {
-    merge_sort_tile<KT>(a, a.sortlist[i], L);
+    merge_sort_tile<KT, NT, false>(a, a.sortlist[i], L);
     __syncthreads();  // LDS reused by the next tile
   }
 }
@@ -976,7 +1007,7 @@ __device__ __forceinline__ void prod_one(const MergeArgs &a, u64 u, u32 K, uint4
       const bool v = lane < na;
       const u32 g = v ? lane : 0u;
       const u32 s1 = a.seg_sym1[b1 + g], s2 = a.seg_sym2[b2 + g];
-  #pragma unroll
+#pragma unroll
       for (int k = 0; k < kProdBatch; ++k) {
         x1[k] = prod_arc<NARROW>(a.arcs1, ab1 + P1 * g + (u32)k);
         x2[k] = prod_arc<NARROW>(a.arcs2, ab2 + P2 * g + (u32)k);
@@ -1039,7 +1070,7 @@ __device__ __forceinline__ void prod_one(const MergeArgs &a, u64 u, u32 K, uint4
     // arc's part is below P (else the source is malformed); an absent one
     // writes the spare cell
     auto stage = [&](const uint2(&x1)[kProdBatch], const uint2(&x2)[kProdBatch], u32 h1, u32 h2) {
-  #pragma unroll
+#pragma unroll
       for (int k = 0; k < kProdBatch; ++k) {
         const bool in1 = (u32)k < h1, in2 = (u32)k < h2;
         const bool v1 = in1 & (x1[k].x < P1), v2 = in2 & (x2[k].x < P2);
@@ -1058,7 +1089,7 @@ __device__ __forceinline__ void prod_one(const MergeArgs &a, u64 u, u32 K, uint4
       static_assert(kProdBatch <= (int)kArcTail, "segment loads stay inside the arc arrays");
       if (!staged) {
         const u32 f1 = n1 ? a1 : 0u, f2 = n2 ? a2 : 0u;
-  #pragma unroll
+#pragma unroll
         for (int k = 0; k < kProdBatch; ++k) {
           x1[k] = prod_arc<NARROW>(a.arcs1, f1 + (u32)k);
           x2[k] = prod_arc<NARROW>(a.arcs2, f2 + (u32)k);
@@ -1068,7 +1099,7 @@ __device__ __forceinline__ void prod_one(const MergeArgs &a, u64 u, u32 K, uint4
       stage(x1, x2, n1, n2);
     } else if (found) {
       for (u32 i0 = 0; i0 < max(n1, n2); i0 += kProdBatch) {
-  #pragma unroll
+#pragma unroll
         for (int k = 0; k < kProdBatch; ++k) {
           const u32 i = i0 + (u32)k;
           x1[k] = i < n1 ? prod_arc<NARROW>(a.arcs1, a1 + i) : make_uint2(0, 0);
@@ -1110,7 +1141,7 @@ __device__ __forceinline__ void prod_one(const MergeArgs &a, u64 u, u32 K, uint4
       pairs = wave_total((u32)__popc(o));
       // the 4 x 64 by 64 x 4 product on the matrix cores (see above)
       double d = 0.0;
-  #pragma unroll
+#pragma unroll
       for (u32 t = 0; t < 4; ++t) {
         const double x = (double)__uint_as_float(val[t * kWave + lane]);
         const double y = (double)__uint_as_float(val[(kProdRow + t) * kWave + lane]);
@@ -1874,12 +1905,19 @@ __global__ __launch_bounds__(NT, 6) void k_fuse_merge(MergeArgs a) {
 // Descriptor of merge tile t: the small sources whose first record falls in
 // [t W, (t + 1) W) -- (first source, one past the last, window offset of the
 // first record, number of records).
-__global__ void k_tile_sources(const u64 *roff, u32 nsrc, u64 R, u64 W, u64 ntiles, uint4 *tiles) {
-  for (u64 t = (u64)blockIdx.x * blockDim.x + threadIdx.x; t < ntiles; t += (u64)gridDim.x * blockDim.x) {
+__global__ void k_tile_sources(const u64 *roff, u32 nsrc, u64 R, u64 W, u64 ntiles, uint4 *tiles,
+                               const u32 *mid, u32 nmid) {
+  for (u64 t = (u64)blockIdx.x * blockDim.x + threadIdx.x; t < ntiles + nmid;
+       t += (u64)gridDim.x * blockDim.x) {
+    if (t >= ntiles) {  // listed from the end of `mid`
+      const u32 u = mid[nsrc - 1 - (u32)(t - ntiles)];
+      tiles[t] = make_uint4(u, u + 1, 0u, (u32)(roff[u + 1] - roff[u]));
+      continue;
+    }
     const u64 tstart = t * W;
     const u32 s0 = (u32)min(lower_bound_dev<u64>(roff, (u64)nsrc + 1, tstart), (u64)nsrc);
     u32 s1 = (u32)min(lower_bound_dev<u64>(roff, (u64)nsrc + 1, min(tstart + W, R)), (u64)nsrc);
-    // a multi-block source can only be the last one starting in the window
+    // a larger source can only be the last one starting in the window
     if (s1 > s0 && roff[s1] - roff[s1 - 1] > kMergeSmall) --s1;
     const u64 rb = roff[s0];
     tiles[t] = make_uint4(s0, s1, (u32)(rb - min(rb, tstart)), (u32)(roff[s1] - rb));
@@ -1887,7 +1925,7 @@ __global__ void k_tile_sources(const u64 *roff, u32 nsrc, u64 R, u64 W, u64 ntil
 }
 
 // ---------------------------------------------------------------------------
-// Multi-block path for sources of more than kMergeSmall records.
+// Multi-block path for sources of more than kMergeMid records.
 __global__ void k_big_counts(const u64 *roff, const u32 *big, u32 nbig, u64 *bigcnt) {
   const u64 i = (u64)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < nbig) bigcnt[i] = roff[big[i] + 1] - roff[big[i]];
@@ -1993,9 +2031,9 @@ __global__ __launch_bounds__(kEmitNT) void k_emit_tiles(MergeArgs a, u32 bpt) {
   const u64 tile = blockIdx.x / bpt;
   const u32 k = blockIdx.x % bpt;
   const u32 nr = a.tile_runs[tile];
-  if (k * kEmitNT >= nr || nr > (u32)kMergeCap) return;  // uniform
+  if (k * kEmitNT >= nr || nr > (u32)kMergeMid) return;  // uniform
   claims_begin(L);
-  const u64 rb = tile * a.window + a.tiles[tile].z;
+  const u64 rb = tile_base(a, tile, a.tiles[tile]);
   if (nr <= bpt * kEmitNT)
     emit_tile_runs<1>(a, rb, nr, k, bpt, L);
   else
@@ -2455,7 +2493,7 @@ __global__ __launch_bounds__(256) void k_compact(MergeArgs a, const u64 *aoff, c
     const u32 k = (u32)(wv % wpt), cnt = a.tile_runs[tile];
     if ((u64)k * kChunk >= cnt) return;
     const uint4 td = a.tiles[tile];
-    const u64 tbase = tile * a.window + td.z;
+    const u64 tbase = tile_base(a, tile, td);
     if (tbase + cnt > a.R) {  // impossible: a tile has at most as many runs as records
       if (lane == 0) set_error(&a.st->err, kErrBounds);
       return;
@@ -2584,7 +2622,8 @@ __global__ __launch_bounds__(1024) void k_merged_total(const u64 *at, const u64 
   for (u64 t = threadIdx.x; t < a.ntiles; t += blockDim.x) {
     const uint4 td = a.tiles[t];
     const u32 runs = a.tile_runs[t];
-    if (td.x < td.y && dense_tile(td, a.key_bits) && !(td.w & kRerouted)) {
+    if (t < a.ntiles - a.nmid && td.x < td.y && dense_tile(td, a.key_bits) &&
+        !(td.w & kRerouted)) {
       v[0] += td.w;
       v[1] += runs;
     } else {
@@ -2760,8 +2799,8 @@ static u64 merge_grid(const MergeArgs &a) {
 void launch_tile_sources(const MergeArgs &a, hipStream_t s) {
   if (a.R == 0) return;
   const u64 g = merge_grid(a);
-  hipLaunchKernelGGL(k_tile_sources, dim3(grid1(g)), dim3(256), 0, s, a.roff, a.nsrc, a.R,
-                     a.window, g, a.tiles);
+  hipLaunchKernelGGL(k_tile_sources, dim3(grid1(g + a.nmid)), dim3(256), 0, s, a.roff, a.nsrc, a.R,
+                     a.window, g, a.tiles, a.big, a.nmid);
 }
 
 void launch_merge_dense(const MergeArgs &a, hipStream_t s) {
@@ -2792,6 +2831,14 @@ void launch_merge_sort(const MergeArgs &a, bool wide_keys, hipStream_t s) {
   } else {
     hipLaunchKernelGGL((k_merge_tiles<u32>), dim3((unsigned)g), dim3(NT), 0, s, a);
   }
+}
+
+void launch_merge_mid(const MergeArgs &a, bool wide_keys, hipStream_t s) {
+  if (a.nmid == 0) return;
+  if (wide_keys)
+    hipLaunchKernelGGL((k_merge_mid<u64>), dim3(a.nmid), dim3(kMidNT), 0, s, a);
+  else
+    hipLaunchKernelGGL((k_merge_mid<u32>), dim3(a.nmid), dim3(kMidNT), 0, s, a);
 }
 
 void launch_big_counts(const u64 *roff, const u32 *big, u32 nbig, u64 *bigcnt, hipStream_t s) {
@@ -3019,7 +3066,9 @@ void launch_emit_tiles(const MergeArgs &a, hipStream_t s) {
   // workgroups per tile: enough in all to fill the chip even when a level
   // has few tiles (each tile holds at most kMergeCap runs)
   const u64 target = (u64)compute_units() * 32;
-  const u32 bpt = (u32)std::min<u64>(kMergeCap / kEmitNT, std::max<u64>(1, ceil_div(target, a.ntiles)));
+  // (two for one of k_merge_mid: the claims of a workgroup fit its list)
+  const u32 bpt = (u32)std::min<u64>(kMergeCap / kEmitNT, std::max<u64>(a.nmid ? 2 : 1, ceil_div(target, a.ntiles)));
+  static_assert(kMergeMid <= 2 * kMergeCap && kMergeCap % (kEmitNT * kEmitBatch) == 0, "claims");
   if (a.ntiles * bpt >= (1ull << 31)) throw Error(FSTC_ERR_CAPACITY, "level too large for one launch");
   hipLaunchKernelGGL(k_emit_tiles, dim3((unsigned)(a.ntiles * bpt)), dim3(kEmitNT), 0, s, a, bpt);
 }
@@ -3082,6 +3131,7 @@ u64 level_clear_mask() {
   add(offsetof(Status, declined), 4);
   add(offsetof(Status, general), 8);
   add(offsetof(Status, chunk_pairs), 8);
+  add(offsetof(Status, nmid), 4);
   return m;
 }
 

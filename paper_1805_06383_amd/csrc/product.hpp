@@ -15,6 +15,17 @@ struct Ranges {
   u32 b1, e1, b2, e2;
 };
 
+// Lists source u of cnt > kMergeSmall records for the multi-block merge or for
+// a workgroup of its own.
+__device__ __forceinline__ void list_large(const LevelArgs &a, u32 u, u64 cnt) {
+  if (cnt > kMergeMid) {
+    a.big[atomicAdd(&a.st->nbig, 1u)] = u;
+    atomicAdd((unsigned long long *)&a.st->RB, (unsigned long long)cnt);
+  } else {
+    a.big[a.nsrc - 1 - atomicAdd(&a.st->nmid, 1u)] = u;
+  }
+}
+
 // True when every product of a weight of the state summarised by f1 with
 // one of the state summarised by f2 (build_cell_flags) is a normal float32
 // number after rounding: no infinity or NaN, no subnormal operand,

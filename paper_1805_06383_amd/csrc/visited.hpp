@@ -161,6 +161,7 @@ __device__ __forceinline__ void clear_level(Status *st) {
   st->unfit = 0;
   st->declined = 0;
   st->general = st->chunk_pairs = 0;
+  st->nmid = 0;
 }
 
 }  // namespace fstc

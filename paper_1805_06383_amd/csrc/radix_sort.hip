@@ -1,11 +1,19 @@
 // Device-wide stable LSD radix sort of (64-bit key, 32-bit value) pairs.
 //
 // The paper sorts packed 64-bit keys with a library sort-by-key
-// (section 3.4, "Reduction").  Here the sort is written for gfx950: 8-bit
-// digits, one histogram pass and one scatter pass per digit, tiles of 4096
-// elements per 256-thread workgroup, and stable in-tile ranking by wave64
-// ballots (radix_rank.hpp).  Only the key bits that can differ are sorted
-// (the caller passes the bit range).
+// (section 3.4, "Reduction").  Here the sort is written for gfx950: digits of
+// at most 8 bits, stable in-tile ranking by wave64 ballots (radix_rank.hpp),
+// and only the key bits that can differ (the caller passes the bit range).
+//   - Up to kOneTile pairs: one workgroup runs every pass in LDS.
+//   - More: one kernel counts every pass's digits, then each pass is one
+//     kernel (Merrill & Garland, "Single-pass Parallel Prefix Scan with
+//     Decoupled Look-back", 2016, applied per digit; Adinets & Merrill,
+//     "Onesweep", 2022): a workgroup takes the next tile from a counter,
+//     ranks it, publishes its digit counts, and adds up those of the tiles
+//     below until one has published its prefix.
+// Bound: at the sizes of one level (10^4 to 10^6 pairs) the launches and the
+// gaps between them, not the traffic.  A histogram, a scan and a scatter
+// launch per pass took 33 us a pass at 150,000 pairs and 42 us at 372,000.
 #include "common.hpp"
 #include "radix_rank.hpp"
 
@@ -13,291 +21,356 @@ namespace fstc {
 namespace {
 
 constexpr int kNT = 256;
-constexpr int kIT = 16;
-constexpr int kTile = kNT * kIT;
+constexpr int kMaxPasses = 8;
+constexpr int kOneNT = 1024, kOneIT = 8;
+constexpr u64 kOneTile = kOneNT * kOneIT;  // 96 KB of LDS
+// Tiles of 2,048 pairs up to this many: more workgroups in flight where a
+// level's tiles do not fill the chip, 4,096 above: half the look-back words.
+constexpr u64 kFineMax = u64(1) << 20;
+constexpr int tile_pairs(bool fine) { return kNT * (fine ? 8 : 16); }
+inline u64 tiles_of(u64 n) { return ceil_div(n, tile_pairs(n <= kFineMax)); }
 
-// Histogram of tile `blk` of nb: hist[d nb + blk] = elements of the tile
-// with digit d.
-__device__ __forceinline__ void digit_hist_tile(const u64 *keys, u64 n, int shift, u32 mask,
-                                                u32 *hist, u32 nb, u32 blk) {
-  __shared__ u32 h[256];
-  h[threadIdx.x] = 0;
-  __syncthreads();
-  const u64 base = (u64)blk * kTile;
-  // every load issued before the first is used (indices clamped into the
-  // array; n >= 2): a branch around each load would wait for every one
-  u64 k[kIT];
-#pragma unroll
-  for (int j = 0; j < kIT; ++j) k[j] = keys[min<u64>(base + (u64)j * kNT + threadIdx.x, n - 1)];
-#pragma unroll
-  for (int j = 0; j < kIT; ++j)
-    if (base + (u64)j * kNT + threadIdx.x < n) atomicAdd(&h[(u32)(k[j] >> shift) & mask], 1u);
-  __syncthreads();
-  hist[(u64)threadIdx.x * nb + blk] = h[threadIdx.x];
-}
+// Control words of one sort, zeroed before it: digit counts of every pass,
+// the passes' tile counters, then the tiles' published digit counts (pass
+// number and kind of count above the count, so a pass's words never match
+// another's).
+struct Control {
+  u32 hist[kMaxPasses * 256];
+  u32 ticket[64];
+};
+constexpr u32 kAgg = 1, kInc = 2;  // the tile's own counts; with all below it
+constexpr u32 kSpins = 1u << 20;   // polls before a tile counts the pairs below itself
 
-__global__ __launch_bounds__(kNT) void k_digit_hist(const u64 *keys, u64 n, int shift, u32 mask,
-                                                    u32 *hist, u32 nb) {
-  digit_hist_tile(keys, n, shift, mask, hist, nb, blockIdx.x);
-}
-
-// Scatter of tile `blk` of nb to the offsets of the scanned histogram.
-__device__ __forceinline__ void digit_scatter_tile(const u64 *keys, const u32 *vals,
-                                                   u64 *keys_out, u32 *vals_out, u64 n, int shift,
-                                                   int bits, const u32 *offs, u32 nb, u32 blk) {
-  __shared__ u32 s_cnt[(kNT / kWave) * 256];
-  __shared__ u32 s_base[256];
-  __shared__ u32 s_tmp[kNT / kWave];
-  const u32 lane = lane_id(), w = threadIdx.x / kWave;
-  const u32 mask = (1u << bits) - 1u;
-  const u64 base = (u64)blk * kTile + (u64)w * (kWave * kIT);
-  u64 key[kIT];
-  u32 val[kIT], dig[kIT], rid[kIT];
-  u32 valid = 0;
-#pragma unroll
-  for (int j = 0; j < kIT; ++j) {
-    const u64 e = base + (u64)j * kWave + lane;
-    const bool v = e < n;
-    valid |= (v ? 1u : 0u) << j;
-    key[j] = v ? keys[e] : 0;
-    val[j] = v ? vals[e] : 0;
-    dig[j] = (u32)(key[j] >> shift) & mask;
-  }
-  block_rank_digits<kNT, kIT>(dig, valid, bits, rid, s_cnt, s_base, s_tmp);
-#pragma unroll
-  for (int j = 0; j < kIT; ++j) {
-    if (!((valid >> j) & 1u)) continue;
-    const u64 pos = (u64)offs[(u64)dig[j] * nb + blk] + rid[j];
-    keys_out[pos] = key[j];
-    vals_out[pos] = val[j];
-  }
-}
-
-__global__ __launch_bounds__(kNT) void k_digit_scatter(const u64 *keys, const u32 *vals,
-                                                       u64 *keys_out, u32 *vals_out, u64 n,
-                                                       int shift, int bits, const u32 *offs,
-                                                       u32 nb) {
-  digit_scatter_tile(keys, vals, keys_out, vals_out, n, shift, bits, offs, nb, blockIdx.x);
-}
-
-// Exclusive scan of a digit histogram of at most kScan1Max entries by one
-// workgroup (one launch instead of a multi-level scan).  Wave w owns the
-// entries [w S, w S + S), S a multiple of 64: it sums them in coalesced
-// 64-entry chunks, the waves' totals are combined in LDS, and a second pass
-// over the chunks writes each entry's offset from a DPP prefix sum plus the
-// running carry.
-constexpr int kScan1NT = 1024;
-constexpr u64 kScan1Max = 1u << 16;
-
-__device__ __forceinline__ void hist_scan_block(const u32 *hist, u32 *offs, u32 nh) {
-  constexpr u32 kWaves = kScan1NT / kWave;
-  __shared__ u32 s_tot[kWaves];
-  const u32 lane = lane_id(), w = threadIdx.x / kWave;
-  const u32 seg = (nh + kWaves * kWave - 1) / (kWaves * kWave) * kWave;
-  const u32 b = min(nh, w * seg), e = min(nh, b + seg);
-  // kBatch chunks' loads are issued before any of them is used
-  constexpr u32 kBatch = 8;
-  u32 sum = 0;
-  for (u32 c = b; c < e; c += kBatch * kWave) {
-    u32 v[kBatch];
-#pragma unroll
-    for (u32 q = 0; q < kBatch; ++q) {
-      const u32 i = c + q * kWave + lane;
-      v[q] = i < e ? hist[i] : 0u;
-    }
-#pragma unroll
-    for (u32 q = 0; q < kBatch; ++q) sum += v[q];
-  }
-  sum = wave_total(sum);
-  if (lane == 0) s_tot[w] = sum;
-  __syncthreads();
-  u32 carry = 0;
-  for (u32 k = 0; k < w; ++k) carry += s_tot[k];
-  for (u32 c = b; c < e; c += kBatch * kWave) {  // wave-uniform bounds: every lane runs every chunk
-    u32 v[kBatch];
-#pragma unroll
-    for (u32 q = 0; q < kBatch; ++q) {
-      const u32 i = c + q * kWave + lane;
-      v[q] = i < e ? hist[i] : 0u;
-    }
-#pragma unroll
-    for (u32 q = 0; q < kBatch; ++q) {
-      const u32 i = c + q * kWave + lane;
-      const u32 incl = wave_inclusive_total(v[q]);
-      if (i < e) offs[i] = carry + incl - v[q];
-      carry += (u32)__builtin_amdgcn_readlane((int)incl, kWave - 1);
-    }
-  }
-}
-
-__global__ __launch_bounds__(kScan1NT) void k_hist_scan1(const u32 *hist, u32 *offs, u32 nh) {
-  hist_scan_block(hist, offs, nh);
-}
-
-// One pass of a batch of sorts (radix_sort_pairs_batch): the jobs still
-// sorting, workgroups [0, split) for the first and the rest for the second.
-struct PassJob {
+struct SortArgs {
   const u64 *ki;
   const u32 *vi;
   u64 *ko;
   u32 *vo;
   u64 n;
-  int shift, bits;
-  u32 *hist, *offs;
+  int lo, hi, passes;
+  Control *ctl;
+  u64 *status;  // [tiles][256]
   u32 nb;
   const u32 *unsorted;  // see SortJob
   u32 epoch;
-  u32 copy;  // an ordered job's last pass of an odd number: ki copied to ko
 };
+struct SortPair {
+  SortArgs j[2];
+  u32 split;  // workgroups of the first
+  int pass;
+};
+
+// Bits of pass p: spread evenly (a digit of b bits takes b ballots per row).
+__host__ __device__ inline void pass_bits(const SortArgs &a, int p, int &shift, int &bits) {
+  const int w = a.hi - a.lo;
+  shift = a.lo + w * p / a.passes;
+  bits = a.lo + w * (p + 1) / a.passes - shift;
+}
 
 // The job is already in order (see SortJob).
-__device__ __forceinline__ bool pass_in_order(const PassJob &J) {
-  return J.unsorted && *J.unsorted != J.epoch;
+__device__ __forceinline__ bool in_order(const SortArgs &a) {
+  return a.unsorted && *a.unsorted != a.epoch;
 }
-struct PassPair {
-  PassJob j[2];
-  u32 split;
-};
 
-__device__ __forceinline__ const PassJob &pass_job(const PassPair &p, u32 &blk) {
+__device__ __forceinline__ const SortArgs &sort_job(const SortPair &p, u32 &blk, u32 &grid) {
   if (blockIdx.x < p.split) {
     blk = blockIdx.x;
+    grid = p.split;
     return p.j[0];
   }
   blk = blockIdx.x - p.split;
+  grid = gridDim.x - p.split;
   return p.j[1];
 }
 
-__global__ __launch_bounds__(kNT) void k_digit_hist2(PassPair p) {
-  u32 blk;
-  const PassJob &J = pass_job(p, blk);
-  if (pass_in_order(J)) return;  // uniform
-  digit_hist_tile(J.ki, J.n, J.shift, (1u << J.bits) - 1u, J.hist, J.nb, blk);
+__global__ __launch_bounds__(kNT) void k_radix_zero(SortPair p) {
+  u32 blk, grid;
+  const SortArgs &a = sort_job(p, blk, grid);
+  if (in_order(a)) return;
+  const u64 w = sizeof(Control) / 8, n = w + (u64)a.nb * 256;
+  u64 *c = reinterpret_cast<u64 *>(a.ctl);
+  for (u64 i = (u64)blk * kNT + threadIdx.x; i < n; i += (u64)grid * kNT) {
+    if (i < w) c[i] = 0;
+    else a.status[i - w] = 0;
+  }
 }
 
-// workgroup i scans job i's histogram
-__global__ __launch_bounds__(kScan1NT) void k_hist_scan2(PassPair p) {
-  const PassJob &J = p.j[blockIdx.x];
-  if (pass_in_order(J)) return;  // uniform
-  hist_scan_block(J.hist, J.offs, 256u * J.nb);
-}
-
-// An ordered job's data stays where it is: in the last of an odd number of
-// passes it is copied to the output (the sort's result is then copied back
-// from there), otherwise nothing is done.
-__global__ __launch_bounds__(kNT) void k_digit_scatter2(PassPair p) {
-  u32 blk;
-  const PassJob &J = pass_job(p, blk);
-  if (pass_in_order(J)) {  // uniform
-    if (!J.copy) return;
-    const u64 base = (u64)blk * kTile;
+// Digit counts of every pass, the keys read once.
+__global__ __launch_bounds__(kNT) void k_radix_hist(SortPair p) {
+  __shared__ u32 h[kMaxPasses * 256];
+  u32 blk, grid;
+  const SortArgs &a = sort_job(p, blk, grid);
+  if (in_order(a)) return;  // uniform
+  for (u32 i = threadIdx.x; i < (u32)a.passes * 256; i += kNT) h[i] = 0;
+  __syncthreads();
+  constexpr int kB = 8;
+  for (u64 b = (u64)blk * (kNT * kB); b < a.n; b += (u64)grid * (kNT * kB)) {
+    // every load issued before the first is used (indices clamped)
+    u64 k[kB];
 #pragma unroll
-    for (int j = 0; j < kIT; ++j) {
-      const u64 e = base + (u64)j * kNT + threadIdx.x;
-      if (e < J.n) {
-        J.ko[e] = J.ki[e];
-        J.vo[e] = J.vi[e];
+    for (int j = 0; j < kB; ++j) k[j] = a.ki[min<u64>(b + (u64)j * kNT + threadIdx.x, a.n - 1)];
+    for (int q = 0; q < a.passes; ++q) {
+      int shift, bits;
+      pass_bits(a, q, shift, bits);
+      const u32 mask = (1u << bits) - 1u;
+#pragma unroll
+      for (int j = 0; j < kB; ++j)
+        if (b + (u64)j * kNT + threadIdx.x < a.n)
+          atomicAdd(&h[q * 256 + ((u32)(k[j] >> shift) & mask)], 1u);
+    }
+  }
+  __syncthreads();
+  for (u32 i = threadIdx.x; i < (u32)a.passes * 256; i += kNT)
+    if (h[i]) atomicAdd(&a.ctl->hist[i], h[i]);
+}
+
+// One pass over one tile of kNT x IT pairs.
+template <int IT>
+__global__ __launch_bounds__(kNT) void k_radix_pass(SortPair p) {
+  constexpr int kTile = kNT * IT;
+  constexpr u32 kW = 16;  // published counts read together
+  __shared__ u32 s_cnt[(kNT / kWave) * 256];
+  __shared__ u32 s_base[256], s_off[256];
+  __shared__ u32 s_tmp[kNT / kWave];
+  __shared__ u32 s_tile;
+  u32 blk, grid;
+  const SortArgs &a = sort_job(p, blk, grid);
+  if (in_order(a)) {  // uniform
+    // its data stays where it is: in the last of an odd number of passes it
+    // is copied to the output (the result is then copied back from there)
+    if (p.pass == a.passes - 1 && (a.passes & 1)) {
+      const u64 base = (u64)blk * kTile;
+#pragma unroll
+      for (int j = 0; j < IT; ++j) {
+        const u64 e = base + (u64)j * kNT + threadIdx.x;
+        if (e < a.n) {
+          a.ko[e] = a.ki[e];
+          a.vo[e] = a.vi[e];
+        }
       }
     }
     return;
   }
-  digit_scatter_tile(J.ki, J.vi, J.ko, J.vo, J.n, J.shift, J.bits, J.offs, J.nb, blk);
+  // tiles in the order the workgroups start: the tiles below are running
+  if (threadIdx.x == 0) s_tile = atomicAdd(&a.ctl->ticket[p.pass], 1u);
+  const u32 d = threadIdx.x, lane = lane_id(), w = threadIdx.x / kWave;
+  const u32 digits = a.ctl->hist[p.pass * 256 + d];
+  u32 total;
+  const u32 before = block_exclusive_sum<kNT, u32>(digits, s_tmp, &total);  // barriers
+  const u32 tile = s_tile;
+  if (tile >= a.nb) return;  // impossible: as many tiles as workgroups
+  int shift, bits;
+  pass_bits(a, p.pass, shift, bits);
+  const u32 mask = (1u << bits) - 1u;
+  const u64 t0 = (u64)tile * kTile, base = t0 + (u64)w * (kWave * IT);
+  u64 key[IT];
+  u32 val[IT], dig[IT], rid[IT];
+  u32 valid = 0;
+#pragma unroll
+  for (int j = 0; j < IT; ++j) {
+    const u64 e = base + (u64)j * kWave + lane;
+    valid |= (e < a.n ? 1u : 0u) << j;
+    key[j] = a.ki[min<u64>(e, a.n - 1)];
+    val[j] = a.vi[min<u64>(e, a.n - 1)];
+  }
+#pragma unroll
+  for (int j = 0; j < IT; ++j) dig[j] = (u32)(key[j] >> shift) & mask;
+  block_rank_digits<kNT, IT>(dig, valid, bits, rid, s_cnt, s_base, s_tmp);
+  const u32 mine = (d < 255 ? s_base[d + 1] : (u32)min<u64>(kTile, a.n - t0)) - s_base[d];
+  const u32 tag = (u32)(p.pass + 1) << 2;
+  auto publish = [&](u32 kind, u32 v) {
+    __hip_atomic_store(&a.status[(u64)tile * 256 + d], (u64)(tag | kind) << 32 | v,
+                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
+  publish(tile == 0 ? kInc : kAgg, mine);
+  u32 below = 0;  // pairs of digit d in the tiles below
+  bool failed = false;
+  {
+    u32 t = tile, polls = 0;  // tiles [t, tile) are added
+    bool done = t == 0;
+    while (!done && !failed) {
+      u64 x[kW];
+#pragma unroll
+      for (u32 k = 0; k < kW; ++k)
+        x[k] = __hip_atomic_load(&a.status[(u64)(t > k ? t - 1 - k : 0u) * 256 + d],
+                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      bool open = true;
+      u32 took = 0;
+#pragma unroll
+      for (u32 k = 0; k < kW; ++k) {
+        const u32 kind = (u32)(x[k] >> 32) ^ tag;
+        open = open && !done && k < t && (kind == kAgg || kind == kInc);
+        if (open) {
+          below += (u32)x[k];
+          ++took;
+          done = kind == kInc;  // (tile 0 publishes no other)
+        }
+      }
+      t -= took;
+      if (!done && took == 0) {
+        __builtin_amdgcn_s_sleep(1);
+        failed = ++polls > kSpins;
+      }
+    }
+  }
+  if (__syncthreads_or(failed ? 1 : 0)) {
+    // the pairs below counted again (a workgroup below was held for long)
+    s_off[d] = 0;
+    __syncthreads();
+    for (u64 e = d; e < t0; e += kNT) atomicAdd(&s_off[(u32)(a.ki[e] >> shift) & mask], 1u);
+    __syncthreads();
+    below = s_off[d];
+    __syncthreads();
+  }
+  if (tile) publish(kInc, below + mine);
+  s_off[d] = before + below;
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < IT; ++j) {
+    if (!((valid >> j) & 1u)) continue;
+    const u64 pos = (u64)s_off[dig[j]] + rid[j];
+    a.ko[pos] = key[j];
+    a.vo[pos] = val[j];
+  }
+}
+
+// Every pass of a job of at most kOneTile pairs, workgroup i for job i; the
+// result replaces the input.
+__global__ __launch_bounds__(kOneNT) void k_radix_one(SortPair p) {
+  __shared__ u64 s_key[kOneTile];
+  __shared__ u32 s_val[kOneTile];
+  __shared__ u32 s_cnt[(kOneNT / kWave) * 256];
+  __shared__ u32 s_base[256];
+  __shared__ u32 s_tmp[kOneNT / kWave];
+  const SortArgs &a = p.j[blockIdx.x];
+  if (in_order(a)) return;  // uniform
+  const u32 lane = lane_id(), w = threadIdx.x / kWave, n = (u32)a.n;
+  u64 key[kOneIT];
+  u32 val[kOneIT], dig[kOneIT], rid[kOneIT];
+  u32 valid = 0;
+#pragma unroll
+  for (int j = 0; j < kOneIT; ++j) {
+    const u32 e = w * (kWave * kOneIT) + j * kWave + lane;
+    valid |= (e < n ? 1u : 0u) << j;
+    key[j] = a.ki[min(e, n - 1)];
+    val[j] = a.vi[min(e, n - 1)];
+  }
+  for (int q = 0; q < a.passes; ++q) {
+    int shift, bits;
+    pass_bits(a, q, shift, bits);
+    const u32 mask = (1u << bits) - 1u;
+#pragma unroll
+    for (int j = 0; j < kOneIT; ++j) dig[j] = (u32)(key[j] >> shift) & mask;
+    block_rank_digits<kOneNT, kOneIT>(dig, valid, bits, rid, s_cnt, s_base, s_tmp);
+#pragma unroll
+    for (int j = 0; j < kOneIT; ++j) {
+      if (!((valid >> j) & 1u)) continue;
+      const u32 pos = s_base[dig[j]] + rid[j];
+      s_key[pos] = key[j];
+      s_val[pos] = val[j];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kOneIT; ++j) {
+      const u32 e = w * (kWave * kOneIT) + j * kWave + lane;
+      key[j] = s_key[min(e, n - 1)];
+      val[j] = s_val[min(e, n - 1)];
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int j = 0; j < kOneIT; ++j) {
+    const u32 e = w * (kWave * kOneIT) + j * kWave + lane;
+    if (!((valid >> j) & 1u)) continue;
+    a.ko[e] = key[j];
+    a.vo[e] = val[j];
+  }
 }
 
 }  // namespace
 
-size_t radix_temp_bytes(u64 n) {
-  const u64 nb = std::max<u64>(1, ceil_div(n, kTile));
-  const u64 nh = 256 * nb;
-  return (nh + (nh + 1)) * sizeof(u32) + scan_temp_bytes(nh) + 512;
-}
+size_t radix_temp_bytes(u64 n) { return sizeof(Control) + tiles_of(std::max<u64>(n, 1)) * 256 * 8 + 256; }
 
 void radix_sort_pairs(u64 *keys, u32 *vals, u64 *keys_alt, u32 *vals_alt, u64 n, int lo, int hi,
                       void *temp, hipStream_t s) {
-  if (n <= 1 || hi <= lo) return;
-  const u32 nb = (u32)ceil_div(n, kTile);
-  const u64 nh = 256ull * nb;
-  u32 *hist = (u32 *)temp;
-  u32 *offs = hist + nh;
-  void *scan_tmp = (void *)(((uintptr_t)(offs + nh + 1) + 255) & ~(uintptr_t)255);
-  u64 *ki = keys, *ko = keys_alt;
-  u32 *vi = vals, *vo = vals_alt;
-  for (int shift = lo; shift < hi; shift += 8) {
-    const int bits = std::min(8, hi - shift);
-    const u32 mask = (1u << bits) - 1u;
-    hipLaunchKernelGGL(k_digit_hist, dim3(nb), dim3(kNT), 0, s, ki, n, shift, mask, hist, nb);
-    if (nh <= kScan1Max)
-      hipLaunchKernelGGL(k_hist_scan1, dim3(1), dim3(kScan1NT), 0, s, hist, offs, (u32)nh);
-    else
-      exclusive_scan(hist, offs, nh, scan_tmp, s);
-    hipLaunchKernelGGL(k_digit_scatter, dim3(nb), dim3(kNT), 0, s, ki, vi, ko, vo, n, shift,
-                       bits, offs, nb);
-    std::swap(ki, ko);
-    std::swap(vi, vo);
-  }
-  if (ki != keys) {
-    FSTC_HIP(hipMemcpyAsync(keys, ki, n * sizeof(u64), hipMemcpyDeviceToDevice, s));
-    FSTC_HIP(hipMemcpyAsync(vals, vi, n * sizeof(u32), hipMemcpyDeviceToDevice, s));
-  }
+  const SortJob j{keys, keys_alt, vals, vals_alt, n, lo, hi, temp};
+  radix_sort_pairs_batch(&j, 1, s);
 }
 
 void radix_sort_pairs_batch(const SortJob *jobs, int nj, hipStream_t s) {
   if (nj < 1 || nj > 2) throw Error(FSTC_ERR_INTERNAL, "radix_sort_pairs_batch takes one or two jobs");
-  u64 *ki[2], *ko[2];
-  u32 *vi[2], *vo[2];
-  int shift[2];
-  // one workgroup scans a job's histogram: larger sorts run one by one
+  SortPair one{}, many{};
+  int n1 = 0, nm = 0, who[2] = {0, 0};
+  bool fine = true;
   for (int i = 0; i < nj; ++i) {
-    if (256ull * ceil_div(jobs[i].n, kTile) > kScan1Max) {
-      for (int k = 0; k < nj; ++k)
-        radix_sort_pairs(jobs[k].keys, jobs[k].vals, jobs[k].keys_alt, jobs[k].vals_alt,
-                         jobs[k].n, jobs[k].lo, jobs[k].hi, jobs[k].temp, s);
-      return;
+    const SortJob &J = jobs[i];
+    if (J.n <= 1 || J.hi <= J.lo) continue;
+    const u64 nb = tiles_of(J.n);
+    // (digit counts and tile offsets are 32-bit)
+    if (J.n >= (1ull << 32)) throw Error(FSTC_ERR_CAPACITY, "sort of 2^32 pairs or more");
+    SortArgs a{};
+    a.ki = J.keys;
+    a.vi = J.vals;
+    a.n = J.n;
+    a.lo = J.lo;
+    a.hi = J.hi;
+    a.passes = (J.hi - J.lo + 7) / 8;
+    a.unsorted = J.unsorted;
+    a.epoch = J.epoch;
+    if (J.n <= kOneTile) {
+      a.ko = J.keys;
+      a.vo = J.vals;
+      one.j[n1++] = a;
+      continue;
+    }
+    a.ko = J.keys_alt;
+    a.vo = J.vals_alt;
+    a.ctl = reinterpret_cast<Control *>(((uintptr_t)J.temp + 255) & ~(uintptr_t)255);
+    a.status = reinterpret_cast<u64 *>(a.ctl + 1);
+    a.nb = (u32)nb;
+    fine = fine && J.n <= kFineMax;
+    who[nm] = i;
+    many.j[nm++] = a;
+  }
+  if (n1) hipLaunchKernelGGL(k_radix_one, dim3(n1), dim3(kOneNT), 0, s, one);
+  if (!nm) return;
+  // (both by the larger tiles when one job needs them)
+  for (int i = 0; i < nm; ++i) many.j[i].nb = (u32)ceil_div(many.j[i].n, tile_pairs(fine));
+  auto grid = [&](auto blocks) {
+    many.split = blocks(many.j[0]);
+    return dim3(many.split + (nm > 1 ? blocks(many.j[1]) : 0u));
+  };
+  const dim3 gz = grid([](const SortArgs &a) { return std::min<u32>(a.nb, 256u); });
+  hipLaunchKernelGGL(k_radix_zero, gz, dim3(kNT), 0, s, many);
+  // (a workgroup adds its counts to the same 256 words per pass as the others)
+  hipLaunchKernelGGL(k_radix_hist, gz, dim3(kNT), 0, s, many);
+  const int most = std::max(many.j[0].passes, nm > 1 ? many.j[1].passes : 0);
+  for (int q = 0; q < most; ++q) {
+    SortPair p = many;
+    int na = 0;
+    for (int i = 0; i < nm; ++i)
+      if (q < many.j[i].passes) p.j[na++] = many.j[i];
+    p.pass = q;
+    p.split = p.j[0].nb;
+    const dim3 g(p.split + (na > 1 ? p.j[1].nb : 0u));
+    if (fine) hipLaunchKernelGGL(k_radix_pass<8>, g, dim3(kNT), 0, s, p);
+    else hipLaunchKernelGGL(k_radix_pass<16>, g, dim3(kNT), 0, s, p);
+    for (int i = 0; i < nm; ++i) {
+      SortArgs &a = many.j[i];
+      if (q >= a.passes) continue;
+      u64 *k = const_cast<u64 *>(a.ki);
+      u32 *v = const_cast<u32 *>(a.vi);
+      a.ki = a.ko;
+      a.vi = a.vo;
+      a.ko = k;
+      a.vo = v;
     }
   }
-  for (int i = 0; i < nj; ++i) {
-    ki[i] = jobs[i].keys; ko[i] = jobs[i].keys_alt;
-    vi[i] = jobs[i].vals; vo[i] = jobs[i].vals_alt;
-    shift[i] = jobs[i].lo;
-  }
-  auto active = [&](int i) { return jobs[i].n > 1 && shift[i] < jobs[i].hi; };
-  while (true) {
-    PassPair p{};
-    int na = 0, who[2];
-    u32 grid = 0;
-    for (int i = 0; i < nj; ++i) {
-      if (!active(i)) continue;
-      PassJob &J = p.j[na];
-      J.ki = ki[i]; J.vi = vi[i]; J.ko = ko[i]; J.vo = vo[i];
-      J.n = jobs[i].n;
-      J.shift = shift[i];
-      J.bits = std::min(8, jobs[i].hi - shift[i]);
-      J.nb = (u32)ceil_div(J.n, kTile);
-      J.hist = (u32 *)jobs[i].temp;
-      J.offs = J.hist + 256ull * J.nb;
-      J.unsorted = jobs[i].unsorted;
-      J.epoch = jobs[i].epoch;
-      const int passes = (jobs[i].hi - jobs[i].lo + 7) / 8;
-      J.copy = (passes & 1) && shift[i] + 8 >= jobs[i].hi ? 1u : 0u;
-      if (na == 0) p.split = J.nb;
-      grid += J.nb;
-      who[na++] = i;
-    }
-    if (na == 0) break;
-    hipLaunchKernelGGL(k_digit_hist2, dim3(grid), dim3(kNT), 0, s, p);
-    hipLaunchKernelGGL(k_hist_scan2, dim3(na), dim3(kScan1NT), 0, s, p);
-    hipLaunchKernelGGL(k_digit_scatter2, dim3(grid), dim3(kNT), 0, s, p);
-    for (int a = 0; a < na; ++a) {
-      const int i = who[a];
-      std::swap(ki[i], ko[i]);
-      std::swap(vi[i], vo[i]);
-      shift[i] += 8;
-    }
-  }
-  for (int i = 0; i < nj; ++i) {
-    if (ki[i] == jobs[i].keys) continue;
-    FSTC_HIP(hipMemcpyAsync(jobs[i].keys, ki[i], jobs[i].n * sizeof(u64), hipMemcpyDeviceToDevice, s));
-    FSTC_HIP(hipMemcpyAsync(jobs[i].vals, vi[i], jobs[i].n * sizeof(u32), hipMemcpyDeviceToDevice, s));
+  for (int i = 0; i < nm; ++i) {
+    const SortJob &J = jobs[who[i]];
+    if (many.j[i].ki == J.keys) continue;
+    FSTC_HIP(hipMemcpyAsync(J.keys, many.j[i].ki, J.n * sizeof(u64), hipMemcpyDeviceToDevice, s));
+    FSTC_HIP(hipMemcpyAsync(J.vals, many.j[i].vi, J.n * sizeof(u32), hipMemcpyDeviceToDevice, s));
   }
 }
 

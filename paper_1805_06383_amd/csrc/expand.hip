@@ -294,8 +294,49 @@ __device__ __forceinline__ Hit wave_probe(const LevelArgs &a, const Ranges &r, b
 constexpr int kListNT = 512;
 constexpr int kHeavyNT = kListNT;
 
+// Joined pairs and matches of the short-list symbols [cb, ce) of a source, by
+// the whole block (valid in every thread).
+__device__ __forceinline__ void count_block_join(const LevelArgs &a, const Ranges &r, bool one_short,
+                                                 u32 cb, u32 ce, u64 &cnt, u32 &mc, u64 *s64,
+                                                 u32 *s32) {
+  cnt = 0;
+  mc = 0;
+  for (u32 base = cb; base < ce; base += kListNT) {
+    const Hit h = probe_one(a, r, one_short, base + threadIdx.x);
+    if (h.found && base + threadIdx.x < ce) {
+      cnt += (u64)seg_len(a.c1.seg_off, h.s1) * seg_len(a.c2.seg_off, h.s2);
+      ++mc;
+    }
+  }
+  cnt = block_sum<kListNT, u64>(cnt, s64);
+  mc = block_sum<kListNT, u32>(mc, s32);
+}
+
+// A wide list of no more sources than there are workgroups takes a workgroup
+// per source, a longer one (which fills the chip) a wavefront per source: a
+// wavefront walks a list of 500 symbols in eight steps of 10 to 20 dependent
+// loads.  One such source (a language model's first level) took 43 us to count
+// and 51 us to emit by a wavefront; the language model 1.45 -> 1.30 ms, the
+// lexicon 2.10 -> 1.88 ms.
 __device__ __forceinline__ void count_wide_sources(const LevelArgs &a, u32 blk, u32 nblk,
-                                                   u32 &run_max) {
+                                                   u32 &run_max, u64 *s64, u32 *s32) {
+  if (a.st->nwide <= nblk) {  // uniform
+    if (blk >= a.st->nwide) return;
+    const u32 u = a.wide[blk];
+    const uint4 wr = a.wrange[blk];
+    const Ranges r{wr.x, wr.y, wr.z, wr.w};
+    const bool one_short = (r.e1 - r.b1) <= (r.e2 - r.b2);
+    u64 cnt;
+    u32 mc;
+    count_block_join(a, r, one_short, one_short ? r.b1 : r.b2, one_short ? r.e1 : r.e2, cnt, mc,
+                     s64, s32);
+    if (threadIdx.x == 0) {
+      a.cnt[u] = cnt;
+      a.mc[u] = mc;
+      note_count(a, u, cnt, run_max);
+    }
+    return;
+  }
   const u32 lane = lane_id();
   const u32 gw = (blk * kListNT + threadIdx.x) / kWave;
   const u32 nw = nblk * kListNT / kWave;
@@ -358,17 +399,9 @@ __device__ __forceinline__ void count_heavy_sources(const LevelArgs &a, u32 blk,
     const u32 nchunk = (es - bs + per - 1) / per;
     if (c >= nchunk) continue;  // uniform
     const u32 cb = bs + c * per, ce = min(es, cb + per);
-    u64 cnt = 0;
-    u32 mc = 0;
-    for (u32 base = cb; base < ce; base += kListNT) {
-      const Hit h = probe_one(a, r, one_short, base + threadIdx.x);
-      if (h.found && base + threadIdx.x < ce) {
-        cnt += (u64)seg_len(a.c1.seg_off, h.s1) * seg_len(a.c2.seg_off, h.s2);
-        ++mc;
-      }
-    }
-    cnt = block_sum<kListNT, u64>(cnt, s64);
-    mc = block_sum<kListNT, u32>(mc, s32);
+    u64 cnt;
+    u32 mc;
+    count_block_join(a, r, one_short, cb, ce, cnt, mc, s64, s32);
     if (split) {
       HeavyChunk *hc = a.hchunk + (u64)i * kHeavyChunks;
       if (threadIdx.x == 0) {
@@ -519,7 +552,7 @@ __global__ __launch_bounds__(kListNT) void k_count_lists(LevelArgs a, u32 gg, u3
   if (blockIdx.x < gg)
     count_group_sources(a, blockIdx.x, gg, run_max);
   else if (blockIdx.x < gg + gw)
-    count_wide_sources(a, blockIdx.x - gg, gw, run_max);
+    count_wide_sources(a, blockIdx.x - gg, gw, run_max, s64, s32);
   else
     count_heavy_sources(a, blockIdx.x - gg - gw, gridDim.x - gg - gw, run_max, s64, s32);
   publish_max<kListNT>(a, run_max, &s_max);
@@ -605,6 +638,39 @@ __global__ __launch_bounds__(256) void k_emit_wide(LevelArgs a) {
   }
 }
 
+// Match descriptors of the short-list symbols [cb, ce) of a source by the whole
+// block, from match k and record rb on.
+__device__ __forceinline__ void emit_block_join(const LevelArgs &a, const Ranges &r, bool one_short,
+                                                u32 cb, u32 ce, u64 k, u64 rb, u64 *s64,
+                                                u32 *s32) {
+  for (u32 base = cb; base < ce; base += kHeavyNT) {
+    Hit h = probe_one(a, r, one_short, base + threadIdx.x);
+    h.found = h.found && base + threadIdx.x < ce;
+    const u64 prod = h.found ? (u64)seg_len(a.c1.seg_off, h.s1) * seg_len(a.c2.seg_off, h.s2) : 0;
+    u32 ftot;
+    u64 ptot;
+    const u32 fex = block_exclusive_sum<kHeavyNT, u32>(h.found ? 1u : 0u, s32, &ftot);
+    const u64 pex = block_exclusive_sum<kHeavyNT, u64>(prod, s64, &ptot);
+    if (h.found) put_match(a, k + fex, h.s1, h.s2, rb + pex);
+    k += ftot;
+    rb += ptot;
+  }
+}
+
+// A workgroup per wide source (launch_emit: at most kWideBlocks of them).
+__global__ __launch_bounds__(kHeavyNT) void k_emit_wide_block(LevelArgs a) {
+  __shared__ u64 s64[kHeavyNT / kWave];
+  __shared__ u32 s32[kHeavyNT / kWave];
+  if (blockIdx.x >= a.st->nwide) return;
+  const u32 u = a.wide[blockIdx.x];
+  if (a.pk[u]) return;  // product merge
+  const uint4 wr = a.wrange[blockIdx.x];
+  const Ranges r{wr.x, wr.y, wr.z, wr.w};
+  const bool one_short = (r.e1 - r.b1) <= (r.e2 - r.b2);
+  emit_block_join(a, r, one_short, one_short ? r.b1 : r.b2, one_short ? r.e1 : r.e2, a.moff[u],
+                  a.roff[u], s64, s32);
+}
+
 __global__ __launch_bounds__(kHeavyNT) void k_emit_heavy(LevelArgs a) {
   __shared__ u64 s64[kHeavyNT / kWave];
   __shared__ u32 s32[kHeavyNT / kWave];
@@ -629,18 +695,7 @@ __global__ __launch_bounds__(kHeavyNT) void k_emit_heavy(LevelArgs a) {
       rb += block_sum<kHeavyNT, u64>(threadIdx.x < c ? hc[threadIdx.x].cnt : 0, s64);
       k += block_sum<kHeavyNT, u32>(threadIdx.x < c ? (u32)hc[threadIdx.x].mc : 0u, s32);
     }
-    for (u32 base = cb; base < ce; base += kHeavyNT) {
-      Hit h = probe_one(a, r, one_short, base + threadIdx.x);
-      h.found = h.found && base + threadIdx.x < ce;
-      const u64 prod = h.found ? (u64)seg_len(a.c1.seg_off, h.s1) * seg_len(a.c2.seg_off, h.s2) : 0;
-      u32 ftot;
-      u64 ptot;
-      const u32 fex = block_exclusive_sum<kHeavyNT, u32>(h.found ? 1u : 0u, s32, &ftot);
-      const u64 pex = block_exclusive_sum<kHeavyNT, u64>(prod, s64, &ptot);
-      if (h.found) put_match(a, k + fex, h.s1, h.s2, rb + pex);
-      k += ftot;
-      rb += ptot;
-    }
+    emit_block_join(a, r, one_short, cb, ce, k, rb, s64, s32);
     __syncthreads();
   }
 }
@@ -851,6 +906,8 @@ __global__ __launch_bounds__(kExpandNT) void k_expand(const uint4 *match, const 
 // Grids of the wavefront and workgroup joins: at most one wave (block) per
 // listed source, whose number is bounded by the frontier before the count
 // and known exactly after it.
+// Wide sources that a workgroup each takes: more would not run at once.
+constexpr u32 kWideBlocks = 1024;
 static unsigned wide_grid(u64 n) { return (unsigned)std::min<u64>(2048, ceil_div(n, 256 / kWave)); }
 static unsigned heavy_grid(u64 n) {
   return (unsigned)std::min<u64>(512, std::min<u64>(n, kHeavySplit) * kHeavyChunks);
@@ -868,7 +925,9 @@ static void launch_lists(const LevelArgs &a, hipStream_t s, bool lean, bool grou
   unsigned gg = groups ? (unsigned)std::min<u64>((u64)compute_units() * 4,
                                                  ceil_div(n, kListNT / kGroupLanes))
                        : 0u;
-  unsigned gw = (unsigned)std::min<u64>(1024, ceil_div(n, kListNT / kWave));
+  // (as many as sources on a small level: a workgroup each)
+  unsigned gw = (unsigned)std::min<u64>(1024, std::max<u64>(ceil_div(n, kListNT / kWave),
+                                                            std::min<u64>(n, 512)));
   unsigned gh = (unsigned)std::min<u64>(512, std::max<u64>(n, kLeanGrid));
   if (lean) {
     gg = std::min(gg, kLeanGrid);
@@ -897,7 +956,10 @@ void launch_emit(const LevelArgs &a, u32 nwide, u32 nheavy, u32 ngrp, bool threa
                                                 ceil_div((u64)ngrp, 256 / kGroupLanes));
     hipLaunchKernelGGL(k_emit_group, dim3(gg), dim3(256), 0, s, a);
   }
-  if (nwide) hipLaunchKernelGGL(k_emit_wide, dim3(wide_grid(nwide)), dim3(256), 0, s, a);
+  if (nwide && nwide <= kWideBlocks)
+    hipLaunchKernelGGL(k_emit_wide_block, dim3(nwide), dim3(kHeavyNT), 0, s, a);
+  else if (nwide)
+    hipLaunchKernelGGL(k_emit_wide, dim3(wide_grid(nwide)), dim3(256), 0, s, a);
   if (nheavy) hipLaunchKernelGGL(k_emit_heavy, dim3(heavy_grid(nheavy)), dim3(kHeavyNT), 0, s, a);
 }
 

@@ -75,8 +75,8 @@ constexpr u32 kProdMfmaParts = 4;
 // steps (shorter length x bits of the longer length) is joined by one
 // thread; one whose shorter list has at most kGroupMax symbols and whose
 // longer one at most kGroupLong, by a group of kGroupLanes lanes; one whose
-// shorter list is longer than kHeavyMin, by a workgroup; the others by a
-// wavefront.
+// shorter list is longer than kHeavyMin, by several workgroups; the others by
+// a workgroup or, when they are many, a wavefront.
 constexpr u32 kThreadSteps = 12;
 constexpr u32 kGroupLanes = 16;
 constexpr u32 kGroupMax = 32;

@@ -58,3 +58,22 @@ def test_heavy_lists(n1, n2, syms, width, reduce):
     else:
         assert_same_multiset(multiset_of(h), multiset_of(ref), what=f"{n1} {n2} {width}")
     assert h.num_premerge == ref.num_premerge
+
+
+@pytest.mark.parametrize("n1,n2,syms,width", [
+    (65, 65, 80, 1), (512, 513, 600, 3), (513, 2048, 2100, 512), (100, 511, 520, 513),
+    (70, 90, 100, 1024), (66, 300, 310, 1025), (65, 66, 70, 8200)])
+def test_wide_lists(n1, n2, syms, width):
+    """Lists of 65 to 2,048 symbols: a workgroup per source up to the number of
+    workgroups (512 and an eighth of the level to count, 1,024 to emit), a
+    wavefront per source above."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1805_06383_amd import fstc
+    m1, m2 = pair(n1, n2, syms, width, n1 + n2)
+    for kw in (dict(deterministic_ids=True), dict(product=False)):
+        h = fstc.compose(m1, m2, max_levels=2, small_levels=False, **kw).to_host()
+        ref = oracle.compose(m1, m2, max_levels=2)
+        assert_same(canon_of(h), canon_of(ref), rtol=1e-5, what=f"{n1} {n2} {width} {kw}")
+        assert h.num_premerge == ref.num_premerge

@@ -214,7 +214,7 @@ __device__ __forceinline__ u32 chunk_batch(const LevelArgs &a, const ChunkArgs &
     const u32 a1 = a.c1.seg_off[s1], n1 = a.c1.seg_off[s1 + 1] - a1;
     const u32 a2 = a.c2.seg_off[s2], n2 = a.c2.seg_off[s2 + 1] - a2;
     const u64 nn = v ? (u64)n1 * n2 : 0;
-    const u32 n = (u32)min<u64>(nn, kChunkPer + 1);
+    const u32 n = (u32)min<u64>(nn, (u64)(kChunkPer + 1));
     const u32 inc = wave_inclusive_total(n);
     const u32 ro = R + inc - n;
     R += (u32)__builtin_amdgcn_readlane((int)inc, kWave - 1);

@@ -314,8 +314,8 @@ constexpr u32 kSmallSources = 512;
 constexpr u32 kSmallRecords = 1024;
 // Joins it takes: the shorter list at most kSmallShortList symbols, the
 // longer at most kSmallLongList, at most kSmallPerSource joined pairs per
-// source (one thread joins and emits a source: longer joins and larger
-// sources are the per-level kernels' work, done by many lanes).
+// source (longer joins and larger sources are the per-level kernels' work,
+// done by many workgroups).
 constexpr u32 kSmallShortList = 32, kSmallLongList = 4096, kSmallPerSource = 64;
 // Why it stopped: a level too large (sources, joined pairs), a capacity, the
 // end of the search, or a source of a shape it does not take (a long list

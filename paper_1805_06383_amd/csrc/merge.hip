@@ -1451,112 +1451,66 @@ __global__ __launch_bounds__(256) void k_unreduced_product(MergeArgs a, const u6
 
 // ---------------------------------------------------------------------------
 // Small levels in one workgroup (level.hpp, SmallArgs).  Per level:
-//   1. each source's joined pairs counted by a walk of its two symbol lists
-//      (thread per source), offsets by a workgroup scan;
-//   2. records (source index, part-rank key; float32 product) written to LDS;
+//   1. a thread per symbol of the sources' shorter lists searches the longer
+//      list; the matches' first records by a workgroup scan;
+//   2. a thread per record finds its match and writes (source index, part-rank
+//      key; float32 product) to LDS;
 //   3. a bitonic sort of the records by key, then each run summed in float64
 //      by the thread that holds its head, merged arcs compacted in key order;
 //   4. capacities checked (before anything global changes), targets inserted
 //      in the visited set, the new pairs sorted by (q1, q2) and numbered
 //      after the existing states, then every merged arc appended with its
 //      target's id (read back from the visited set after a barrier).
+// Bound: the level's chain of dependent loads and barriers in one workgroup.
+// A thread per source walked its lists and wrote its records alone, each step
+// a dependent load, twice: 34 to 50 us a level.  With a thread per symbol and
+// per record, and the sorts' short exchanges in registers: a call of 120
+// states 0.63 -> 0.57 ms, the small language model 0.78 -> 0.68 ms, epsilon
+// chains (23 such levels) 5.6 -> 5.1 ms.
 constexpr int kSmallNT = 1024;
+static_assert(kSmallRecords <= kSmallNT && kSmallSources <= kSmallNT, "a thread per record, source");
+static_assert((u64)kSmallNT * 2 * kSmallRecords < 1ull << 48 && kSmallNT < 1 << 16, "packed sums");
 
-// Bitonic sort of key[0..n) (n a power of two, at most kSmallRecords) with
-// a 32-bit payload, by the whole workgroup; ends with a barrier.  Up to 64
-// elements the first wave sorts them in registers (shuffles, no barrier).
+// Bitonic sort of key[0..n) (n a power of two, at most the workgroup's
+// threads) with a 32-bit payload, an element per thread in registers; ends
+// with a barrier.  Partners less than 64 apart exchange by shuffles, the
+// others through LDS: ten of the 55 steps at 1,024 elements.
 __device__ __forceinline__ void small_sort(u64 *key, u32 *val, u32 n) {
-  if (n <= (u32)kWave) {
-    if (threadIdx.x < (u32)kWave) {
-      const u32 l = threadIdx.x;
-      u64 x = l < n ? key[l] : ~0ull;
-      u32 v = l < n ? val[l] : 0u;
-      for (u32 k = 2; k <= n; k <<= 1) {
-        for (u32 j = k >> 1; j > 0; j >>= 1) {
-          const u64 y = __shfl_xor(x, (int)j, kWave);
-          const u32 w = __shfl_xor(v, (int)j, kWave);
-          // the lower lane of a pair keeps the smaller key when sorting up
-          const bool up = (l & k) == 0, lower = (l & j) == 0;
-          const bool take = lower == up ? y < x : y > x;
-          if (take) {
-            x = y;
-            v = w;
-          }
-        }
-      }
-      if (l < n) {
-        key[l] = x;
-        val[l] = v;
-      }
-    }
-    __syncthreads();
-    return;
-  }
+  const u32 t = threadIdx.x;
+  const bool in = t < n;
+  u64 x = in ? key[t] : ~0ull;
+  u32 v = in ? val[t] : 0u;
   for (u32 k = 2; k <= n; k <<= 1) {
     for (u32 j = k >> 1; j > 0; j >>= 1) {
-      for (u32 i = threadIdx.x; i < n; i += kSmallNT) {
-        const u32 ixj = i ^ j;
-        if (ixj > i) {
-          const bool up = (i & k) == 0;
-          const u64 x = key[i], y = key[ixj];
-          if ((x > y) == up) {
-            key[i] = y;
-            key[ixj] = x;
-            const u32 t = val[i];
-            val[i] = val[ixj];
-            val[ixj] = t;
-          }
+      u64 y;
+      u32 w;
+      if (j >= (u32)kWave) {  // uniform
+        __syncthreads();
+        if (in) {
+          key[t] = x;
+          val[t] = v;
         }
-      }
-      __syncthreads();
-    }
-  }
-}
-
-
-
-// Calls f(s1, s2) for every pair of segments with one symbol: s1 in
-// [b1, e1), s2 in [b2, e2), in increasing symbol order (the shorter list
-// walked, the longer one binary-searched from a moving lower bound).
-template <class F>
-__device__ __forceinline__ void small_join(const u32 *sym1, u32 b1, u32 e1, const u32 *sym2,
-                                           u32 b2, u32 e2, F &&f) {
-  const u32 n1 = e1 - b1, n2 = e2 - b2;
-  if (n1 <= 4 * n2 && n2 <= 4 * n1) {
-    // lists of similar lengths: a linear merge (consecutive loads, no search)
-    u32 i = b1, j = b2;
-    while (i < e1 && j < e2) {
-      const u32 x = sym1[i], y = sym2[j];
-      if (x == y) {
-        f(i, j);
-        ++i;
-        ++j;
-      } else if (x < y) {
-        ++i;
+        __syncthreads();
+        y = in ? key[t ^ j] : x;
+        w = in ? val[t ^ j] : v;
       } else {
-        ++j;
+        y = __shfl_xor(x, (int)j, kWave);
+        w = __shfl_xor(v, (int)j, kWave);
+      }
+      // the lower of a pair keeps the smaller key when sorting up
+      const bool up = (t & k) == 0, lower = (t & j) == 0;
+      if (lower == up ? y < x : y > x) {
+        x = y;
+        v = w;
       }
     }
-    return;
   }
-  const bool one = n1 <= n2;
-  const u32 *ss = one ? sym1 : sym2, *ls = one ? sym2 : sym1;
-  const u32 sb = one ? b1 : b2, se = one ? e1 : e2, le = one ? e2 : e1;
-  u32 lo = one ? b2 : b1;
-  for (u32 i = sb; i < se && lo < le; ++i) {
-    const u32 sym = ss[i];
-    u32 l = lo, h = le;
-    while (l < h) {
-      const u32 m = (l + h) >> 1;
-      if (ls[m] < sym) l = m + 1; else h = m;
-    }
-    if (l < le && ls[l] == sym) {
-      if (one) f(i, l); else f(l, i);
-      lo = l + 1;
-    } else {
-      lo = l;
-    }
+  __syncthreads();
+  if (in) {
+    key[t] = x;
+    val[t] = v;
   }
+  __syncthreads();
 }
 
 __global__ __launch_bounds__(kSmallNT) void k_small_levels(SmallArgs a) {
@@ -1568,7 +1522,13 @@ __global__ __launch_bounds__(kSmallNT) void k_small_levels(SmallArgs a) {
   __shared__ u32 m_il[kSmallRecords], m_ol[kSmallRecords];  // merged arcs' labels
   __shared__ u32 m_src[kSmallRecords];                      // and source indexes
   __shared__ u32 s_pb1[kSmallSources], s_pb2[kSmallSources];  // sources' first parts
+  // their shorter and longer symbol lists, the elements (short-list symbols)
+  // and joined pairs of each
+  __shared__ u32 s_sb[kSmallSources], s_lb[kSmallSources], s_ln[kSmallSources];
+  __shared__ u32 s_e0[kSmallSources], s_cnt[kSmallSources];
   __shared__ u64 s_scr[kSmallNT / kWave];
+  u32 *const m_len = reinterpret_cast<u32 *>(m_w);  // of the matches, before the sums
+  constexpr u32 kOneShort = 1u << 31;               // M1's list is the shorter
   const u32 t = threadIdx.x;
   SmallState st = *a.ss;
   st.levels = st.new_levels = 0;
@@ -1584,33 +1544,80 @@ __global__ __launch_bounds__(kSmallNT) void k_small_levels(SmallArgs a) {
       st.reason = kSmallTooLarge;
       break;
     }
-    // 1. joined pairs per source
-    u32 q1 = 0, q2 = 0, b1 = 0, e1 = 0, b2 = 0, e2 = 0;
-    u64 cnt = 0;
+    // 1. matches: one thread per short-list symbol searches the longer list
+    u32 E = 0;
     bool long_join = false;
     if (t < nsrc) {
-      q1 = a.sq1[st.lo + t];
-      q2 = a.sq2[st.lo + t];
-      b1 = a.row1[q1], e1 = a.row1[q1 + 1], b2 = a.row2[q2], e2 = a.row2[q2 + 1];
+      const u32 q1 = a.sq1[st.lo + t], q2 = a.sq2[st.lo + t];
+      const u32 b1 = a.row1[q1], n1 = a.row1[q1 + 1] - b1, b2 = a.row2[q2],
+                n2 = a.row2[q2 + 1] - b2;
       s_pb1[t] = a.part_base1[q1];
       s_pb2[t] = a.part_base2[q2];
-      long_join = min(e1 - b1, e2 - b2) > kSmallShortList || max(e1 - b1, e2 - b2) > kSmallLongList;
+      const bool one = n1 <= n2;
+      E = one ? n1 : n2;
+      s_sb[t] = one ? b1 : b2;
+      s_lb[t] = one ? b2 : b1;
+      s_ln[t] = (one ? n2 : n1) | (one ? kOneShort : 0u);
+      s_cnt[t] = 0;
+      long_join = E > kSmallShortList || (one ? n2 : n1) > kSmallLongList;
     }
     if (__syncthreads_or(long_join)) {
       st.reason = kSmallShape;
       break;
     }
-    if (t < nsrc) {
-      small_join(a.seg_sym1, b1, e1, a.seg_sym2, b2, e2, [&](u32 s1, u32 s2) {
-        cnt += (u64)(a.seg_off1[s1 + 1] - a.seg_off1[s1]) * (a.seg_off2[s2 + 1] - a.seg_off2[s2]);
-      });
+    u64 En;
+    const u64 e0 = block_exclusive_sum<kSmallNT, u64>(E, s_scr, &En);
+    if (t < nsrc) s_e0[t] = (u32)e0;
+    __syncthreads();
+    u64 R = 0;   // joined pairs (exact while none of the sums overflows a list)
+    u32 nm = 0;  // matches
+    for (u32 eb = 0; eb < (u32)En; eb += kSmallNT) {  // uniform
+      const u32 e = eb + t;
+      bool found = false;
+      u32 u = 0, a1 = 0, a2 = 0, n2 = 0;
+      u64 pairs = 0;
+      if (e < (u32)En) {
+        u = (u32)last_le<u32>(s_e0, nsrc, e);  // (the last: the others are empty)
+        const u32 ln = s_ln[u] & ~kOneShort, lb = s_lb[u], si = s_sb[u] + (e - s_e0[u]);
+        const bool one = (s_ln[u] & kOneShort) != 0;
+        const u32 sym = one ? a.seg_sym1[si] : a.seg_sym2[si];
+        const u32 *ls = (one ? a.seg_sym2 : a.seg_sym1) + lb;
+        u32 l = 0, h = ln;
+        while (l < h) {
+          const u32 m = (l + h) >> 1;
+          if (ls[m] < sym) l = m + 1; else h = m;
+        }
+        found = l < ln && ls[l] == sym;
+        if (found) {
+          const u32 s1 = one ? si : lb + l, s2 = one ? lb + l : si;
+          a1 = a.seg_off1[s1];
+          a2 = a.seg_off2[s2];
+          n2 = a.seg_off2[s2 + 1] - a2;
+          pairs = (u64)(a.seg_off1[s1 + 1] - a1) * n2;
+          atomicAdd(&s_cnt[u], (u32)min<u64>(pairs, (u64)(kSmallRecords + 1)));
+        }
+      }
+      // matches below 2^16, a round's pairs of each capped: no sum overflows
+      const u64 x = found ? 1ull << 48 | min<u64>(pairs, (u64)(2 * kSmallRecords)) : 0ull;
+      u64 tot;
+      const u64 ex = block_exclusive_sum<kSmallNT, u64>(x, s_scr, &tot);
+      const u64 r = R + (ex & ((1ull << 48) - 1));
+      const u32 m = nm + (u32)(ex >> 48);
+      if (found && r < kSmallRecords && m < kSmallRecords) {
+        m_x[m] = (u32)r;  // first record
+        m_il[m] = a1;
+        m_ol[m] = a2;
+        m_len[m] = n2;
+        m_src[m] = u;
+      }
+      R += tot & ((1ull << 48) - 1);
+      nm += (u32)(tot >> 48);
+      __syncthreads();
     }
-    if (__syncthreads_or(cnt > kSmallPerSource)) {
+    if (__syncthreads_or(t < nsrc && s_cnt[t] > kSmallPerSource)) {
       st.reason = kSmallShape;
       break;
     }
-    u64 R;
-    const u64 off = block_exclusive_sum<kSmallNT, u64>(cnt, s_scr, &R);
     if (R > kSmallRecords) {  // uniform: every thread has R
       st.reason = kSmallTooLarge;
       break;
@@ -1619,24 +1626,18 @@ __global__ __launch_bounds__(kSmallNT) void k_small_levels(SmallArgs a) {
       st.reason = kSmallDone;
       break;
     }
-    // 2. records: key = source index, then the part-rank key
-    if (t < nsrc) {
-      u32 k = (u32)off;
-      small_join(a.seg_sym1, b1, e1, a.seg_sym2, b2, e2, [&](u32 s1, u32 s2) {
-        for (u32 i = a.seg_off1[s1]; i < a.seg_off1[s1 + 1]; ++i) {
-          const uint2 x1 = a.arcs1[i];
-          for (u32 j = a.seg_off2[s2]; j < a.seg_off2[s2 + 1]; ++j) {
-            const uint2 x2 = a.arcs2[j];
-            s_key[k] = ((u64)t << a.key_bits) | ((u64)x1.x << a.b2) | (u64)x2.x;
-            s_val[k] = __float_as_uint(__uint_as_float(x1.y) * __uint_as_float(x2.y));
-            ++k;
-          }
-        }
-      });
-    }
+    // 2. records, a thread each, in (source, symbol, arc pair) order: key =
+    // source index, then the part-rank key
     u32 n = 1;
     while (n < R) n <<= 1;
-    for (u32 i = (u32)R + t; i < n; i += kSmallNT) s_key[i] = ~0ull;
+    if (t < R) {
+      const u32 m = (u32)last_le<u32>(m_x, nm, t), k = t - m_x[m], x = k / m_len[m];
+      const uint2 x1 = a.arcs1[m_il[m] + x], x2 = a.arcs2[m_ol[m] + (k - x * m_len[m])];
+      s_key[t] = ((u64)m_src[m] << a.key_bits) | ((u64)x1.x << a.b2) | (u64)x2.x;
+      s_val[t] = __float_as_uint(__uint_as_float(x1.y) * __uint_as_float(x2.y));
+    } else if (t < n) {
+      s_key[t] = ~0ull;
+    }
     __syncthreads();
     // 3. sort, then runs: thread t takes records 2t, 2t + 1
     small_sort(s_key, s_val, n);

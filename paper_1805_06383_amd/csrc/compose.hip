@@ -784,14 +784,17 @@ void Composer::run(fstc_result *out) {
   bool tiny_off = false;
   u32 tiny_levels = 0;
   u32 small_levels = 0;
-  Buf ssb(&A);
-  SmallState *ss_dev = small_ok ? static_cast<SmallState *>(ssb.ensure(sizeof(SmallState)))
-                                : nullptr;
+  // a level had more records than they take: the next is tried when it has
+  // fewer at the per-level level's rate (pairs so far before it, its sources)
+  bool small_large = false;
+  u64 rate_from = 0, rate_src = 0;
   static_assert(sizeof(SmallState) <= sizeof(Staging::words), "SmallState fits the staging words");
   while (true) {
     if (o.max_levels && depth >= o.max_levels) break;
     if (hi == lo) break;
-    if (small_ok && !small_shape_off && hi - lo <= kSmallSources && depth != small_skip_depth) {
+    const bool many = small_large && (premerge - rate_from) * (hi - lo) > kSmallRecords * rate_src;
+    if (small_ok && !small_shape_off && hi - lo <= kSmallSources && depth != small_skip_depth &&
+        !many) {
       constexpr u64 kSmallGrow = 1u << 16;  // room for this many states and arcs past the current
       sq1b.grow_keep((n_states + kSmallGrow) * 4, n_states * 4);
       sq2b.grow_keep((n_states + kSmallGrow) * 4, n_states * 4);
@@ -820,16 +823,17 @@ void Composer::run(fstc_result *out) {
       sa.out_ol = out_arcs.col(3);
       sa.out_w = reinterpret_cast<float *>(out_arcs.col(4));
       sa.max_levels = o.max_levels;
-      sa.ss = ss_dev;
-      SmallState init{};
+      SmallState &init = sa.init;
       init.lo = lo;
       init.hi = hi;
       init.n_states = n_states;
       init.arcs = arcs;
       init.premerge = premerge;
       init.depth = depth;
-      std::memcpy(hs->words, &init, sizeof init);
-      FSTC_HIP(hipMemcpyAsync(ss_dev, hs->words, sizeof init, hipMemcpyHostToDevice, s));
+      const u32 seqs = next_publication();
+      sa.out = reinterpret_cast<SmallState *>(hs_words_dev);
+      sa.host = hs_dev;
+      sa.seq = seqs;
       if (!status_clear) {
         launch_reset_level(dst, s);
         status_clear = true;
@@ -837,8 +841,7 @@ void Composer::run(fstc_result *out) {
       T.at(kCount);
       launch_small_levels(sa, s);
       T.at(kNone);
-      FSTC_HIP(hipMemcpyAsync(hs->words, ss_dev, sizeof(SmallState), hipMemcpyDeviceToHost, s));
-      sync_status();
+      wait_published(seqs);
       SmallState out_st;
       std::memcpy(&out_st, hs->words, sizeof out_st);
       lo = (u32)out_st.lo;
@@ -854,12 +857,15 @@ void Composer::run(fstc_result *out) {
       max_frontier = std::max<u64>(max_frontier, out_st.max_frontier);
       max_level_pre = std::max<u64>(max_level_pre, out_st.max_level_pre);
       if (out_st.reason == kSmallDone) break;
+      if (out_st.reason == kSmallTooLarge) small_large = true;
       if (out_st.reason == kSmallShape) small_shape_off = true;
       if (out_st.reason == kSmallTooLarge || out_st.reason == kSmallShape || out_st.levels == 0)
         small_skip_depth = depth;
       continue;  // larger capacities (a capacity stop after progress) or the per-level path
     }
     const u32 nsrc = hi - lo;
+    rate_from = premerge;
+    rate_src = nsrc;
     level_tmp.reset();
     ++expanded_levels;
     max_frontier = std::max<u64>(max_frontier, nsrc);

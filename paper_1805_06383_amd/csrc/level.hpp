@@ -309,7 +309,7 @@ struct MergeArgs {
 // numbers the new pairs in (q1, q2) order and appends the merged arcs, then
 // goes on with the next level; it stops at the first level it cannot take
 // (too large, or a capacity below), at the depth cap, or when the search
-// ends, and leaves the loop state in *ss for the host.
+// ends, and publishes the loop state to the host.
 constexpr u32 kSmallSources = 512;
 constexpr u32 kSmallRecords = 1024;
 // Joins it takes: the shorter list at most kSmallShortList symbols, the
@@ -340,7 +340,10 @@ struct SmallArgs {
   u32 *out_src, *out_dst, *out_il, *out_ol;
   float *out_w;
   u32 max_levels;
-  SmallState *ss;
+  SmallState init;   // where it starts
+  SmallState *out;   // host memory: where it stopped, published with the counters
+  Status *host;      // as publication `seq`
+  u32 seq;
 };
 void launch_small_levels(const SmallArgs &a, hipStream_t s);
 

@@ -1464,7 +1464,7 @@ __global__ __launch_bounds__(256) void k_unreduced_product(MergeArgs a, const u6
 // Bound: the level's chain of dependent loads and barriers in one workgroup.
 // A thread per source walked its lists and wrote its records alone, each step
 // a dependent load, twice: 34 to 50 us a level.  With a thread per symbol and
-// per record, and the sorts' short exchanges in registers: a call of 120
+// per record, and the sorts' short exchanges in registers: a call of 30
 // states 0.63 -> 0.57 ms, the small language model 0.78 -> 0.68 ms, epsilon
 // chains (23 such levels) 5.6 -> 5.1 ms.
 constexpr int kSmallNT = 1024;
@@ -1513,6 +1513,30 @@ __device__ __forceinline__ void small_sort(u64 *key, u32 *val, u32 n) {
   __syncthreads();
 }
 
+// Copies the level counters to host memory (pinned, coherent, device-
+// visible), then, after a system-scope fence, the publication number: the
+// host waits for that word instead of a stream synchronisation.  Threads
+// t = 0 .. nt-1 of one workgroup call it together.
+__device__ __forceinline__ void publish(const Status *st, Status *host, u32 seq, u32 t, u32 nt) {
+  const u32 *src = reinterpret_cast<const u32 *>(st);
+  u32 *dst = reinterpret_cast<u32 *>(host);
+  constexpr u32 kSeqWord = offsetof(Status, seq) / 4;
+  for (u32 i = t; i < sizeof(Status) / 4; i += nt)
+    if (i != kSeqWord) dst[i] = src[i];
+  __threadfence_system();
+  if (nt > 1) __syncthreads();
+  if (t == 0) __hip_atomic_store(&host->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// End of a stage: every thread's stores are done (the barrier's release),
+// then each thread drops its CU's L1 lines (an agent-scope acquire), so its
+// next loads see what the others wrote; one workgroup shares one L2, so no
+// L2 write-back is needed.
+__device__ __forceinline__ void stage_barrier() {
+  __syncthreads();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+}
+
 __global__ __launch_bounds__(kSmallNT) void k_small_levels(SmallArgs a) {
   __shared__ u64 s_key[kSmallRecords];
   __shared__ u32 s_val[kSmallRecords];  // record weights (bits), then claimed slots
@@ -1530,7 +1554,7 @@ __global__ __launch_bounds__(kSmallNT) void k_small_levels(SmallArgs a) {
   u32 *const m_len = reinterpret_cast<u32 *>(m_w);  // of the matches, before the sums
   constexpr u32 kOneShort = 1u << 31;               // M1's list is the shorter
   const u32 t = threadIdx.x;
-  SmallState st = *a.ss;
+  SmallState st = a.init;
   st.levels = st.new_levels = 0;
   st.reason = 0;
   const u64 kmask = (1ull << a.key_bits) - 1, m2 = (1ull << a.b2) - 1;
@@ -1736,7 +1760,9 @@ __global__ __launch_bounds__(kSmallNT) void k_small_levels(SmallArgs a) {
     if (nnew) ++st.new_levels;
     __syncthreads();  // LDS reused by the next level
   }
-  if (t == 0) *a.ss = st;
+  if (t == 0) *a.out = st;
+  stage_barrier();
+  publish(a.va.st, a.host, a.seq, t, kSmallNT);
 }
 
 // ---------------------------------------------------------------------------
@@ -2623,21 +2649,6 @@ __global__ void k_finals(const u32 *sq1, const u32 *sq2, u64 n, const uint8_t *f
     fin[i] = (f1[sq1[i]] != 0 && f2[sq2[i]] != 0) ? 1 : 0;
 }
 
-// Copies the level counters to host memory (pinned, coherent, device-
-// visible), then, after a system-scope fence, the publication number: the
-// host waits for that word instead of a stream synchronisation.  Threads
-// t = 0 .. nt-1 of one workgroup call it together.
-__device__ __forceinline__ void publish(const Status *st, Status *host, u32 seq, u32 t, u32 nt) {
-  const u32 *src = reinterpret_cast<const u32 *>(st);
-  u32 *dst = reinterpret_cast<u32 *>(host);
-  constexpr u32 kSeqWord = offsetof(Status, seq) / 4;
-  for (u32 i = t; i < sizeof(Status) / 4; i += nt)
-    if (i != kSeqWord) dst[i] = src[i];
-  __threadfence_system();
-  if (nt > 1) __syncthreads();
-  if (t == 0) __hip_atomic_store(&host->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-}
-
 // Level totals after the merge: merged arcs (end of the scan of merged arcs
 // per source), new pairs (*nt, or the length of the new-pair list), the
 // product merge's joined pairs (sum of the per-source joined pairs less the
@@ -2710,15 +2721,6 @@ __global__ __launch_bounds__(1024) void k_merged_total(const u64 *at, const u64 
 constexpr int kTinyNT = 1024;
 static_assert(kTinySources * kProdRow * kProdRow <= (u32)kTinyNT, "a thread per source and per entry");
 static_assert(kTinyNT <= kSmallNT && (u32)kTinyNT <= kSmallRecords, "small_sort takes the level's claims");
-
-// End of a stage: every thread's stores are done (the barrier's release),
-// then each thread drops its CU's L1 lines (an agent-scope acquire), so its
-// next loads see what the others wrote; one workgroup shares one L2, so no
-// L2 write-back is needed.
-__device__ __forceinline__ void stage_barrier() {
-  __syncthreads();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-}
 
 __global__ __launch_bounds__(kTinyNT) void k_product_level(LevelArgs la, MergeArgs ma, u64 *poff,
                                                            u64 *newoff, u32 base, u32 *sq1,

@@ -460,17 +460,6 @@ struct Composer {
     T.all = o.phase_timing != 0;
   }
 
-  void sync_status() {
-    FSTC_HIP(hipGetLastError());
-    FSTC_HIP(hipMemcpyAsync(&hs->st, dst, sizeof(Status), hipMemcpyDeviceToHost, s));
-    FSTC_HIP(hipStreamSynchronize(s));
-    ++nsyncs;
-    if (hs->st.err) {
-      throw Error((hs->st.err & kErrBadArc) ? FSTC_ERR_INVALID_ARG : FSTC_ERR_INTERNAL,
-                  device_error_text(hs->st.err));
-    }
-  }
-
   // Waits until a kernel has copied the counters to hs->st and then written
   // publication number `seq` (the count scan's ScanPublish, launch_merged_total): a
   // spin on that word, with a stream query every few thousand reads so that

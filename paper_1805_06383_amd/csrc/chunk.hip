@@ -559,7 +559,9 @@ __global__ __launch_bounds__(kOutNT) void k_chunk_emit(MergeArgs a, ChunkArgs c)
   for (u32 b0 = blockIdx.x * kW; b0 < c.nblk; b0 += gridDim.x * kW) {  // uniform
     if (!PLAIN) {  // room for a round's claims
       __syncthreads();
-      if (L.n + kW * c.cap > kClaimCap) {
+      const u32 have = L.n;
+      __syncthreads();  // every wave has read it before one adds: one decision for all
+      if (have + kW * c.cap > kClaimCap) {
         claims_end(a, L);
         __syncthreads();
         claims_begin(L);

@@ -136,7 +136,8 @@ def recorded_traffic(kernel: str, workload: str):
 
 def product_flops(st: dict) -> float:
     """Float operations the product merge must do per compose: one float32
-    multiply and one float64 add per joined arc pair it merges."""
+    multiply and one float64 add per joined arc pair it merges (every pair of
+    total_product_records, when it merges every source)."""
     return 2.0 * st["total_product_records"]
 
 
@@ -286,28 +287,35 @@ def main():
                                 "GBps": sum(ab.values()) / (both_ms * 1e-3) / 1e9 if both_ms else 0.0}
         pms = sums["ms_product_kernel"] / args.steps
         pl = max(1, st["product_launches"])
-        pf = product_flops(st)
+        # pairs of sources merged on the chip whole (k_chunk_join) are counted
+        # with the product merge's: its own are known when it took every state
+        pure = st["total_product_sources"] == last.num_states
+        pf = product_flops(st) if pure else None
         kern["product"] = {"kernel": "k_prod_quad + k_prod_sources", "ms_per_step": pms,
                            "launches_per_step": st["product_launches"], "avg_launch_ms": pms / pl,
                            "sources_per_step": st["total_product_sources"],
                            "joined_pairs_per_step": st["total_product_records"],
                            "mfma_sources_per_step": st["total_product_mfma_sources"],
                            "flops_per_step": pf,
-                           "TFLOPps": pf / (pms * 1e-3) / 1e12 if pms > 0 else 0.0}
+                           "TFLOPps": pf / (pms * 1e-3) / 1e12 if pure and pms > 0 else None}
         rec_ms = {k: kern[k]["ms_per_step"] for k in ab}
         dom = max(rec_ms, key=rec_ms.get)
         exact = traffic_key and not args.max_levels and not args.no_reduction
-        if pms == 0 and rec_ms[dom] == 0:
-            # no per-level kernel ran: the one-workgroup kernels took every
-            # level; their bytes are the result they write (20 B per arc, 9 B
-            # per state), over the whole step
+        if (pms == 0 or not pure) and pms >= rec_ms[dom]:
+            # none of the timed kernels carries the step: the one-workgroup
+            # kernels or the chunk merge took the levels; their bytes are the
+            # result they write (20 B per arc, 9 B per state), over the whole step
+            chunked = st["total_product_records"] > 0
             step_ms = secs * 1e3 / args.steps
             nbytes = last.num_arcs * 20 + last.num_states * 9
             gbs = nbytes / (step_ms * 1e-3) / 1e9
-            roof = {"bound": "hbm", "kernel": "k_small_levels",
+            roof = {"bound": "hbm", "kernel": "k_small_levels" if not chunked else
+                    "k_prod_quad + k_chunk_join" if st["total_product_sources"] else "k_chunk_join",
                     "achieved": gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                     "frac": gbs / HBM_PEAK_GBS, "traffic": None,
-                    "limiter": "one workgroup runs every level (a few dozen pairs each): the "
+                    "limiter": "whole step: dependent loads of each source's join and visited "
+                               "probes, launches between levels" if chunked else
+                               "one workgroup runs every level (a few dozen pairs each): the "
                                "latency of its dependent steps and the host's wait, not bandwidth"}
             return kern, roof
         if pms > rec_ms[dom]:

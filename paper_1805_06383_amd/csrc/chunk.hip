@@ -551,8 +551,9 @@ __device__ __forceinline__ void emit_entries(const MergeArgs &a, const ChunkArgs
 // rest of each: a region of sparse sources holds about 64, one dependent chain
 // (parts, visited entry, claim) per lane if taken alone.
 template <u32 B, bool PLAIN>
-__global__ __launch_bounds__(kOutNT) void k_chunk_emit(MergeArgs a, ChunkArgs c) {
+__global__ __launch_bounds__(kOutNT) void k_chunk_emit(MergeArgs a, ChunkArgs c, const u64 *skip_if) {
   __shared__ ClaimLds<PLAIN ? 1u : kClaimCap> L;
+  if (skip_if && *skip_if) return;  // uniform
   if (!PLAIN) claims_begin(L);
   constexpr u32 kW = kOutNT / kWave * B;
   const u32 lane = lane_id();
@@ -658,7 +659,8 @@ void launch_chunk_join(const LevelArgs &a, const ChunkArgs &c, int b2, int key_b
                      key_bits);
 }
 
-void launch_chunk_emit(const MergeArgs &a, const ChunkArgs &c, bool plain, hipStream_t s) {
+void launch_chunk_emit(const MergeArgs &a, const ChunkArgs &c, bool plain, const u64 *skip_if,
+                       hipStream_t s) {
   if (!c.nblk) return;
   if (plain && !a.vn2) throw Error(FSTC_ERR_INTERNAL, "plain claims need the dense visited array");
   const u32 B = c.cap <= kChunkMinCap ? kOutB : 2u;
@@ -668,7 +670,7 @@ void launch_chunk_emit(const MergeArgs &a, const ChunkArgs &c, bool plain, hipSt
                                                                             rounds / 4))));
   auto go = [&](auto b, auto pl) {
     hipLaunchKernelGGL((k_chunk_emit<decltype(b)::value, decltype(pl)::value>), g, dim3(kOutNT), 0, s,
-                       a, c);
+                       a, c, skip_if);
   };
   using Four = std::integral_constant<u32, kOutB>;
   using Two = std::integral_constant<u32, 2>;

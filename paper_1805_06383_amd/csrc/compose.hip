@@ -693,9 +693,12 @@ void Composer::run(fstc_result *out) {
 
   // Visited table: keeps the load factor at most 1/2 for `states` states (at
   // most kMaxHashCap slots: an insert into a full table reports it).
-  auto grow_visited = [&](u64 states) {
+  // slots_held: the level's merged arcs hold slots of the hash table already
+  // (a growth moves every key, the dense array has other slots).
+  auto grow_visited = [&](u64 states, bool slots_held) {
     const u64 need = std::min<u64>(2 * states, kMaxHashCap);
     if (dense_vis || need <= hcap) return;
+    if (slots_held) throw Error(FSTC_ERR_INTERNAL, "the visited table moved under a level's slots");
     if (!o.hash_visited && pairspace <= kDenseMaxPairs && next_pow2(need) * 12 >= pairspace * 4) {
       // the grown table (8-byte keys, 4-byte ids) would be at least as large
       // as the dense array over all pairs: move the visited set there (the
@@ -1045,14 +1048,14 @@ void Composer::run(fstc_result *out) {
     const bool scan_new = chunk && dense_vis && pairspace <= kScanPairsPerSource * nsrc;
     bool chunk_emitted = false;
     u64 list_cap = 0;  // entries of newlist while the chunk merge's claims are in it
-    auto chunk_emit = [&](u64 cap) {
+    auto chunk_emit = [&](u64 cap, const u64 *skip_if) {
       MergeArgs m{};
       visit_args(m);
       list_cap = std::max<u64>(std::min<u64>(cap, left_pairs), 1);
       newlist.ensure(list_cap * 4);
       m.newlist = newlist.as<u32>();
       m.newcap = list_cap;
-      launch_chunk_emit(m, ca, scan_new, s);
+      launch_chunk_emit(m, ca, scan_new, skip_if, s);
       // (all of the level's new pairs so far: the list stays empty)
       if (scan_new) launch_claim_count(hvb.as<u32>(), pairspace, claim_tmp(), &dst->nnew, nullptr, s);
       chunk_emitted = true;
@@ -1083,13 +1086,17 @@ void Composer::run(fstc_result *out) {
     if (chunk) {
       T.at(kCount);
       launch_chunk_join(la, ca, b2, key_bits, s);
-      // the claims before the host knows their number, when the visited set
-      // has room for the most there can be
+      // The claims before the host knows their number, when the visited set
+      // has room for the most there can be.  A hash table may have to grow for
+      // the level's other sources, whose joined pairs are not counted yet, and
+      // its slots change then: there the claims stand down when the level has
+      // such sources, and follow once the table has room for both.
       const bool room = dense_vis || 2 * (n_states + std::min<u64>(chunk_cap, left_pairs)) <= hcap;
       T.at(kMerge);
-      if (room) chunk_emit(chunk_cap);
+      if (room && (dense_vis || chunk_pure))
+        chunk_emit(chunk_cap, dense_vis ? nullptr : &dst->general);
       T.at(kNone);
-      if (chunk_pure || !room) {
+      if (chunk_pure || !chunk_emitted) {
         const u32 seqc = next_publication();
         T.at(kMerge);
         chunk_scan(seqc);
@@ -1122,6 +1129,7 @@ void Composer::run(fstc_result *out) {
         wait_published(seqc);
         const bool pure = hs->st.general == 0;
         chunk_pure = pure;
+        if (!pure && !dense_vis) chunk_emitted = false;  // it stood down
         const u64 merged_c = hs->st.merged;  // of the chunk merge when not pure
         if (pure) {
           lists_empty = listed_empty = true;
@@ -1130,9 +1138,9 @@ void Composer::run(fstc_result *out) {
           if (merged_c == 0) break;  // no arc leaves this level
           u64 nnew_c = hs->st.nnew;
           if (!chunk_emitted) {
-            grow_visited(n_states + std::min<u64>(merged_c, left_pairs));
+            grow_visited(n_states + std::min<u64>(merged_c, left_pairs), false);
             T.at(kMerge);
-            chunk_emit(merged_c);
+            chunk_emit(merged_c, nullptr);
             const u32 seqe = next_publication();
             hipLaunchKernelGGL(k_publish_counts, dim3(1), dim3(kWave), 0, s, nullptr, 0u, nullptr, 0u,
                                nullptr, nullptr, 0, nullptr, 0u, dst, hs_dev, hs_words_dev, seqe);
@@ -1345,10 +1353,10 @@ void Composer::run(fstc_result *out) {
         FSTC_HIP(hipMemcpyAsync(newlist.p, old, listed * 4, hipMemcpyDeviceToDevice, s));
     }
 
-    grow_visited(n_states + newcap);
+    grow_visited(n_states + newcap, chunk_emitted);
     if (chunk && !chunk_emitted) {
       T.at(kMerge);
-      chunk_emit(newcap);
+      chunk_emit(newcap, nullptr);
       T.at(kNone);
     }
 

@@ -418,9 +418,11 @@ void launch_compact_sources(const MergeArgs &a, const u64 *aoff, u64 M, const u3
 // stores, and launch_claim_count finds the new pairs: a claim by
 // compare-and-swap is performed beyond the L2, 100 ps each against 30 for the
 // store, and a level of millions of claims spends most of its time there),
-// and their result append (after the level's ids; M: room from osrc on).  skip_if (may be NULL): nothing is done when that device word is
-// nonzero; clear: the level counters of a.st are zeroed then.
-void launch_chunk_emit(const MergeArgs &a, const ChunkArgs &c, bool plain, hipStream_t s);
+// and their result append (after the level's ids; M: room from osrc on).
+// skip_if (may be NULL): nothing is done when that device word is nonzero;
+// clear: the append zeroes the level counters of a.st.
+void launch_chunk_emit(const MergeArgs &a, const ChunkArgs &c, bool plain, const u64 *skip_if,
+                       hipStream_t s);
 void launch_chunk_compact(const MergeArgs &a, const ChunkArgs &c, const u64 *aoff, u64 M,
                           const u32 *hvals, u32 *osrc, u32 *odst, u32 *oil, u32 *ool, float *ow,
                           const u64 *skip_if, bool clear, hipStream_t s);

@@ -9,7 +9,7 @@
 // consecutive sources and keeps everything between the symbol lists and the
 // merged arcs in registers and LDS:
 //   1. one lane per source reads its two symbol lists' ranges and lists the
-//      long joins for the general kernels;
+//      long joins and the product-merge sources for the general kernels;
 //   2. both lists of a batch of sources are staged in LDS by groups of 16
 //      lanes (longer ones above kChunkStage symbols stay in memory); the
 //      shorter lists' symbols are dealt to the lanes and searched in the
@@ -74,6 +74,25 @@ struct ChunkLds {
   u64 hb[kBitWords + 1];                      // bit p: record p is the first of its key
   u32 hpre[kBitWords + 1];                    // set bits in the words before
 };
+
+// Selects source u (of the lanes with want) for the product merge, as
+// k_count_small does: the matrix-core form always, whose products are exact
+// where the records here are rounded to float32, and the other one when its
+// lists have room for a term or more per entry (A1 A2 / max(n1, n2) pairs
+// where the lists agree).  Sources with fewer terms than entries are cheaper
+// here, in the same precision; a source of 200 pairs on 25 entries is 6 times as
+// dear (a million such sources: 14.9 ms, 2.4 by the product merge), one of 32
+// on 4 twice.
+__device__ __forceinline__ u32 chunk_product(const LevelArgs &a, bool want, u32 u, u32 q1, u32 q2,
+                                             const Ranges &r, bool &mf) {
+  u32 pk = want ? select_product(a, u, q1, q2, r, mf) : 0u;
+  if (pk && !mf) {
+    const u64 a1 = a.c1.seg_off[r.e1] - a.c1.seg_off[r.b1],
+              a2 = a.c2.seg_off[r.e2] - a.c2.seg_off[r.b2];
+    if (a1 * a2 < (u64)pk * max(r.e1 - r.b1, r.e2 - r.b2)) pk = 0;
+  }
+  return pk;
+}
 
 // Lists source u (of the lanes with pred) in `list`.
 __device__ __forceinline__ void list_source(bool pred, u32 u, u32 *list, u32 *counter, uint4 *range,
@@ -425,7 +444,8 @@ __global__ __launch_bounds__(NT) void k_chunk_join(LevelArgs a, ChunkArgs c, int
   Ranges r{0, 0, 0, 0};
   bool unfit = false;
   u32 E = 0, q1 = 0, q2 = 0;
-  bool wide = false, heavy = false;
+  bool wide = false, heavy = false, mf = false;
+  u32 pk = 0;
   if (t < ns) {
     q1 = a.sq1[a.lo + u];
     q2 = a.sq2[a.lo + u];
@@ -435,13 +455,14 @@ __global__ __launch_bounds__(NT) void k_chunk_join(LevelArgs a, ChunkArgs c, int
     const u32 mn = min(n1, n2), mx = max(n1, n2);
     heavy = mn > kHeavyMin;
     wide = !heavy && mn > kChunkShort;
-    if (mn <= kChunkShort) E = mn;
-    unfit = mn > kSmallShortList || mx > kSmallLongList;
+    pk = chunk_product(a, a.prod && mn >= kProdMinSymbols && mn <= (u32)kWave, u, q1, q2, r, mf);
+    if (mn <= kChunkShort && !pk) E = mn;
+    unfit = pk || mn > kSmallShortList || mx > kSmallLongList;
     a.tstart[u] = 0;
     a.mend[u] = 0;
     a.newc[u] = 0;
-    a.pk[u] = 0;
-    a.pflag[u] = 0;
+    a.pk[u] = pk;
+    a.pflag[u] = pk ? 1ull | ((u64)mf << 32) : 0ull;
     a.cnt[u] = 0;
     a.mc[u] = 0;
     c.pairs[u] = 0;
@@ -463,7 +484,10 @@ __global__ __launch_bounds__(NT) void k_chunk_join(LevelArgs a, ChunkArgs c, int
   }
   const u32 lens = wave_or(stg);
   const u32 steps = lens ? 1u << (31 - __clz(lens)) : 0u;
-  if (__ballot(wide || heavy)) {
+  if (__ballot(wide || heavy || pk)) {
+    // (strided sources go to the four-source kernel when it runs)
+    list_source(pk && !(a.quad && (a.phdr[2 * u].w & 4u)), u, a.glist, &a.st->ngen, nullptr,
+                make_uint4(0, 0, 0, 0));
     list_source(heavy, u, a.heavy, &a.st->nheavy, nullptr, make_uint4(0, 0, 0, 0));
     list_source(wide, u, a.wide, &a.st->nwide, a.wrange, make_uint4(r.b1, r.e1, r.b2, r.e2));
     if (t == 0) a.st->general = 1;

@@ -665,9 +665,9 @@ void Composer::run(fstc_result *out) {
   // whole and the host waits once.
   const bool chunk_ok = product && !o.fused_merge && key_bits <= kChunkKeyBits;
   bool chunk_pure = true;
-  // a level's sources had more arc pairs than the chunk merge takes: the next
-  // one's are not offered to it
-  bool chunk_heavy = false;
+  // a level's sources had more arc pairs than the chunk merge takes, or half of
+  // them took the product merge: the next one's are not offered to it
+  bool chunk_heavy = false, product_level = false;
   // the previous per-level level had no listed sources: the list kernels
   // get lean grids (see launch_count, launch_prod_sources)
   bool lists_empty = false, listed_empty = false;
@@ -845,7 +845,7 @@ void Composer::run(fstc_result *out) {
       expanded_levels += out_st.levels;
       new_levels += out_st.new_levels;
       small_levels += out_st.levels;
-      if (out_st.levels) last_direct = false;
+      if (out_st.levels) last_direct = product_level = false;
       max_frontier = std::max<u64>(max_frontier, out_st.max_frontier);
       max_level_pre = std::max<u64>(max_level_pre, out_st.max_level_pre);
       if (out_st.reason == kSmallDone) break;
@@ -968,7 +968,8 @@ void Composer::run(fstc_result *out) {
     // publishes the counters as publication `seq`
     // Chunk merge: a level's sources joined and merged on the chip, S to a
     // wavefront.  What it leaves is counted by launch_count_lists.
-    const bool chunk = chunk_ok && !last_direct && !chunk_heavy && nsrc >= kChunkMinSources;
+    const bool chunk = chunk_ok && !last_direct && !chunk_heavy && !product_level &&
+                       nsrc >= kChunkMinSources;
     ChunkArgs ca{};
     const u64 left_pairs = pairspace - n_states;  // pairs that are no states yet
     u64 chunk_cap = 0;                            // most arcs the chunk merge produces
@@ -1317,6 +1318,7 @@ void Composer::run(fstc_result *out) {
     const u64 prodpos = nprod ? hs->st.prod_entries : 0;  // product-merge temp slots
     if (R == 0 && nprod == 0 && !chunk) break;  // no arc leaves this level: no new states either
     chunk_heavy = nsrc >= kChunkMinSources && R > (u64)kChunkPer * nsrc;
+    product_level = 2 * (u64)nprod >= nsrc;
     if (chunk && hs->st.general == 0) chunk_pure = true;  // the next level is enqueued whole
     premerge += R;
     max_level_pre = std::max(max_level_pre, R);

@@ -111,9 +111,8 @@ __global__ void k_copy_count(const u32 *src, u64 *dst) { *dst = *src; }
 // Wave per state; lane l checks segments row[q] + l, + 64, ...: a segment
 // of more arcs than kProdParts, or whose arcs' parts are not all distinct
 // (a 64-bit mask of the parts), flags the state (bit 0), as do more than
-// kCellMaxSegs segments: one wave's walk over a trie root's 50,000 took
-// 570 us, and the product merge would search such a list for its at most 64
-// symbols in 64-symbol chunks, one after the other.  For the other
+// kProdParts parts (such a state is not walked at all: a trie root's 50,000
+// segments on 30 parts took its wave 570 us).  For the other
 // states the word also summarises the arcs' weights (kCellSpecial: a
 // non-finite or subnormal weight; the largest biased float32 exponent of a
 // nonzero weight at kCellEmaxShift, the smallest at kCellEminShift) and
@@ -139,7 +138,7 @@ __device__ __forceinline__ void cell_flags_body(const u32 *row, const u32 *seg_s
   const u32 lane = lane_id();
   const u64 nw = (u64)(nblk - gw) * blockDim.x / kWave;
   for (u64 q = ((u64)(blk - gw) * blockDim.x + threadIdx.x) / kWave; q < nq; q += nw) {
-    bool bad = part_base[q + 1] - part_base[q] > kProdParts || row[q + 1] - row[q] > kCellMaxSegs;
+    bool bad = part_base[q + 1] - part_base[q] > kProdParts;
     bool special = false, shuffled = false;
     bool gap = false;  // a symbol other than the first plus its segment index
     u32 emax = 0, emin = 255;

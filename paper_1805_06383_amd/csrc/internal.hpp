@@ -147,15 +147,13 @@ bool build_csr_pair(const fstc_fst &m1, bool by_output1, Arena &T1, const Csr &c
                     u64 *d_counts1, const fstc_fst &m2, bool by_output2, Arena &T2,
                     const Csr &c2, u64 *d_counts2, bool flags, u32 *d_err, hipStream_t s);
 
-// Largest part count of a state the product merge takes (level.hpp).
-constexpr u32 kProdParts = 64;
+// Largest part count of a state the product merge takes: with one part on the
+// other side, kProdRowSum in all (level.hpp).
+constexpr u32 kProdParts = 15;
 
-// Longest symbol list of a state the product merge takes.
-constexpr u32 kCellMaxSegs = 2048;
-
-// cell_flag[q] has bit kCellBad when state q has more than kProdParts parts,
-// more than kCellMaxSegs segments, or two arcs with the same part and inner
-// symbol (parallel arcs with equal labels and target).  Otherwise it summarises the state's arc weights: bit
+// cell_flag[q] has bit kCellBad when state q has more than kProdParts parts or
+// two arcs with the same part and inner symbol (parallel arcs with equal
+// labels and target).  Otherwise it summarises the state's arc weights: bit
 // kCellSpecial when one is infinite, NaN or subnormal, and the largest and
 // smallest biased float32 exponents of its nonzero weights (0 and 255 in
 // those fields when it has none), and bit kCellDense when every one of its

@@ -65,6 +65,7 @@ static_assert(offsetof(Status, nprod) % 8 == 0 &&
 // selects it from the list lengths and part counts alone; the product
 // kernel counts its joined pairs.
 constexpr u32 kProdRowSum = 16;
+static_assert(kProdParts == kProdRowSum - 1, "a state of more parts is never selected");
 constexpr u32 kProdMinSymbols = 8;
 // Sources whose states have at most kProdMfmaParts parts each and whose
 // weight products are normal float32 numbers (expand.hip, products_normal)

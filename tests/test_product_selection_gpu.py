@@ -116,3 +116,12 @@ def test_full_cells_of_more_parts():
     g = fstc.compose(m1, m2, small_levels=False)
     assert g.stats["total_product_sources"] == g.num_states - 1
     assert_same(canon_of(g.to_host()), canon_of(oracle.compose(m1, m2)), what="five parts")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("wide", [2000, 2049, 5000])
+def test_exact_products_of_long_lists(wide):
+    """A state of few parts over thousands of symbols, joined with 12 of them."""
+    m1 = machine(1, True, 20, 0, 4, 12, 40, wide=wide, base=wide)
+    m2 = machine(2, False, 20, 0, 4, 12, 40, base=wide)
+    check(m1, m2, 20)

@@ -180,8 +180,8 @@ def test_csr_few_large_states(fstc, nq, n):
 
 @pytest.mark.parametrize("syms", [2047, 2048, 2049])
 def test_long_lists_against_short(fstc, syms):
-    """States of few parts whose symbol list is at the longest one the product
-    merge takes, composed with states of eight and of 2,000 symbols."""
+    """States of few parts and long symbol lists, which the product merge takes
+    however long they are, composed with states of 8, 64 and 2,000 symbols."""
     import oracle
     from fstcheck import assert_same, canon_of
     rng = np.random.default_rng(syms)
@@ -197,4 +197,4 @@ def test_long_lists_against_short(fstc, syms):
                final=np.ones(3, np.uint8))
     g = fstc.compose(m1, m2, small_levels=False)
     assert_same(canon_of(g.to_host()), canon_of(oracle.compose(m1, m2)), rtol=1e-5, what=f"{syms}")
-    assert (g.stats["total_product_sources"] > 0) == (syms <= 2048)
+    assert g.stats["total_product_sources"] > 0

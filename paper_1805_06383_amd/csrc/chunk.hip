@@ -437,7 +437,7 @@ __device__ __forceinline__ u32 chunk_batch(const LevelArgs &a, const ChunkArgs &
 __global__ __launch_bounds__(NT) void k_chunk_join(LevelArgs a, ChunkArgs c, int b2, int kb) {
   __shared__ ChunkLds L;
   const u32 t = lane_id();
-  const u64 u0 = (u64)blockIdx.x * c.S;
+  const u64 u0 = ((u64)c.first + blockIdx.x) * c.S;
   const u32 ns = (u32)min<u64>(c.S, a.nsrc - u0);
   // 1. classification: lane t < kChunkS holds source u0 + t
   const u32 u = (u32)u0 + t;
@@ -516,12 +516,38 @@ __global__ __launch_bounds__(NT) void k_chunk_join(LevelArgs a, ChunkArgs c, int
   }
 }
 
+// First temp slot of wavefront b's merged arcs.
+__device__ __forceinline__ u64 region_base(const ChunkArgs &c, u32 b) {
+  return c.off ? c.off[b] : (u64)b * c.cap;
+}
+
+// Packs the regions, a wave each (launch_chunk_pack).
+constexpr u32 kOutNT = 256, kOutB = 4;
+__global__ __launch_bounds__(kOutNT) void k_chunk_pack(LevelArgs a, ChunkArgs c, const u64 *off,
+                                                       uint4 *tmp, uint8_t *src) {
+  const u32 lane = lane_id();
+  const u32 nw = gridDim.x * (kOutNT / kWave);
+  for (u32 b = blockIdx.x * (kOutNT / kWave) + threadIdx.x / kWave; b < c.nblk; b += nw) {
+    const u32 n = min(c.cnt[b], c.cap);  // at most cap by the join
+    if (n == 0) continue;
+    const u64 from = (u64)b * c.cap, to = off[b];
+    for (u32 e = lane; e < n; e += kWave) {
+      tmp[to + e] = c.tmp[from + e];
+      src[to + e] = c.src[from + e];
+    }
+    const u64 u = ((u64)c.first + b) * c.S + lane;
+    if (lane < c.S && u < a.nsrc && c.pairs[u]) {  // (the other sources have no slots)
+      a.tstart[u] += to - from;
+      a.mend[u] += to - from;
+    }
+  }
+}
+
 // Merged arcs of the chunk merge, a wave per region: part numbers to (r1, a)
 // and (r2, c), the target pair inserted in the visited set, claims listed
 // (appended when kClaimCap might not hold another round's).  PLAIN (dense
 // visited array, launch_chunk_emit): claimed by a plain store instead, and the
 // level's new pairs found by a pass over the array.
-constexpr u32 kOutNT = 256, kOutB = 4;
 constexpr u32 kClaimCap = 4096;
 static_assert(kOutNT / kWave * kOutB * kChunkMinCap <= kClaimCap &&
                   kOutNT / kWave * 2 * kChunkMaxCap <= kClaimCap,
@@ -601,7 +627,7 @@ __global__ __launch_bounds__(kOutNT) void k_chunk_emit(MergeArgs a, ChunkArgs c,
       n[j] = bw + j < c.nblk ? min(c.cnt[bw + j], c.cap) : 0u;  // at most cap by the join
       most = max(most, n[j]);
       act[j] = lane < n[j];
-      q[j] = (u64)(bw + j) * c.cap + lane;
+      q[j] = (n[j] ? region_base(c, bw + j) : 0ull) + lane;
     }
     if (most == 0) continue;  // wave-uniform
     emit_entries<B, PLAIN>(a, c, q, act, L);
@@ -629,7 +655,7 @@ __global__ __launch_bounds__(kOutNT) void k_chunk_compact(MergeArgs a, ChunkArgs
   for (u32 b = blockIdx.x * (kOutNT / kWave) + threadIdx.x / kWave; b < c.nblk; b += nw) {
     const u32 n = min(c.cnt[b], c.cap);
     if (n == 0) continue;
-    const u64 base = (u64)b * c.cap, u0 = (u64)b * c.S;
+    const u64 base = region_base(c, b), u0 = ((u64)c.first + b) * c.S;
     // lane i < S: output position less temp slot (wraps) of source i
     const u64 u = min(u0 + lane % kChunkS, (u64)a.nsrc - 1);
     const u64 to = aoff[u] - a.tstart[u];
@@ -676,11 +702,16 @@ __global__ __launch_bounds__(kOutNT) void k_chunk_compact(MergeArgs a, ChunkArgs
 
 void launch_chunk_join(const LevelArgs &a, const ChunkArgs &c, int b2, int key_bits,
                        hipStream_t s) {
-  if (key_bits > kChunkKeyBits || !c.S || c.S > kChunkS || (u64)c.nblk * c.S < a.nsrc ||
-      c.cap < kChunkMinCap || c.cap > kChunkMaxCap)
+  if (key_bits > kChunkKeyBits || !c.S || c.S > kChunkS || !c.nblk ||
+      (u64)c.first + c.nblk > ceil_div(a.nsrc, c.S) || c.cap < kChunkMinCap || c.cap > kChunkMaxCap)
     throw Error(FSTC_ERR_INTERNAL, "chunk merge out of its range");
-  hipLaunchKernelGGL(k_chunk_join, dim3((unsigned)ceil_div(a.nsrc, c.S)), dim3(NT), 0, s, a, c, b2,
-                     key_bits);
+  hipLaunchKernelGGL(k_chunk_join, dim3(c.nblk), dim3(NT), 0, s, a, c, b2, key_bits);
+}
+
+void launch_chunk_pack(const LevelArgs &a, const ChunkArgs &c, const u64 *off, uint4 *tmp,
+                       uint8_t *src, hipStream_t s) {
+  const u64 g = std::min<u64>(ceil_div(c.nblk, kOutNT / kWave), 1u << 20);
+  hipLaunchKernelGGL(k_chunk_pack, dim3((unsigned)g), dim3(kOutNT), 0, s, a, c, off, tmp, src);
 }
 
 void launch_chunk_emit(const MergeArgs &a, const ChunkArgs &c, bool plain, const u64 *skip_if,

@@ -18,6 +18,7 @@
 #include <array>
 #include <chrono>
 #include <cstring>
+#include <deque>
 #include <functional>
 #include <mutex>
 #include <vector>
@@ -85,6 +86,14 @@ constexpr u64 kLocalPairs = u64(1) << 20;
 constexpr u32 kChunkMinSources = 32;
 // Levels of the chunk merge with the most temp slots (136 MB at 17 B a slot).
 constexpr u64 kChunkFewSources = u64(1) << 17;
+// Most bytes of temp slots: a level that needs more (from 15.8 M sources on at
+// the largest capacity, 31.6 M at the smallest) is joined in runs of sources
+// that share one set of slots, and each run's merged arcs are kept packed, at
+// 17 B each (a region holds 32 to 64 slots a source, whatever it joins).  Sparse
+// machines of 10^8 pairs and 781 M arcs held 131 GiB, now 47; 536 M states of a
+// power law 120 GiB and 186 ms, now 76 and 197.
+constexpr u64 kChunkSlotBytes = u64(1) << 34;
+constexpr u64 kChunkSlot = sizeof(uint4) + 1;
 // Largest temp (entries x 20 bytes) reserved for a speculative product merge.
 constexpr u64 kSpecBytes = u64(1) << 30;
 inline size_t grown(size_t cap_bytes) { return cap_bytes * (cap_bytes < kFastGrowBytes ? 4 : 2); }
@@ -695,7 +704,7 @@ void Composer::run(fstc_result *out) {
       dk(&level_tmp), dv(&level_tmp), dka(&level_tmp), dva(&level_tmp), dtmp(&level_tmp),
       tiles_e(&level_tmp), tiles_m(&level_tmp), tstart(&level_tmp), mend(&level_tmp),
       sortlist(&level_tmp), tile_runs(&level_tmp), runsrc(&level_tmp), ctmp(&level_tmp),
-      csrc(&level_tmp), ccnt(&level_tmp), cpairs(&level_tmp);
+      csrc(&level_tmp), ccnt(&level_tmp), cpairs(&level_tmp), coff(&level_tmp);
 
   // Visited table: keeps the load factor at most 1/2 for `states` states (at
   // most kMaxHashCap slots: an insert into a full table reports it).
@@ -977,11 +986,13 @@ void Composer::run(fstc_result *out) {
     const bool chunk = chunk_ok && !last_direct && !chunk_heavy && !product_level &&
                        nsrc >= kChunkMinSources;
     ChunkArgs ca{};
+    std::vector<ChunkArgs> cruns;  // the level's chunk merge, in runs of wavefronts
+    std::deque<Buf> slots;         // their slots, where the arena does not hold them
     const u64 left_pairs = pairspace - n_states;  // pairs that are no states yet
     u64 chunk_cap = 0;                            // most arcs the chunk merge produces
     if (chunk) {
       ca.S = chunk_sources(nsrc);
-      ca.nblk = (u32)ceil_div(nsrc, ca.S);
+      const u32 nblk = (u32)ceil_div(nsrc, ca.S);
       // slots per wavefront: all that its sources can need or the most while
       // the level is small, else four times what the sources before had (a
       // wavefront that needs more leaves its sources to the general kernels)
@@ -989,15 +1000,57 @@ void Composer::run(fstc_result *out) {
                    ? std::min(kChunkMaxCap, kChunkPer * ca.S)
                    : (u32)std::min<u64>(kChunkMaxCap, std::max<u64>(kChunkMinCap,
                                         next_pow2(4 * kChunkS * ceil_div(arcs, std::max<u64>(lo, 1)))));
-      chunk_cap = (u64)ca.nblk * ca.cap;
-      ctmp.ensure(chunk_cap * sizeof(uint4));
-      csrc.ensure(chunk_cap);
-      ccnt.ensure((u64)ca.nblk * 4);
+      ccnt.ensure((u64)nblk * 4);
       cpairs.ensure(np1 * 4);
-      ca.tmp = ctmp.as<uint4>();
-      ca.src = csrc.as<uint8_t>();
       ca.cnt = ccnt.as<u32>();
       ca.pairs = cpairs.as<u32>();
+      const u32 per = (u32)std::min<u64>(nblk, kChunkSlotBytes / (kChunkSlot * ca.cap));
+      chunk_cap = (u64)per * ca.cap;
+      // (a large level's are given back with the level: the arena would keep
+      // 1.5 times as much)
+      if (chunk_cap * kChunkSlot <= kEarlyBytes) {
+        ca.tmp = static_cast<uint4 *>(ctmp.ensure(chunk_cap * sizeof(uint4)));
+        ca.src = static_cast<uint8_t *>(csrc.ensure(chunk_cap));
+      } else {
+        ca.tmp = static_cast<uint4 *>(slots.emplace_back(&A).ensure(chunk_cap * sizeof(uint4)));
+        ca.src = static_cast<uint8_t *>(slots.emplace_back(&A).ensure(chunk_cap));
+      }
+      T.at(kCount);
+      if (per == nblk) {
+        ca.nblk = nblk;
+        launch_chunk_join(la, ca, b2, key_bits, s);
+        cruns.push_back(ca);
+      } else {
+        coff.ensure(((u64)nblk + ceil_div(nblk, per)) * 8);
+        u64 *off = coff.as<u64>();
+        chunk_cap = 0;
+        for (u32 b = 0; b < nblk; b += ca.nblk) {
+          ca.first = b;
+          ca.nblk = std::min(per, nblk - b);
+          ca.cnt = ccnt.as<u32>() + b;
+          launch_chunk_join(la, ca, b2, key_bits, s);
+          ScanJob job{ca.cnt, false, off};
+          job.total_to = &dst->merged;
+          const u32 seqr = next_publication();
+          const ScanPublish pub{dst, hs_dev, (u32)(sizeof(Status) / 4),
+                                (u32)(offsetof(Status, seq) / 4), seqr};
+          exclusive_scan_lb(&job, 1, ca.nblk, lb(ca.nblk), &dst->scan_ctr, &dst->err, s, &pub);
+          wait_published(seqr);
+          const u64 n = hs->st.merged;
+          if (n) {
+            ChunkArgs run = ca;
+            run.tmp = static_cast<uint4 *>(slots.emplace_back(&A).ensure(n * sizeof(uint4)));
+            run.src = static_cast<uint8_t *>(slots.emplace_back(&A).ensure(n));
+            run.off = off;
+            launch_chunk_pack(la, ca, off, run.tmp, run.src, s);
+            cruns.push_back(run);
+            chunk_cap += n;
+          }
+          off += ca.nblk + 1;
+        }
+        slots.pop_front();  // the shared slots (stream-ordered, after the last copy)
+        slots.pop_front();
+      }
     }
     auto count_and_scan = [&](u32 seq) {
       T.at(kCount);
@@ -1058,11 +1111,11 @@ void Composer::run(fstc_result *out) {
     auto chunk_emit = [&](u64 cap, const u64 *skip_if) {
       MergeArgs m{};
       visit_args(m);
-      list_cap = std::max<u64>(std::min<u64>(cap, left_pairs), 1);
+      list_cap = std::max<u64>(scan_new ? 0 : std::min<u64>(cap, left_pairs), 1);
       newlist.ensure(list_cap * 4);
       m.newlist = newlist.as<u32>();
       m.newcap = list_cap;
-      launch_chunk_emit(m, ca, scan_new, skip_if, s);
+      for (const ChunkArgs &c : cruns) launch_chunk_emit(m, c, scan_new, skip_if, s);
       // (all of the level's new pairs so far: the list stays empty)
       if (scan_new) launch_claim_count(hvb.as<u32>(), pairspace, claim_tmp(), &dst->nnew, nullptr, s);
       chunk_emitted = true;
@@ -1086,13 +1139,13 @@ void Composer::run(fstc_result *out) {
       out_arcs.grow(arcs + room, arcs);
       MergeArgs m{};
       visit_args(m);
-      launch_chunk_compact(m, ca, aoff.as<u64>(), room, hvb.as<u32>(), out_arcs.col(0) + arcs,
-                           out_arcs.col(1) + arcs, out_arcs.col(2) + arcs, out_arcs.col(3) + arcs,
-                           reinterpret_cast<float *>(out_arcs.col(4)) + arcs, skip_if, clear, s);
+      for (const ChunkArgs &c : cruns)
+        launch_chunk_compact(m, c, aoff.as<u64>(), room, hvb.as<u32>(), out_arcs.col(0) + arcs,
+                             out_arcs.col(1) + arcs, out_arcs.col(2) + arcs, out_arcs.col(3) + arcs,
+                             reinterpret_cast<float *>(out_arcs.col(4)) + arcs, skip_if,
+                             clear && &c == &cruns.back(), s);
     };
     if (chunk) {
-      T.at(kCount);
-      launch_chunk_join(la, ca, b2, key_bits, s);
       // The claims before the host knows their number, when the visited set
       // has room for the most there can be.  A hash table may have to grow for
       // the level's other sources, whose joined pairs are not counted yet, and

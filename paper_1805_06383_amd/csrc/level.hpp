@@ -221,8 +221,11 @@ struct ChunkArgs {
                 // then (slot or id, a, c, weight bits) after launch_chunk_emit
   uint8_t *src; // [nblk cap] source of each, less the wavefront's first
   u32 *cnt;     // [nblk] merged arcs of each wavefront
+  const u64 *off;  // NULL, or (after launch_chunk_pack) wavefront b's first slot
+                   // in place of b cap
   u32 *pairs;   // [nsrc] joined pairs of each source merged here, else 0
-  u32 S, nblk, cap;  // nblk = ceil(nsrc / S); kChunkMinCap .. kChunkMaxCap
+  u32 S, cap;   // kChunkMinCap .. kChunkMaxCap
+  u32 first, nblk;  // wavefronts [first, first + nblk) of the level's ceil(nsrc / S)
 };
 // Sources per wavefront: fewer on a level that would not fill the chip's
 // 8,192 wave slots (a source's steps run one after the other in its wave).
@@ -234,6 +237,11 @@ inline u32 chunk_sources(u64 nsrc) {
 // Sets tstart / mend (into c.tmp) of the sources it merges, cnt = mc = 0.
 void launch_chunk_join(const LevelArgs &a, const ChunkArgs &c, int b2, int key_bits,
                        hipStream_t s);
+// Moves the merged arcs of c's wavefronts from their regions to tmp / src
+// without the unused slots, wavefront b's to off[b] (exclusive scan of c.cnt),
+// and its sources' tstart / mend with them.
+void launch_chunk_pack(const LevelArgs &a, const ChunkArgs &c, const u64 *off, uint4 *tmp,
+                       uint8_t *src, hipStream_t s);
 
 struct MergeArgs {
   const void *rec_key;

@@ -35,8 +35,8 @@
 // records in registers (8.3 ms).  A lane takes a record, not a match: a match
 // of 250 arc pairs copied by its lane alone held its wavefront for 100 us
 // (1,656 sources of a language model: 127 us, now 54).
-// Measured on MI355X: 15.9 M sources with 127 M records in six levels (degree
-// 8 states, 3,000 symbols) 5.3 ms, and the whole composition 19.7 -> 14.9 ms
+// Measured on MI355X: 15.9 M sources with 127 M records in six levels (states
+// of degree 20, 5,000 symbols: eight joined pairs a source) 5.3 ms, and the whole composition 19.7 -> 14.9 ms
 // against joining, scanning, emitting, expanding and tile-merging them; 29
 // levels of 320 to 816,000 sources with two records each 9.5 -> 5.6 ms; a
 // lexicon's levels of 5,000 to 44,000 sources 3.35 -> 2.30 ms.
@@ -59,7 +59,6 @@ struct ChunkLds {
   u32 l0[kChunkS + 1];                        // staged symbols of the sources before
   u32 pb1[kChunkS], pb2[kChunkS];             // first parts
   u32 e0[kChunkS + 1];                        // first element (short-list symbol)
-  u32 h0[kChunkS + 1];                        // first match of the batch
   u32 r0[kChunkS], rc[kChunkS];               // first record of the batch; records
   unsigned long long pairs[kChunkS];          // joined pairs
   u32 one[kChunkS];                           // M1's list is the shorter
@@ -203,8 +202,6 @@ __device__ __forceinline__ u32 chunk_batch(const LevelArgs &a, const ChunkArgs &
     }
     found = found && e0 + t < En;
     const u64 m = __ballot(found);
-    // sources' first matches: the lane of a source's first element
-    if (e0 + t < En && e == L.e0[i] - eb) L.h0[i] = H + count_below(m);
     if (found) {
       const u32 h = H + count_below(m);
       L.hsrc[h] = (uint8_t)i;

@@ -499,13 +499,6 @@ struct Composer {
     }
   }
 
-  void read_words(const u64 *d, int n) {
-    FSTC_HIP(hipGetLastError());
-    FSTC_HIP(hipMemcpyAsync(hs->words, d, n * sizeof(u64), hipMemcpyDeviceToHost, s));
-    FSTC_HIP(hipStreamSynchronize(s));
-    ++nsyncs;
-  }
-
   void run(fstc_result *out);
 };
 

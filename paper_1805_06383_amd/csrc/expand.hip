@@ -903,11 +903,11 @@ __global__ __launch_bounds__(kExpandNT) void k_expand(const uint4 *match, const 
 
 }  // namespace
 
-// Grids of the wavefront and workgroup joins: at most one wave (block) per
-// listed source, whose number is bounded by the frontier before the count
-// and known exactly after it.
 // Wide sources that a workgroup each takes: more would not run at once.
 constexpr u32 kWideBlocks = 1024;
+// Grids of the emission joins, whose lists' lengths are known: at most a wave
+// per wide source, at most a workgroup per chunk of a heavy one (the kernels
+// loop over the rest).
 static unsigned wide_grid(u64 n) { return (unsigned)std::min<u64>(2048, ceil_div(n, 256 / kWave)); }
 static unsigned heavy_grid(u64 n) {
   return (unsigned)std::min<u64>(512, std::min<u64>(n, kHeavySplit) * kHeavyChunks);

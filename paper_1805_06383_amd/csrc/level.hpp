@@ -381,10 +381,10 @@ void launch_fuse_merge(const MergeArgs &a, bool narrow, hipStream_t s);
 // lean: a grid for a listed-source list expected empty (the previous level
 // had none; the waves loop over the list).
 void launch_prod_sources(const MergeArgs &a, bool narrow, hipStream_t s, bool lean = false);
-// Multi-block merge of the nbig sources listed in a.big; bigoff has nbig + 1
-// entries (exclusive scan of their record counts, total RB).
 // Merge of the a.nmid sources listed from the end of a.big.
 void launch_merge_mid(const MergeArgs &a, bool wide_keys, hipStream_t s);
+// Multi-block merge of the nbig sources listed in a.big; bigoff has nbig + 1
+// entries (exclusive scan of their record counts, total RB).
 void launch_big_counts(const u64 *roff, const u32 *big, u32 nbig, u64 *bigcnt, hipStream_t s);
 void merge_big(const MergeArgs &a, bool wide_keys, u32 nbig, const u64 *bigoff, u64 RB,
                Arena &T, hipStream_t s);

@@ -13,8 +13,9 @@
 //   * a workgroup takes the whole sources whose records start in a window
 //     (at most 4096 records in all), sorts them in LDS by (source, key) with
 //     a stable radix sort ranked by wave ballots, and sums every run of
-//     equal keys in float64; sources of more than 2048 records are merged by
-//     a device-wide radix sort and a segmented reduce;
+//     equal keys in float64; sources of 2,049 to 8,192 records are sorted the
+//     same way by a workgroup each, larger ones by a device-wide radix sort
+//     and merged by a segmented reduce;
 //   * the visited set is an open-addressing hash table of 64-bit pair keys
 //     (r1 << 32 | r2) in HBM, filled with atomicCAS; a pair is looked up
 //     once per merged arc, after merging, so repeated targets cost one probe

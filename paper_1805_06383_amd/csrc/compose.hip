@@ -72,6 +72,9 @@ constexpr u64 kEarlyBytes = u64(1) << 30;
 // Largest pair space whose ordered ids are given before the host reads a
 // level's counts (a pass over the dense visited array).
 constexpr u64 kIdScanPairs = u64(1) << 22;
+// Largest pair space that is cheaper to pass over than a few new pairs are to
+// sort (see assign_ids).
+constexpr u64 kIdPassPairs = 53u * 1000 * 1000;
 // Pairs per source up to which a level finds its new pairs by a pass.
 constexpr u64 kScanPairsPerSource = 128;
 // Pairs whose visited entries fit the 4 MB L2 of an XCD: above it, the sources
@@ -739,8 +742,9 @@ void Composer::run(fstc_result *out) {
   // (a5) ids n_states, ... for the level's nnew listed pairs (count: the list's
   // length on the device).  Ordered ids: ranked in one launch up to kRankMax
   // new pairs; a larger level takes a pass over the dense visited array while
-  // that is cheaper than a radix sort (0.9 ps a pair of the array against
-  // about 60 us and 150 ps a new pair), or the sort.
+  // that is cheaper than a radix sort (9 us, 0.8 ps a pair of the array and 50
+  // ps a new one, against 52 us and 100 ps: 64 M pairs with 16,384, 131,072 and
+  // 524,288 new ones 65, 72 and 85 us against 53, 66 and 101), or the sort.
   auto assign_ids = [&](u32 nnew, u32 *slots, const u32 *count) {
     if (!nnew) return;
     u32 *q1 = sq1b.as<u32>(), *q2 = sq2b.as<u32>();
@@ -750,7 +754,7 @@ void Composer::run(fstc_result *out) {
                            q2, s);
         return;
       }
-      if (dense_vis && pairspace <= kDensePairs + 160ull * nnew) {
+      if (dense_vis && pairspace <= kIdPassPairs + 60ull * nnew) {
         launch_claim_ids(hvb.as<u32>(), pairspace, vn2, (u32)n_states, q1, q2, claim_tmp(), nullptr, s);
         return;
       }

@@ -479,9 +479,10 @@ __global__ __launch_bounds__(NT, 4) void k_merge_tiles(MergeArgs a) {
 // sort's passes one after the other in one workgroup per CU (112 KB of LDS):
 // 37 us for any number of sources up to 256.  kMergeMid is what one
 // workgroup's LDS sorts (64-bit keys, float weights).  The multi-block path
-// takes three launches per 8 key bits and ten more, 210 us at 6,306 records:
-// language model (one to four such sources in each of three levels)
-// 1.59 -> 1.47 ms, lexicon 2.30 -> 2.19 ms.
+// also sorts that many in one workgroup, but its counts, scans, gather and
+// reduction are launches of their own: lexicon 1.81 -> 1.76 ms; language models
+// (one to four such sources in each of three levels) 653 -> 648 us and the
+// same within the runs' spread at 1.22 ms.
 template <class KT>
 __global__ __launch_bounds__(kMidNT) void k_merge_mid(MergeArgs a) {
   __shared__ SortLds<kMidNT, true> L;
@@ -2177,8 +2178,9 @@ __global__ __launch_bounds__(256) void k_newlist_product(MergeArgs a) {
 // waves compare them with an eighth of the list each, staged in LDS (every
 // lane of a wave reads one address: a broadcast).  In the dense visited array
 // the slot is the pair's order, in the hash table its key.  Quadratic, but one
-// launch: a radix sort takes three launches per 8 bits of the pair, 12 to 15
-// launches (about 60 us) for any list up to a few thousand pairs.
+// launch: 512, 4,096 and 16,384 pairs of a dense array take 7, 12 and 36 us
+// against 27, 29 and 48 by keys, a radix sort and launch_assign (in the hash
+// table 8, 15 and 57 us against 37, 40 and 67); twice as many would take longer.
 // The list's length is read from *count on the device; above `cap` nothing is
 // done (the host then takes another form).
 constexpr u32 kRankNT = 512, kRankTile = 2048;

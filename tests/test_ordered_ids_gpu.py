@@ -75,6 +75,16 @@ def test_hub_levels(h1, h2, form):
         assert_same_multiset(multiset_of(h), multiset_of(ref), what=f"{h1}x{h2} {form}")
 
 
+@pytest.mark.parametrize("nq,h1,h2", [(7400, 160, 130), (8000, 160, 130)])
+def test_pass_or_sort(nq, h1, h2):
+    """More new pairs than are ranked, over a dense visited array on both sides
+    of the size from which their sort is cheaper than a pass over it."""
+    m1, m2 = hubs(h1, h2, nq, nq + 1)
+    h = compose(m1, m2).to_host()
+    check_order(h, m2.num_states)
+    assert_same(canon_of(h), canon_of(oracle.compose(m1, m2)), rtol=1e-5, what=f"{nq}")
+
+
 @pytest.mark.parametrize("slots", [1, 3, 4])
 @pytest.mark.parametrize("nq,m", [(3, 8), (9, 8), (40, 64), (70, 33)])
 def test_direct_product_levels(nq, m, slots):

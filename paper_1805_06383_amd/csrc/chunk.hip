@@ -448,11 +448,14 @@ __global__ __launch_bounds__(NT) void k_chunk_join(LevelArgs a, ChunkArgs c, int
     q2 = a.sq2[a.lo + u];
     r = Ranges{a.c1.row[q1], a.c1.row[q1 + 1], a.c2.row[q2], a.c2.row[q2 + 1]};
     const u32 pb1 = a.c1.part_base[q1], pb2 = a.c2.part_base[q2];
+    const u32 parts = a.c1.part_base[q1 + 1] - pb1 + a.c2.part_base[q2 + 1] - pb2;
     const u32 n1 = r.e1 - r.b1, n2 = r.e2 - r.b2;
     const u32 mn = min(n1, n2), mx = max(n1, n2);
     heavy = mn > kHeavyMin;
     wide = !heavy && mn > kChunkShort;
-    pk = chunk_product(a, a.prod && mn >= kProdMinSymbols && mn <= (u32)kWave, u, q1, q2, r, mf);
+    // (part counts first, which come with the part bases: most sources have too many)
+    pk = chunk_product(a, a.prod && mn >= kProdMinSymbols && mn <= (u32)kWave && parts <= kProdRowSum,
+                       u, q1, q2, r, mf);
     if (mn <= kChunkShort && !pk) E = mn;
     unfit = pk || mn > kSmallShortList || mx > kSmallLongList;
     a.tstart[u] = 0;

@@ -18,8 +18,8 @@
 #include <array>
 #include <chrono>
 #include <cstring>
-#include <deque>
 #include <functional>
+#include <memory>
 #include <mutex>
 #include <vector>
 
@@ -984,7 +984,11 @@ void Composer::run(fstc_result *out) {
                        nsrc >= kChunkMinSources;
     ChunkArgs ca{};
     std::vector<ChunkArgs> cruns;  // the level's chunk merge, in runs of wavefronts
-    std::deque<Buf> slots;         // their slots, where the arena does not hold them
+    std::vector<std::unique_ptr<Buf>> slots;  // their slots, where the arena does not hold them
+    auto own_slots = [&](u64 bytes) {
+      slots.push_back(std::make_unique<Buf>(&A));
+      return slots.back()->ensure(bytes);
+    };
     const u64 left_pairs = pairspace - n_states;  // pairs that are no states yet
     u64 chunk_cap = 0;                            // most arcs the chunk merge produces
     if (chunk) {
@@ -1009,8 +1013,8 @@ void Composer::run(fstc_result *out) {
         ca.tmp = static_cast<uint4 *>(ctmp.ensure(chunk_cap * sizeof(uint4)));
         ca.src = static_cast<uint8_t *>(csrc.ensure(chunk_cap));
       } else {
-        ca.tmp = static_cast<uint4 *>(slots.emplace_back(&A).ensure(chunk_cap * sizeof(uint4)));
-        ca.src = static_cast<uint8_t *>(slots.emplace_back(&A).ensure(chunk_cap));
+        ca.tmp = static_cast<uint4 *>(own_slots(chunk_cap * sizeof(uint4)));
+        ca.src = static_cast<uint8_t *>(own_slots(chunk_cap));
       }
       T.at(kCount);
       if (per == nblk) {
@@ -1036,8 +1040,8 @@ void Composer::run(fstc_result *out) {
           const u64 n = hs->st.merged;
           if (n) {
             ChunkArgs run = ca;
-            run.tmp = static_cast<uint4 *>(slots.emplace_back(&A).ensure(n * sizeof(uint4)));
-            run.src = static_cast<uint8_t *>(slots.emplace_back(&A).ensure(n));
+            run.tmp = static_cast<uint4 *>(own_slots(n * sizeof(uint4)));
+            run.src = static_cast<uint8_t *>(own_slots(n));
             run.off = off;
             launch_chunk_pack(la, ca, off, run.tmp, run.src, s);
             cruns.push_back(run);
@@ -1045,8 +1049,8 @@ void Composer::run(fstc_result *out) {
           }
           off += ca.nblk + 1;
         }
-        slots.pop_front();  // the shared slots (stream-ordered, after the last copy)
-        slots.pop_front();
+        slots[0]->release();  // the shared slots (stream-ordered, after the last copy)
+        slots[1]->release();
       }
     }
     auto count_and_scan = [&](u32 seq) {

@@ -944,14 +944,16 @@ namespace {
 constexpr u32 kLocMaxStates = 1u << 17;
 constexpr u64 kLocMaxAvg = 1024;
 constexpr u64 kLocAnyArcs = 1u << 16;
-// Average state up to which a small input still takes it: one tile of the
-// large class's workgroup.  (One state of 60,000 arcs, eight tiles a sort
-// pass in one workgroup, took 800 us; the global sorts take 180.)
-constexpr u64 kLocOneTile = 8192;
+// Average state up to which a small input still takes it: two tiles of the
+// large class's workgroup (both inputs of one state: 8,000 arcs 108 us, 9,000
+// 150, 16,000 225, 24,000 325, 64,000 860; the global sorts take 235 at any of
+// them.  Two and seven states of 9,000: 166 and 172, by the global sorts 232
+// and 269; three of 20,000 308 and 252).
+constexpr u64 kLocTwoTiles = 16384;
 
 bool use_local_build(u64 n, u32 nq) {
   return nq <= kLocMaxStates &&
-         (n <= kLocMaxAvg * nq || (n <= kLocAnyArcs && n <= kLocOneTile * nq));
+         (n <= kLocMaxAvg * nq || (n <= kLocAnyArcs && n <= kLocTwoTiles * nq));
 }
 
 size_t arena_bytes(std::initializer_list<size_t> sizes) {

@@ -166,10 +166,12 @@ def test_csr_grouped_by_state(fstc, nq):
 
 
 @pytest.mark.parametrize("nq,n", [(1, 8192), (1, 8193), (2, 16_384), (2, 16_385), (7, 57_345),
-                                  (1, 65_536), (1, 65_537)])
+                                  (1, 65_536), (1, 65_537), (1, 16_384), (1, 16_385),
+                                  (3, 49_152), (3, 49_153)])
 def test_csr_few_large_states(fstc, nq, n):
     """Around the line between the per-state build and the global sorts for
-    few states of up to 8,192 arcs on average."""
+    few states (16,384 arcs on average), and where the former's states take one
+    tile of 8,192 arcs or two."""
     rng = np.random.default_rng(n)
     m = W.FST(num_states=nq, start=0, num_isyms=900, num_osyms=1200,
               src=rng.integers(0, nq, n), dst=rng.integers(0, nq, n),

@@ -75,6 +75,9 @@ constexpr u64 kIdScanPairs = u64(1) << 22;
 // Largest pair space that is cheaper to pass over than a few new pairs are to
 // sort (see assign_ids).
 constexpr u64 kIdPassPairs = 53u * 1000 * 1000;
+// Entries of a direct product level from which its ids are given by that pass
+// in the default numbering too (see direct_scan).
+constexpr u64 kDirectScanEntries = u64(1) << 20;
 // Pairs per source up to which a level finds its new pairs by a pass.
 constexpr u64 kScanPairsPerSource = 128;
 // Pairs whose visited entries fit the 4 MB L2 of an XCD: above it, the sources
@@ -1256,9 +1259,13 @@ void Composer::run(fstc_result *out) {
     // table first); when the level turns out to have records it writes
     // nothing and the level takes the usual path.  An arc cap, and ordered ids
     // over a large pair space, keep the usual path.
-    // (small pair spaces in either numbering: 2 x 3.5 us a level of 10^6 pairs
-    // against 7.5 us for the per-source form, whose lanes read every entry)
-    const bool direct_scan = o.deterministic_ids || pairspace <= kIdScanPairs;
+    // Default numbering: by a pass over a small pair space (9 us for 10^6 pairs,
+    // 15 for 4 10^6) when the level's entries, which the per-source form reads
+    // all, would take longer (4 to 5 us up to 200,000 of them, 9 to 16 from
+    // 0.8 M to 5 M, 41 at 8.5 M).
+    const bool direct_scan = o.deterministic_ids ||
+                             (pairspace <= kIdScanPairs &&
+                              (u64)nsrc * maxk >= kDirectScanEntries + pairspace / 4);
     const bool direct = spec && ids_by_scan && !o.max_arcs &&
                         (arcs + (u64)nsrc * maxk) * 20 <= kEarlyBytes;
     if (spec) {

@@ -680,8 +680,9 @@ void Composer::run(fstc_result *out) {
   const bool chunk_ok = product && !o.fused_merge && key_bits <= kChunkKeyBits;
   bool chunk_pure = true;
   // a level's sources had more arc pairs than the chunk merge takes, or half of
-  // them took the product merge: the next one's are not offered to it
-  bool chunk_heavy = false, product_level = false;
+  // them took the product merge or had symbol lists too long for it: the next
+  // one's are not offered to it
+  bool chunk_heavy = false, product_level = false, wide_level = false;
   // the previous per-level level had no listed sources: the list kernels
   // get lean grids (see launch_count, launch_prod_sources)
   bool lists_empty = false, listed_empty = false;
@@ -860,7 +861,7 @@ void Composer::run(fstc_result *out) {
       expanded_levels += out_st.levels;
       new_levels += out_st.new_levels;
       small_levels += out_st.levels;
-      if (out_st.levels) last_direct = product_level = false;
+      if (out_st.levels) last_direct = product_level = wide_level = false;
       max_frontier = std::max<u64>(max_frontier, out_st.max_frontier);
       max_level_pre = std::max<u64>(max_level_pre, out_st.max_level_pre);
       if (out_st.reason == kSmallDone) break;
@@ -983,7 +984,7 @@ void Composer::run(fstc_result *out) {
     // publishes the counters as publication `seq`
     // Chunk merge: a level's sources joined and merged on the chip, S to a
     // wavefront.  What it leaves is counted by launch_count_lists.
-    const bool chunk = chunk_ok && !last_direct && !chunk_heavy && !product_level &&
+    const bool chunk = chunk_ok && !last_direct && !chunk_heavy && !product_level && !wide_level &&
                        nsrc >= kChunkMinSources;
     ChunkArgs ca{};
     std::vector<ChunkArgs> cruns;  // the level's chunk merge, in runs of wavefronts
@@ -1386,6 +1387,7 @@ void Composer::run(fstc_result *out) {
     if (R == 0 && nprod == 0 && !chunk) break;  // no arc leaves this level: no new states either
     chunk_heavy = nsrc >= kChunkMinSources && R > (u64)kChunkPer * nsrc;
     product_level = 2 * (u64)nprod >= nsrc;
+    wide_level = nsrc >= kChunkMinSources && 2 * ((u64)hs->st.nwide + hs->st.nheavy) >= nsrc;
     if (chunk && hs->st.general == 0) chunk_pure = true;  // the next level is enqueued whole
     premerge += R;
     max_level_pre = std::max(max_level_pre, R);
